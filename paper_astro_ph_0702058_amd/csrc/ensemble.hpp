@@ -289,7 +289,7 @@ __device__ void block_force_staged(const StateRW &s, int32_t lo, int32_t hi, con
                 M::fold(S, T);
             }
         }
-        for (int off = Sl >> 1; off > 0; off >>= 1) M::shfl_add(S, off);
+        lanes_add<M>(S, Sl);
         if (has && slice == 0) {
             const Out7 o = M::out(S);
 #pragma unroll
@@ -422,7 +422,7 @@ static_assert(RES_MAX <= WGL, "the resident selection takes one particle per wor
 // Returns false (n_act = 0) when the block lies beyond t_end; red and cnt are LDS scratch of
 // WGL / 64 entries each, free again when this returns.
 __device__ bool resident_select(const int64_t *tick, const int32_t *level, int32_t n,
-                                int32_t lmax, int64_t t_end, int32_t *out, int64_t *red,
+                                int32_t lmax, int64_t t_end, uint16_t *out, int64_t *red,
                                 int32_t *cnt, int32_t &n_act, int64_t &t_next) {
     const int32_t i = threadIdx.x;
     const int lane = i & 63, wave = i >> 6;
@@ -452,7 +452,7 @@ __device__ bool resident_select(const int64_t *tick, const int32_t *level, int32
         below += w < wave ? c : 0;
         total += c;
     }
-    if (f) out[below + __popcll(mask & ((1ull << lane) - 1ull))] = i;
+    if (f) out[below + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)i;
     // equal on every work-item: kept in scalar registers
     n_act = __builtin_amdgcn_readfirstlane(total);
     t_next = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(t_min >> 32)) << 32) |
@@ -468,7 +468,7 @@ __device__ bool resident_select(const int64_t *tick, const int32_t *level, int32
 // Waves whose slots are all past the block only stage.  The state is read only while staging
 // and predicting the i-particles, so the correctors need no barrier before their writes.
 template <class M>
-__device__ void resident_force_correct(const StateRW &s, const int32_t *list, int32_t n_act,
+__device__ void resident_force_correct(const StateRW &s, const uint16_t *list, int32_t n_act,
                                        int64_t t_next, typename EpsOf<M>::T eps2,
                                        typename M::Smem (&sm)[RES_NT], double eta, int32_t lmin,
                                        int32_t lmax, bool &bad, bool &clamp) {
@@ -519,7 +519,7 @@ __device__ void resident_force_correct(const StateRW &s, const int32_t *list, in
         }
     }
     if (!busy) return;
-    for (int off = Sl >> 1; off > 0; off >>= 1) M::shfl_add(S, off);
+    lanes_add<M>(S, Sl);
     if (!has || slice != 0) return;
     const Out7 o = M::out(S);
     const double a1[3] = {o.v[0], o.v[1], o.v[2]}, k1[3] = {o.v[3], o.v[4], o.v[5]};
@@ -547,7 +547,8 @@ __global__ void __launch_bounds__(WGL) run_resident(StateRW g, int32_t *active, 
     __shared__ double lx[3 * RES_MAX], lv[3 * RES_MAX], la[3 * RES_MAX], lk[3 * RES_MAX];
     __shared__ double lm[RES_MAX];
     __shared__ int64_t ltick[RES_MAX];
-    __shared__ int32_t llevel[RES_MAX], lact[RES_MAX];
+    __shared__ int32_t llevel[RES_MAX];
+    __shared__ uint16_t lact[RES_MAX];
     __shared__ int64_t red[WGL / 64];
     __shared__ int32_t wcnt[WGL / 64];
     __shared__ typename M::Smem sm[RES_NT];
@@ -715,7 +716,7 @@ __device__ void ens_item(const EnsView &e, const StateRW &st, int32_t c, int32_t
         }
         M::fold(S, T);
     }
-    for (int off = Sl >> 1; off > 0; off >>= 1) M::shfl_add(S, off);
+    lanes_add<M>(S, Sl);
     if (slice == 0 && q < n_act) {
         const Out7 o = M::out(S);
         const int32_t P = e.prow[c];

@@ -52,7 +52,8 @@ struct DevControl {
 // ------------------------------------------------------------------------------------------
 struct ForcePlan {
     int32_t n_i, n_iblk, ntiles, tps, K, items;
-    int32_t S;   // lanes sharing one i-particle (1 unless the i-list is small)
+    int32_t S;   // slices of a tile's j-slots an i-particle's lanes take (1: every lane all)
+    int32_t H;   // helper lanes per slice (quad_tile); S * H lanes share one i-particle
     int32_t ib;  // i-particles per i-block
     int64_t P;   // padded i rows of one partial plane
 };
@@ -61,24 +62,51 @@ struct ForcePlan {
 // spread over the list, up to smax lanes (at most one wave) per i.
 __host__ __device__ inline int32_t lane_split(int32_t n_i, bool allowed, int32_t smax = 64) {
     if (!allowed || n_i >= WG) return 1;
-    int32_t p2 = 1;
-    while (p2 < n_i) p2 <<= 1;
-    const int32_t S = WG / p2;
+    // WG over the least power of two not below n_i
+    const int32_t S = n_i > 1 ? WG >> (32 - __builtin_clz((uint32_t)n_i - 1)) : WG;
     return S > smax ? smax : S;
 }
 
+// How an arithmetic's lists may be spread over more lanes than lane_split gives, on launches too
+// small to fill the chip.  A lane's 256-j tile sum is a serial chain on a wave that issues one
+// instruction every four cycles however idle its SIMD is (measured: 185-200 cycles per j, 21 us
+// per tile, the same with one wave per SIMD as with four).  Predict + force of all rows, without
+// and with the spread: N = 1024 FP32 49 and 19 us, FP64 36 and 15 us; 300 rows at N = 10000 FP32
+// 33 and 19 us, double-single 164 and 32 us.
+struct Spread {
+    int32_t smax;     // most slices
+    int32_t hmax;     // 4: helper lanes keep the order of the sums (FP32); 1: none
+    int32_t fill;     // lanes per tile that fill the chip (0: lane_split alone)
+};
+
+// Slices S and helper lanes H of each of n_i rows.
+__host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, int32_t &H) {
+    S = lane_split(n_i, true, sp.smax);
+    H = 1;
+    if (n_i > sp.fill) return;  // also keeps the products below in range
+    if (sp.hmax > 1) {
+        if (S * 4 <= 64 && n_i * S * 4 <= sp.fill) H = 4;
+    } else {
+        while (S < sp.smax && n_i * S * 2 <= sp.fill) S *= 2;
+    }
+}
+
 // ib_max: WG * (i-particles per work-item).  Lists shorter than a workgroup take the lane
-// split whatever the variant (one i per group of S lanes), so that a short block costs work in
-// proportion to its length.
+// split whatever the variant (one i per group of lanes), so that a short block costs work in
+// proportion to its length.  Where the rows' lanes, on every tile, leave the chip unfilled (no
+// more than sp.fill per tile), rows take more lanes: more slices where the order of the sums is
+// free, helper lanes where the float tile sums fix it.
 __host__ __device__ inline ForcePlan make_plan(int32_t n_i, int32_t n, int32_t ib_max,
-                                               int32_t target, int32_t kmax, int32_t smax = 64) {
+                                               int32_t target, int32_t kmax,
+                                               Spread sp = Spread{64, 1, 0}) {
     ForcePlan p;
     p.n_i = n_i;
-    p.S = lane_split(n_i, true, smax);
-    const int32_t ib = p.S > 1 ? WG / p.S : ib_max;
+    p.ntiles = (n + TJ - 1) / TJ;
+    row_lanes(n_i, sp, p.S, p.H);
+    const int32_t L = p.S * p.H;
+    const int32_t ib = L > 1 ? WG / L : ib_max;
     p.ib = ib;
     p.n_iblk = (n_i + ib - 1) / ib;
-    p.ntiles = (n + TJ - 1) / TJ;
     int32_t K = p.n_iblk > 0 ? target / p.n_iblk : 1;
     if (K > kmax) K = kmax;
     if (K > p.ntiles) K = p.ntiles;
@@ -101,7 +129,7 @@ struct ForceCommon {
     int32_t ld;              // leading dimension of acc/jerk/pot
     double *partial;         // K > 1: [K][7][P]
     DevControl *ctl;         // latched flags (may be NULL)
-    int32_t smax;            // largest lane split of the arithmetic mode
+    Spread sp;               // how the arithmetic mode's lists spread over lanes
     int32_t scalar_min;      // fewest j-tiles per item read with scalar loads (float modes)
 };
 
@@ -121,6 +149,41 @@ __device__ __forceinline__ double uload(const double *p, int j) {
 __device__ __forceinline__ float4 uload(const float4 *p, int j) {
     const f4v q = ((const __attribute__((address_space(4))) f4v *)p)[j];
     return make_float4(q.x, q.y, q.z, q.w);
+}
+
+// The value that the lane OFF away (xor) holds, by DPP moves within a row of 16 lanes and the
+// row-swap instructions across rows (no LDS; a permute through LDS of the seven sums of a record
+// took 570 cycles per step of the exchange).
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t old, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, 0xf, BANKS, false);
+}
+template <int OFF>
+__device__ __forceinline__ uint32_t lane_xor_word(uint32_t v) {
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "");
+    if constexpr (OFF == 1) return dpp_mov<0xb1>(v, v);       // quad_perm [1,0,3,2]
+    else if constexpr (OFF == 2) return dpp_mov<0x4e>(v, v);  // quad_perm [2,3,0,1]
+    else if constexpr (OFF == 4)  // banks 0, 2 from four lanes up, banks 1, 3 from four down
+        return dpp_mov<0x114, 0xa>(dpp_mov<0x104, 0x5>(v, v), v);
+    else if constexpr (OFF == 8) return dpp_mov<0x128>(v, v); // row_ror 8
+    else if constexpr (OFF == 16) {  // even rows paired with odd rows
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (threadIdx.x & 16) ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return (threadIdx.x & 32) ? r[0] : r[1];
+    }
+}
+template <int OFF, class T>
+__device__ __forceinline__ T lane_xor(T v) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "");
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, lane_xor_word<OFF>(__builtin_bit_cast(uint32_t, v)));
+    } else {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const uint64_t lo = lane_xor_word<OFF>((uint32_t)u), hi = lane_xor_word<OFF>((uint32_t)(u >> 32));
+        return __builtin_bit_cast(T, lo | hi << 32);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -177,39 +240,80 @@ struct ModeF32 {
     __device__ static __forceinline__ J load_j(const Args &a, int j) {
         return J{uload(a.px, j), uload(a.py, j), uload(a.pz, j), uload(a.vm, j)};
     }
+    __device__ static __forceinline__ J lds_j(const Smem &s, int jj) {
+        return J{s.x[jj], s.y[jj], s.z[jj], s.vm[jj]};
+    }
     template <bool SOFT, bool MASK = false>
     __device__ static __forceinline__ void interact(const I &i, const Smem &s, int jj, float eps2,
                                                     Tile &T, bool self = false) {
-        pair<SOFT, MASK>(i, J{s.x[jj], s.y[jj], s.z[jj], s.vm[jj]}, eps2, T, self);
+        pair<SOFT, MASK>(i, lds_j(s, jj), eps2, T, self);
     }
+    // What one pair adds: mr to the potential sum, mr3 (dx, dy, dz) to the acceleration and
+    // mr3 (wx, wy, wz) to the jerk.
+    struct Terms {
+        float mr, mr3, dx, dy, dz, wx, wy, wz;
+    };
     // MASK: the pair may be the i-particle's own slot (self), which then adds nothing
     template <bool SOFT, bool MASK = false>
-    __device__ static __forceinline__ void pair(const I &i, const J &j, float eps2, Tile &T,
-                                                bool self = false) {
-        const float dx = (float)(j.x - i.x);
-        const float dy = (float)(j.y - i.y);
-        const float dz = (float)(j.z - i.z);
+    __device__ static __forceinline__ Terms terms(const I &i, const J &j, float eps2,
+                                                  bool self = false) {
+        Terms o;
+        o.dx = (float)(j.x - i.x);
+        o.dy = (float)(j.y - i.y);
+        o.dz = (float)(j.z - i.z);
         const float4 q = j.q;
         const float ux = q.x - i.vx;
         const float uy = q.y - i.vy;
         const float uz = q.z - i.vz;
-        const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
-        const float rv = __builtin_fmaf(dz, uz, __builtin_fmaf(dy, uy, dx * ux));
+        const float r2 = __builtin_fmaf(o.dz, o.dz, __builtin_fmaf(o.dy, o.dy, __builtin_fmaf(o.dx, o.dx, eps2)));
+        const float rv = __builtin_fmaf(o.dz, uz, __builtin_fmaf(o.dy, uy, o.dx * ux));
         float rinv = __builtin_amdgcn_rsqf(r2);
         if (!SOFT) rinv = r2 > 0.0f ? rinv : 0.0f;
         const float rinv2 = rinv * rinv;
-        float mr = q.w * rinv;
-        if (MASK) mr = self ? 0.0f : mr;
-        const float mr3 = mr * rinv2;
+        o.mr = q.w * rinv;
+        if (MASK) o.mr = self ? 0.0f : o.mr;
+        o.mr3 = o.mr * rinv2;
         const float t = -3.0f * (rv * rinv2);
-        T.p += mr;
-        T.ax = __builtin_fmaf(mr3, dx, T.ax);
-        T.ay = __builtin_fmaf(mr3, dy, T.ay);
-        T.az = __builtin_fmaf(mr3, dz, T.az);
-        T.jx = __builtin_fmaf(mr3, __builtin_fmaf(t, dx, ux), T.jx);
-        T.jy = __builtin_fmaf(mr3, __builtin_fmaf(t, dy, uy), T.jy);
-        T.jz = __builtin_fmaf(mr3, __builtin_fmaf(t, dz, uz), T.jz);
+        o.wx = __builtin_fmaf(t, o.dx, ux);
+        o.wy = __builtin_fmaf(t, o.dy, uy);
+        o.wz = __builtin_fmaf(t, o.dz, uz);
+        return o;
     }
+    template <bool SOFT, bool MASK = false>
+    __device__ static __forceinline__ void pair(const I &i, const J &j, float eps2, Tile &T,
+                                                bool self = false) {
+        const Terms o = terms<SOFT, MASK>(i, j, eps2, self);
+        T.p += o.mr;
+        T.ax = __builtin_fmaf(o.mr3, o.dx, T.ax);
+        T.ay = __builtin_fmaf(o.mr3, o.dy, T.ay);
+        T.az = __builtin_fmaf(o.mr3, o.dz, T.az);
+        T.jx = __builtin_fmaf(o.mr3, o.wx, T.jx);
+        T.jy = __builtin_fmaf(o.mr3, o.wy, T.jy);
+        T.jz = __builtin_fmaf(o.mr3, o.wz, T.jz);
+    }
+    // Adds the terms of the four lanes of a quad to every lane's T, in lane order (DPP operands
+    // take the other lanes' values; each addition is the one `pair` makes).  The four lanes of a
+    // quad hold the same T.
+#define NB_QUAD(n) " quad_perm:[" n "," n "," n "," n "] row_mask:0xf bank_mask:0xf\n"
+#define NB_QUAD_ADD(n, m)                                                                     \
+    "v_add_f32_dpp %0, %11, %0" NB_QUAD(n) "v_fmac_f32_dpp %1, %12, " m NB_QUAD(n)            \
+    "v_fmac_f32_dpp %2, %13, " m NB_QUAD(n) "v_fmac_f32_dpp %3, %14, " m NB_QUAD(n)           \
+    "v_fmac_f32_dpp %4, %15, " m NB_QUAD(n) "v_fmac_f32_dpp %5, %16, " m NB_QUAD(n)           \
+    "v_fmac_f32_dpp %6, %17, " m NB_QUAD(n)
+    __device__ static __forceinline__ void add_quad(Tile &T, const Terms &o) {
+        float m0, m1, m2, m3;
+        asm("s_nop 1\n"  // a DPP operand is read two wait states after it was written
+            "v_mov_b32_dpp %7, %18" NB_QUAD("0") "v_mov_b32_dpp %8, %18" NB_QUAD("1")
+            "v_mov_b32_dpp %9, %18" NB_QUAD("2") "v_mov_b32_dpp %10, %18" NB_QUAD("3")
+            NB_QUAD_ADD("0", "%7") NB_QUAD_ADD("1", "%8") NB_QUAD_ADD("2", "%9")
+            NB_QUAD_ADD("3", "%10")
+            : "+v"(T.p), "+v"(T.ax), "+v"(T.ay), "+v"(T.az), "+v"(T.jx), "+v"(T.jy), "+v"(T.jz),
+              "=&v"(m0), "=&v"(m1), "=&v"(m2), "=&v"(m3)
+            : "v"(o.mr), "v"(o.dx), "v"(o.dy), "v"(o.dz), "v"(o.wx), "v"(o.wy), "v"(o.wz),
+              "v"(o.mr3));
+    }
+#undef NB_QUAD_ADD
+#undef NB_QUAD
     __device__ static void fold(Sum &S, const Tile &T) {
         S.ax += (double)T.ax; S.ay += (double)T.ay; S.az += (double)T.az;
         S.jx += (double)T.jx; S.jy += (double)T.jy; S.jz += (double)T.jz;
@@ -218,12 +322,13 @@ struct ModeF32 {
     __device__ static Out7 out(const Sum &S) {
         return Out7{{S.ax, S.ay, S.az, S.jx, S.jy, S.jz, S.p}};
     }
-    // S += the same record of the lane `off` away (xor), within a wave
-    __device__ static void shfl_add(Sum &S, int off) {
-        S.ax += __shfl_xor(S.ax, off, 64); S.ay += __shfl_xor(S.ay, off, 64);
-        S.az += __shfl_xor(S.az, off, 64); S.jx += __shfl_xor(S.jx, off, 64);
-        S.jy += __shfl_xor(S.jy, off, 64); S.jz += __shfl_xor(S.jz, off, 64);
-        S.p += __shfl_xor(S.p, off, 64);
+    // S += the same record of the lane OFF away (xor), within a wave
+    template <int OFF>
+    __device__ static __forceinline__ void shfl_add(Sum &S) {
+        S.ax += lane_xor<OFF>(S.ax); S.ay += lane_xor<OFF>(S.ay);
+        S.az += lane_xor<OFF>(S.az); S.jx += lane_xor<OFF>(S.jx);
+        S.jy += lane_xor<OFF>(S.jy); S.jz += lane_xor<OFF>(S.jz);
+        S.p += lane_xor<OFF>(S.p);
     }
 };
 
@@ -316,11 +421,12 @@ struct ModeF32All {
         return Out7{{(double)S.ax, (double)S.ay, (double)S.az, (double)S.jx, (double)S.jy,
                      (double)S.jz, (double)S.p}};
     }
-    __device__ static void shfl_add(Sum &S, int off) {
-        S.ax += __shfl_xor(S.ax, off, 64); S.ay += __shfl_xor(S.ay, off, 64);
-        S.az += __shfl_xor(S.az, off, 64); S.jx += __shfl_xor(S.jx, off, 64);
-        S.jy += __shfl_xor(S.jy, off, 64); S.jz += __shfl_xor(S.jz, off, 64);
-        S.p += __shfl_xor(S.p, off, 64);
+    template <int OFF>
+    __device__ static __forceinline__ void shfl_add(Sum &S) {
+        S.ax += lane_xor<OFF>(S.ax); S.ay += lane_xor<OFF>(S.ay);
+        S.az += lane_xor<OFF>(S.az); S.jx += lane_xor<OFF>(S.jx);
+        S.jy += lane_xor<OFF>(S.jy); S.jz += lane_xor<OFF>(S.jz);
+        S.p += lane_xor<OFF>(S.p);
     }
 };
 
@@ -383,12 +489,13 @@ struct ModeF32Fixed : ModeF32 {
         for (int c = 0; c < 7; ++c)
             base[(int64_t)c * P] = __longlong_as_double(S.bad ? INT64_MIN : (long long)v[c]);
     }
-    __device__ static void shfl_add(Sum &S, int off) {
-        add(S.ax, __shfl_xor(S.ax, off, 64), S.bad); add(S.ay, __shfl_xor(S.ay, off, 64), S.bad);
-        add(S.az, __shfl_xor(S.az, off, 64), S.bad); add(S.jx, __shfl_xor(S.jx, off, 64), S.bad);
-        add(S.jy, __shfl_xor(S.jy, off, 64), S.bad); add(S.jz, __shfl_xor(S.jz, off, 64), S.bad);
-        add(S.p, __shfl_xor(S.p, off, 64), S.bad);
-        S.bad |= __shfl_xor(S.bad, off, 64);
+    template <int OFF>
+    __device__ static __forceinline__ void shfl_add(Sum &S) {
+        add(S.ax, lane_xor<OFF>(S.ax), S.bad); add(S.ay, lane_xor<OFF>(S.ay), S.bad);
+        add(S.az, lane_xor<OFF>(S.az), S.bad); add(S.jx, lane_xor<OFF>(S.jx), S.bad);
+        add(S.jy, lane_xor<OFF>(S.jy), S.bad); add(S.jz, lane_xor<OFF>(S.jz), S.bad);
+        add(S.p, lane_xor<OFF>(S.p), S.bad);
+        S.bad |= lane_xor<OFF>(S.bad);
     }
 };
 
@@ -501,14 +608,16 @@ struct ModeDS {
                      ds_to_double(S.jx), ds_to_double(S.jy), ds_to_double(S.jz),
                      ds_to_double(S.p)}};
     }
-    __device__ static ds shfl_ds(ds a, int off) {
-        return ds{__shfl_xor(a.hi, off, 64), __shfl_xor(a.lo, off, 64)};
+    template <int OFF>
+    __device__ static __forceinline__ ds shfl_ds(ds a) {
+        return ds{lane_xor<OFF>(a.hi), lane_xor<OFF>(a.lo)};
     }
-    __device__ static void shfl_add(Sum &S, int off) {
-        S.ax = ds_add(S.ax, shfl_ds(S.ax, off)); S.ay = ds_add(S.ay, shfl_ds(S.ay, off));
-        S.az = ds_add(S.az, shfl_ds(S.az, off)); S.jx = ds_add(S.jx, shfl_ds(S.jx, off));
-        S.jy = ds_add(S.jy, shfl_ds(S.jy, off)); S.jz = ds_add(S.jz, shfl_ds(S.jz, off));
-        S.p = ds_add(S.p, shfl_ds(S.p, off));
+    template <int OFF>
+    __device__ static __forceinline__ void shfl_add(Sum &S) {
+        S.ax = ds_add(S.ax, shfl_ds<OFF>(S.ax)); S.ay = ds_add(S.ay, shfl_ds<OFF>(S.ay));
+        S.az = ds_add(S.az, shfl_ds<OFF>(S.az)); S.jx = ds_add(S.jx, shfl_ds<OFF>(S.jx));
+        S.jy = ds_add(S.jy, shfl_ds<OFF>(S.jy)); S.jz = ds_add(S.jz, shfl_ds<OFF>(S.jz));
+        S.p = ds_add(S.p, shfl_ds<OFF>(S.p));
     }
 };
 
@@ -531,9 +640,11 @@ struct ModeF64 {
     struct I {
         double x, y, z, vx, vy, vz, m;
     };
-    // one 64-byte record per staged j (a single LDS address for all seven values)
-    struct Rec {
-        double x, y, z, m, vx, vy, vz, pad;
+    // one 80-byte record per staged j: a single LDS address for all seven values, 16-byte reads,
+    // and slices of consecutive j without bank conflicts (in 64-byte records every fourth j falls
+    // on the same banks: a block step's force on 132 rows at N = 5000 took 13 us against 7)
+    struct alignas(16) Rec {
+        double x, y, z, m, vx, vy, vz, pad[3];
     };
     struct Smem {
         Rec r[TJ];
@@ -550,7 +661,7 @@ struct ModeF64 {
         const bool ok = j < n;
         s.r[t] = Rec{ok ? a.px[j] : 0.0, ok ? a.py[j] : 0.0, ok ? a.pz[j] : 0.0,
                      ok ? a.pm[j] : 0.0, ok ? a.vx[j] : 0.0, ok ? a.vy[j] : 0.0,
-                     ok ? a.vz[j] : 0.0, 0.0};
+                     ok ? a.vz[j] : 0.0, {0.0, 0.0, 0.0}};
     }
     __device__ static Tile tile_zero() { return Tile{0., 0., 0., 0., 0., 0., 0.}; }
     __device__ static Sum sum_zero() { return tile_zero(); }
@@ -558,7 +669,7 @@ struct ModeF64 {
         return I{xp[0], xp[1], xp[2], vp[0], vp[1], vp[2], m};
     }
     __device__ static void put(Smem &s, int t, const double xp[3], const double vp[3], double m) {
-        s.r[t] = Rec{xp[0], xp[1], xp[2], m, vp[0], vp[1], vp[2], 0.0};
+        s.r[t] = Rec{xp[0], xp[1], xp[2], m, vp[0], vp[1], vp[2], {0.0, 0.0, 0.0}};
     }
 
     struct J {
@@ -603,13 +714,26 @@ struct ModeF64 {
     __device__ static Out7 out(const Sum &S) {
         return Out7{{S.ax, S.ay, S.az, S.jx, S.jy, S.jz, S.p}};
     }
-    __device__ static void shfl_add(Sum &S, int off) {
-        S.ax += __shfl_xor(S.ax, off, 64); S.ay += __shfl_xor(S.ay, off, 64);
-        S.az += __shfl_xor(S.az, off, 64); S.jx += __shfl_xor(S.jx, off, 64);
-        S.jy += __shfl_xor(S.jy, off, 64); S.jz += __shfl_xor(S.jz, off, 64);
-        S.p += __shfl_xor(S.p, off, 64);
+    template <int OFF>
+    __device__ static __forceinline__ void shfl_add(Sum &S) {
+        S.ax += lane_xor<OFF>(S.ax); S.ay += lane_xor<OFF>(S.ay);
+        S.az += lane_xor<OFF>(S.az); S.jx += lane_xor<OFF>(S.jx);
+        S.jy += lane_xor<OFF>(S.jy); S.jz += lane_xor<OFF>(S.jz);
+        S.p += lane_xor<OFF>(S.p);
     }
 };
+
+// Sums of the lanes that share an i-particle: L adjacent lanes in groups of H that hold the same
+// sums, combined by xor, the widest distance first.
+template <class M>
+__device__ __forceinline__ void lanes_add(typename M::Sum &S, int32_t L, int32_t H = 1) {
+    if (L > 32 && H <= 32) M::template shfl_add<32>(S);
+    if (L > 16 && H <= 16) M::template shfl_add<16>(S);
+    if (L > 8 && H <= 8) M::template shfl_add<8>(S);
+    if (L > 4 && H <= 4) M::template shfl_add<4>(S);
+    if (L > 2 && H <= 2) M::template shfl_add<2>(S);
+    if (L > 1 && H <= 1) M::template shfl_add<1>(S);
+}
 
 __device__ __forceinline__ bool finite7(const Out7 &o) {
     bool ok = true;
@@ -702,18 +826,56 @@ __device__ __forceinline__ void sums_tile(const typename M::I &ii, const typenam
     }
 }
 
-// Small i-lists: S adjacent lanes share one i-particle, lane `slice` of the group takes the
-// j-particles slice, slice + S, ... of every staged tile, and the S partial sums are combined
+// The tile sums of one slice by the four lanes of a quad (h = lane & 3): each evaluates every
+// fourth pair of the slice's j-slots slice, slice + Sl, ..., and all four add the pairs' terms in
+// slot order, so the sums are bitwise those of one lane taking the slice (56 instructions per
+// four pairs instead of 124: a tile sum on one wave takes 2.6 times less time).
+template <class M, bool SOFT, bool MASK>
+__device__ __forceinline__ void quad_tile(const typename M::I &ii, const typename M::Smem &sm,
+                                          int32_t slice, int32_t Sl, int32_t own,
+                                          typename EpsOf<M>::T eps2, typename M::Sum &S) {
+    typename M::Tile T = M::tile_zero();
+    const int32_t h = (int32_t)threadIdx.x & 3;
+    for (int32_t n = 0; n < TJ; n += 8 * Sl) {  // two quads of pairs in flight
+        const int32_t j0 = n + h * Sl + slice, j1 = j0 + 4 * Sl;
+        const typename M::Terms o0 = M::template terms<SOFT, MASK>(ii, M::lds_j(sm, j0), eps2, j0 == own);
+        const typename M::Terms o1 = M::template terms<SOFT, MASK>(ii, M::lds_j(sm, j1), eps2, j1 == own);
+        M::add_quad(T, o0);
+        M::add_quad(T, o1);
+    }
+    M::fold(S, T);
+}
+
+// One staged tile for a lane of a slice with H lanes.
+template <class M, int UNR, bool SOFT, bool HELP>
+__device__ __forceinline__ void tile_sums(const typename M::I &ii, const typename M::Smem &sm,
+                                          int32_t slice, int32_t Sl, int32_t H, int32_t own,
+                                          typename EpsOf<M>::T eps2, typename M::Sum &S) {
+    // a tile holding some lane's own slot takes the masked loop (wave-uniform branch)
+    const bool mask = SOFT && __ballot((uint32_t)own < (uint32_t)TJ) != 0;
+    if constexpr (HELP) {
+        if (H > 1) {
+            if (mask) quad_tile<M, SOFT, true>(ii, sm, slice, Sl, own, eps2, S);
+            else quad_tile<M, SOFT, false>(ii, sm, slice, Sl, own, eps2, S);
+            return;
+        }
+    }
+    if (mask) sums_tile<M, UNR, SOFT, true>(ii, sm, slice, Sl, own, eps2, S);
+    else sums_tile<M, UNR, SOFT, false>(ii, sm, slice, Sl, own, eps2, S);
+}
+
+// Short i-lists: L = S H adjacent lanes share one i-particle, its slices (of H lanes each) take
+// the j-particles slice, slice + S, ... of every staged tile, and the S partial sums are combined
 // by xor-shuffles within the wave (a fixed order) before the result is stored.
-template <class M, int UNR, bool SOFT>
+template <class M, int UNR, bool SOFT, bool HELP>
 __device__ void force_items_split(const typename M::Args &pa, const ForceCommon &fc,
                                   const ForcePlan &pl, typename M::Smem &sm, int32_t n_i,
                                   typename EpsOf<M>::T eps2) {
-    const int32_t Sl = pl.S;
-    const int32_t slice = (int32_t)threadIdx.x % Sl;
+    const int32_t Sl = pl.S, H = pl.H, L = Sl * H;
+    const int32_t slice = (int32_t)threadIdx.x % L / H;
     for (int32_t w = blockIdx.x; w < pl.items; w += gridDim.x) {
         const int32_t iblk = w / pl.K, ks = w - (w / pl.K) * pl.K;
-        const int32_t q = iblk * pl.ib + (int32_t)threadIdx.x / Sl;
+        const int32_t q = iblk * pl.ib + (int32_t)threadIdx.x / L;
         const int32_t g = q < n_i ? (fc.ilist ? fc.ilist[q] : q) : 0;
         const int32_t own = q < n_i ? g : -1;  // the i-particle's own j-slot (none on padding)
         const typename M::I ii = M::load_i(pa, g);
@@ -724,16 +886,11 @@ __device__ void force_items_split(const typename M::Args &pa, const ForceCommon 
             __syncthreads();
             M::stage(pa, sm, threadIdx.x, t * TJ + (int32_t)threadIdx.x, fc.n);
             __syncthreads();
-            // a tile holding a lane's own slot takes the masked loop (wave-uniform branch)
             const int32_t rel = own - t * TJ;
-            if (SOFT && __ballot((uint32_t)rel < (uint32_t)TJ) != 0) {
-                sums_tile<M, UNR, SOFT, true>(ii, sm, slice, Sl, rel, eps2, S);
-            } else {
-                sums_tile<M, UNR, SOFT, false>(ii, sm, slice, Sl, rel, eps2, S);
-            }
+            tile_sums<M, UNR, SOFT, HELP>(ii, sm, slice, Sl, H, rel, eps2, S);
         }
-        for (int off = Sl >> 1; off > 0; off >>= 1) M::shfl_add(S, off);
-        if (slice == 0 && q < n_i) store_result<M>(fc, pl, ks, q, S);
+        lanes_add<M>(S, L, H);
+        if ((int32_t)threadIdx.x % L == 0 && q < n_i) store_result<M>(fc, pl, ks, q, S);
     }
 }
 
@@ -855,21 +1012,19 @@ __device__ __forceinline__ void block_sums_lds(const typename M::Args &pa, int32
 // then be relative to m_i / eps rather than to the potential; with eps = 0 every pair at zero
 // separation is skipped anyway.)
 // ------------------------------------------------------------------------------------------
-// CLS only separates the symbols of full-force launches (0) and block-step launches (1) so that
-// profilers report the two launch classes apart; the code is the same.
-template <class M, int IPL, int UNR, bool SOFT, int CLS>
-__global__ void __launch_bounds__(WG) force_kernel(typename M::Args pa, ForceCommon fc) {
-    __shared__ typename M::Smem sm;
+template <class M, int IPL, int UNR, bool SOFT, bool HELP>
+__device__ __forceinline__ void force_items(const typename M::Args &pa, const ForceCommon &fc,
+                                            typename M::Smem &sm) {
     int32_t n_i = fc.n_i_max;
     if (fc.n_i_dev) {
         const int32_t d = *fc.n_i_dev;
         n_i = d < n_i ? d : n_i;
     }
     if (n_i <= 0) return;
-    const ForcePlan pl = make_plan(n_i, fc.n, WG * IPL, fc.target, fc.kmax, fc.smax);
+    const ForcePlan pl = make_plan(n_i, fc.n, WG * IPL, fc.target, fc.kmax, fc.sp);
     const auto eps2 = pa.eps2;
-    if (pl.S > 1) {
-        force_items_split<M, UNR, SOFT>(pa, fc, pl, sm, n_i, eps2);
+    if (pl.S * pl.H > 1) {
+        force_items_split<M, UNR, SOFT, HELP>(pa, fc, pl, sm, n_i, eps2);
         return;
     }
     // XCD-aware order: workgroups are dealt to the chip's 8 XCDs round-robin, so with a grid
@@ -911,6 +1066,23 @@ __global__ void __launch_bounds__(WG) force_kernel(typename M::Args pa, ForceCom
     }
 }
 
+// CLS only separates the symbols of full-force launches (0) and block-step launches (1) so that
+// profilers report the two launch classes apart; the code is the same.
+template <class M, int IPL, int UNR, bool SOFT, int CLS>
+__global__ void __launch_bounds__(WG) force_kernel(typename M::Args pa, ForceCommon fc) {
+    __shared__ typename M::Smem sm;
+    force_items<M, IPL, UNR, SOFT, false>(pa, fc, sm);
+}
+
+// The same with helper lanes for short lists.  A kernel of its own: the helpers' registers (87
+// instead of 71) cost the whole-block path two of its seven waves per SIMD (1.4 % of a gradient
+// at N = 16384), so only launches whose plans may take helpers use it.
+template <class M, bool SOFT>
+__global__ void __launch_bounds__(WG) force_kernel_helped(typename M::Args pa, ForceCommon fc) {
+    __shared__ typename M::Smem sm;
+    force_items<M, 1, 2, SOFT, true>(pa, fc, sm);
+}
+
 // Fixed-order sum over the K partial planes (deterministic; no atomics).
 // One workgroup per (64 consecutive i-rows, one of the 7 sums): wave w adds the planes
 // k = w, w + RW, w + 2 RW, ... (in four interleaved partial sums, so that four loads are in
@@ -932,7 +1104,7 @@ __global__ void __launch_bounds__(WG_REDUCE) force_reduce(ForceCommon fc, int32_
         n_i = d < n_i ? d : n_i;
     }
     if (n_i <= 0) return;
-    const ForcePlan pl = make_plan(n_i, fc.n, ib, fc.target, fc.kmax, fc.smax);
+    const ForcePlan pl = make_plan(n_i, fc.n, ib, fc.target, fc.kmax, fc.sp);
     if (pl.K == 1) return;
     const int32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int32_t units = ((n_i + 63) >> 6) * 7;
@@ -1478,7 +1650,7 @@ __global__ void __launch_bounds__(WG_REDUCE) reduce_correct_level(ForceCommon fc
     const int32_t n_act = ctl->n_act < fc.n_i_max ? ctl->n_act : fc.n_i_max;
     const int64_t t_next = ctl->t_next;
     if (n_act <= 0) return;
-    const ForcePlan pl = make_plan(n_act, fc.n, ib, fc.target, fc.kmax, fc.smax);
+    const ForcePlan pl = make_plan(n_act, fc.n, ib, fc.target, fc.kmax, fc.sp);
     const int32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int32_t c = lane / RC_ROWS, r = lane % RC_ROWS;  // c = 7: idle lanes
     const int32_t U = (n_act + RC_ROWS - 1) / RC_ROWS;

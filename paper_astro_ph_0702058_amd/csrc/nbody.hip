@@ -351,6 +351,17 @@ void launch_fixed(const ModeF32Fixed::Args &pa, const ForceCommon &fc, const Var
 // Largest lane split of a precision's force kernel (fixed-point sums: whole 64-j sub-blocks).
 int32_t smax_of(int prec) { return prec == NB_FP32_FIXED ? TJ / ModeTraits<ModeF32Fixed>::FOLD : 64; }
 
+// How the lists of a precision and variant spread over lanes on small launches: four waves per
+// SIMD fill the chip.  The float tile sums of FP32 keep their order (helper lanes, with the
+// default shape of the kernel), the paper's all-single sums have no helpers, and the other
+// arithmetics take more slices.
+Spread spread_of(const nb_ctx *c, const Variant &v) {
+    const int32_t fill = c->num_cu * 1024 / ((c->n + TJ - 1) / TJ);
+    if (c->prec == NB_FP32) return Spread{64, v.ipl == 1 && v.unroll == 2 ? 4 : 1, v.ipl == 1 && v.unroll == 2 ? fill : 0};
+    if (c->prec == NB_FP32_ALL) return Spread{64, 1, 0};
+    return Spread{smax_of(c->prec), 1, fill};
+}
+
 // Largest K * P over every i-count up to n_i_max against n j-particles, for one variant (the
 // plan depends on the count only through its number of i-blocks, and lists shorter than a
 // workgroup have the one i-block's K with fewer rows).
@@ -359,7 +370,7 @@ int64_t partial_rows_upto(int32_t n_i_max, int32_t n, const Variant &v, int32_t 
     int64_t rows = 0;
     for (int32_t nb = 1; nb <= (n_i_max + ib - 1) / ib; ++nb) {
         const ForcePlan pl = make_plan((int32_t)std::min<int64_t>((int64_t)nb * ib, n_i_max), n,
-                                       ib, v.target, v.kmax, smax);
+                                       ib, v.target, v.kmax, Spread{smax, 1, 0});
         if (pl.K > 1) rows = std::max<int64_t>(rows, (int64_t)pl.K * pl.P);
         if (pl.K == 1) break;  // K only falls as the number of i-blocks grows
     }
@@ -377,16 +388,20 @@ nb_status enqueue_force(nb_ctx *c, const Variant &v, int cls, const int32_t *ili
                         double *pot, int32_t ld, hipStream_t s, double *partial = nullptr,
                         bool second_pass = true) {
     const int32_t ib = WG * v.ipl;
-    const int32_t smax = smax_of(c->prec);
+    const Spread sp = spread_of(c, v);
     ForceCommon fc{c->n, ilist, n_i_dev, n_i_max, v.target, v.kmax, acc, jerk, pot, ld,
-                   partial ? partial : c->partial, c->ctl, smax, v.scalar_tiles};
+                   partial ? partial : c->partial, c->ctl, sp, v.scalar_tiles};
     int32_t grid;
+    bool helped;  // the plan takes helper lanes, or for a device count may take them
     if (n_i_dev) {
         // the count is known only on the device: enough workgroups for any count up to n_i_max
-        const ForcePlan full = make_plan(n_i_max, c->n, ib, v.target, v.kmax, smax);
+        // (fewer than 64 rows that may have helpers are not worth their kernel)
+        helped = sp.hmax > 1 && sp.fill >= 256;
+        const ForcePlan full = make_plan(n_i_max, c->n, ib, v.target, v.kmax, sp);
         grid = std::max(std::max(1, v.target), std::min(full.items, 65535));
     } else {
-        const ForcePlan p = make_plan(n_i_max, c->n, ib, v.target, v.kmax, smax);
+        const ForcePlan p = make_plan(n_i_max, c->n, ib, v.target, v.kmax, sp);
+        helped = p.H > 1;
         grid = std::min(p.items, 1 << 20);
     }
     grid = (grid + 7) & ~7;  // a multiple of 8: the force kernel's XCD-aware item order
@@ -400,7 +415,9 @@ nb_status enqueue_force(nb_ctx *c, const Variant &v, int cls, const int32_t *ili
     switch (c->prec) {
         case NB_FP32: {
             ModeF32::Args pa{c->js.px, c->js.py, c->js.pz, c->js.vm, (float)(c->eps * c->eps)};
-            launch_f32(pa, fc, v, soft, cls, grid, s);
+            if (helped && soft) force_kernel_helped<ModeF32, true><<<grid, WG, 0, s>>>(pa, fc);
+            else if (helped) force_kernel_helped<ModeF32, false><<<grid, WG, 0, s>>>(pa, fc);
+            else launch_f32(pa, fc, v, soft, cls, grid, s);
             break;
         }
         case NB_FP32_FIXED: {
@@ -499,7 +516,7 @@ nb_status enqueue_step(nb_ctx *c, double eta, hipStream_t s) {
     // the j-split sums and the corrector in one launch; the same ForceCommon as the force
     const Variant &v = c->var_block;
     ForceCommon fc{c->n, c->active, &c->ctl->n_act, c->n, v.target, v.kmax, c->acc1, c->jerk1,
-                   c->pot1, c->n, c->partial, c->ctl, smax_of(c->prec), v.scalar_tiles};
+                   c->pot1, c->n, c->partial, c->ctl, spread_of(c, v), v.scalar_tiles};
     const int32_t units = (c->n + RC_ROWS - 1) / RC_ROWS;
     const int32_t rgrid = (std::max(8, std::min(units, c->num_cu * 2)) + 7) & ~7;
     if (c->prec == NB_FP32_FIXED)
@@ -838,7 +855,7 @@ nb_status nb_force_noalloc(nb_ctx *c, const int32_t *i_idx, const int32_t *n_i,
     if (n_i) {
         rows = partial_rows_upto(n_i_max, c->n, v, smax);
     } else {
-        const ForcePlan pl = make_plan(n_i_max, c->n, WG * v.ipl, v.target, v.kmax, smax);
+        const ForcePlan pl = make_plan(n_i_max, c->n, WG * v.ipl, v.target, v.kmax, Spread{smax, 1, 0});
         rows = pl.K > 1 ? (int64_t)pl.K * pl.P : 0;
     }
     const size_t bytes = (size_t)rows * 7 * sizeof(double);
