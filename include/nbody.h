@@ -213,7 +213,11 @@ nb_status nb_run(nb_ctx *ctx, double eta, int64_t t_end, int64_t max_steps, int3
  * a chain of launches per step; the state is written back at the end of each launch.  The same
  * steps up to the summation order; nb_run does not write the j-particle stream then (call
  * nb_predict before a later nb_force).  NB_EINVAL for max_n outside [0, 1024] (the largest
- * state one workgroup's LDS holds). */
+ * state one workgroup's LDS holds).
+ * Larger contexts, to 65536 particles, take one cooperative launch of resident workgroups, one
+ * or more per 256 particles, under the same conditions (max_n > 0, eps > 0, those arithmetics)
+ * and with use_graph != 0: the same sums as the launch chain's, the j-particle stream written.
+ * A block too large for it takes the chain.  max_n = 0 keeps every context on the chain. */
 nb_status nb_set_resident(nb_ctx *ctx, int32_t max_n);
 
 /* Sec. 4.2 energy diagnostic, synchronising: kinetic sum m v^2 / 2 and softened potential

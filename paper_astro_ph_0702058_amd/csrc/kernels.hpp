@@ -38,11 +38,12 @@ struct DevControl {
     int32_t flag_dtmin;     // latched: the criterion asked for a step below 2^-lmax
     // fused block step
     int32_t flag_sched;     // latched: a particle's next time preceded the block time
-    int32_t pad_;
+    int32_t flag_wait;      // latched: the workgroups of a tiled run did not meet
     int32_t hist[64];       // particles per level
     // fused selection: block members appended so far (low word) and chunks finished (high
     // word); zero between steps
     uint64_t sel;
+    int32_t tile_steps;     // block steps the last tiled launch took
 };
 
 // ------------------------------------------------------------------------------------------
@@ -1261,7 +1262,7 @@ __global__ void __launch_bounds__(WG) reset_control(DevControl *ctl) {
         ctl->t_cur = 0; ctl->t_next = 0; ctl->t_end = INT64_MAX; ctl->n_steps = 0;
         ctl->n_active_sum = 0; ctl->n_act = 0; ctl->flags = 0; ctl->t_cand = 0;
         ctl->n_pending = 0; ctl->done = 0; ctl->flag_nonfinite = 0; ctl->flag_dtmin = 0;
-        ctl->flag_sched = 0; ctl->sel = 0;
+        ctl->flag_sched = 0; ctl->flag_wait = 0; ctl->sel = 0; ctl->tile_steps = 0;
     }
 }
 
@@ -1313,9 +1314,10 @@ __device__ __forceinline__ bool correct_particle(const StateRW &s, int32_t i, do
                                                  const double a1v[3], const double k1v[3],
                                                  double pot1, int64_t t_new, double *crit,
                                                  double *crit_num = nullptr,
-                                                 double *crit_den = nullptr) {
+                                                 double *crit_den = nullptr,
+                                                 double idt = 0.0) {
     const int32_t n = s.n;
-    const double idt = 1.0 / dt;  // a power of two: exact
+    if (idt == 0.0) idt = 1.0 / dt;  // a power of two: exact
     const double dt2 = dt * dt, dt3 = dt2 * dt, dt4 = dt3 * dt, dt5 = dt4 * dt;
     double na1 = 0.0, nk1 = 0.0, na2p = 0.0, na3 = 0.0;
     bool ok = true;

@@ -19,6 +19,7 @@
 #include "adjoint.hpp"
 #include "ensemble.hpp"
 #include "kernels.hpp"
+#include "tiles.hpp"
 
 using namespace nbody;
 
@@ -103,6 +104,10 @@ struct nb_ctx {
     int32_t sched_groups = 1, sched_chunk = 1;
     int32_t fused_groups = 1, fused_chunk = 1;  // chunks of the fused step's count + predict
     int32_t resident_max = 1024;         // nb_run: one resident workgroup up to this n
+    // nb_run above that: one cooperative launch of tile owners (tiles.hpp)
+    bool tiles_ok = true;                // cleared when the device refuses the launch
+    uint64_t tile_epoch = 1;             // first epoch of the next launch
+    uint64_t *tile_word = nullptr, *tile_arrive = nullptr;
     Variant var_full{2, 2, 4096, 256, 16};   // calls on (nearly) all particles
     Variant var_block{2, 2, 4096, 256, 16};  // block-step calls (device-resident count)
     int32_t max_target = 4096;           // partial planes are sized for targets up to this
@@ -557,11 +562,53 @@ nb_status enqueue_resident(nb_ctx *c, double eta, int32_t steps, hipStream_t s) 
     return NB_OK;
 }
 
+// nb_run's tiled path: contexts of more particles than one workgroup holds and of at most one
+// tile per compute unit, softened, in the FP32, double-single or FP64 arithmetic.
+bool use_tiles(const nb_ctx *c) {
+    return c->tiles_ok && c->resident_max > 0 && c->n > RES_MAX && !c->profile &&
+           (c->n + TJ - 1) / TJ <= std::min<int32_t>(TL_TILES, c->num_cu) && c->eps > 0.0 &&
+           (c->prec == NB_FP32 || c->prec == NB_DS || c->prec == NB_FP64);
+}
+
+// Up to `steps` block steps in one cooperative launch.  false in `launched`: the device refused
+// it (the caller goes on with the launch chain).
+nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, bool &launched) {
+    TilesArgs a;
+    a.T = (c->n + TJ - 1) / TJ;
+    a.R = std::max(1, std::min(c->num_cu / a.T, TL_REPS));
+    // blocks of more rows (in LDS: the row map; in the partial planes, held twice) go to the chain
+    const int64_t room = c->partial_rows * 7 / (2 * (int64_t)a.T * TL_WORDS);
+    a.limit = (int32_t)std::min<int64_t>(room, TL_ROWS);
+    a.steps = steps;
+    a.epoch = c->tile_epoch;
+    c->tile_epoch += (uint64_t)steps + 2;
+    a.word = c->tile_word; a.arrive = c->tile_arrive;
+    // records in the energy's and the adjoint's scratch (8 and 12 doubles per particle), which
+    // hold nothing between calls
+    a.rec[0] = c->exp_; a.rec[1] = c->adj;
+    a.part = c->partial;
+    a.active = c->active; a.js = c->js; a.ctl = c->ctl;
+    a.eps2 = c->eps * c->eps; a.eta = eta; a.lmin = c->lmin; a.lmax = c->lmax;
+    a.sp = spread_of(c, Variant{1, 2, 0, 0, 0});
+    a.g = state_rw(c);
+    void *args[] = {&a};
+    const void *f = c->prec == NB_FP32 ? (const void *)run_tiles<ModeF32, 4>
+                  : c->prec == NB_DS ? (const void *)run_tiles<ModeDS, 1>
+                                     : (const void *)run_tiles<ModeF64, 2>;
+    launched = hipLaunchCooperativeKernel(f, dim3(a.T * a.R), dim3(TL_WG), args, 0, s) == hipSuccess;
+    if (!launched) {
+        (void)hipGetLastError();
+        c->tiles_ok = false;
+    }
+    return NB_OK;
+}
+
 nb_status latched(nb_ctx *c) {
     DevControl h;
     HIP_OK(c, hipMemcpyAsync(&h, c->ctl, sizeof h, hipMemcpyDeviceToHost, c->stream));
     HIP_OK(c, hipStreamSynchronize(c->stream));
     if (h.flag_nonfinite) return fail(c, NB_ENONFINITE, "non-finite force or state on device");
+    if (h.flag_wait) return fail(c, NB_EDEVICE, "the workgroups of a tiled run did not meet");
     if (h.flag_sched)
         return fail(c, NB_ESTATE, "block selection: a particle's next time preceded the block time");
     if (h.flag_dtmin) return fail(c, NB_EDTMIN, "time step below 2^-%d requested (clamped)", c->lmax);
@@ -670,6 +717,8 @@ size_t ctx_layout(nb_ctx *c, char *base) {
     c->adj_flag = k.take<int32_t>(4);
     c->t_zero = k.take<int64_t>(1);
     c->tune_n = k.take<int32_t>(1);
+    c->tile_word = k.take<uint64_t>(3 * TL_TILES);  // published words, then arrivals
+    c->tile_arrive = base ? c->tile_word + 2 * TL_TILES : nullptr;
     return k.off;
 }
 
@@ -736,6 +785,9 @@ nb_status nb_bind_scratch(nb_ctx *c, void *scratch, size_t bytes) {
     ctx_layout(c, (char *)scratch);
     zero_words<<<1, WG, 0, c->stream>>>(c->t_zero, 2, c->adj_flag, 4);
     LAUNCH_OK(c);
+    zero_words<<<1, WG, 0, c->stream>>>((int64_t *)c->tile_word, 3 * TL_TILES, nullptr, 0);
+    LAUNCH_OK(c);
+    c->tile_epoch = 1;
     reset_control<<<1, WG, 0, c->stream>>>(c->ctl);
     LAUNCH_OK(c);
     c->scratch_ok = true;
@@ -925,23 +977,47 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
                                                                     eta, c->lmin, c->lmax, c->ctl);
         LAUNCH_OK(c);
     }
+    const bool tiles = use_graph && use_tiles(c);
+    // a block too large for the tiled path ends its launch and takes the launch chain: for one
+    // step, or for ever longer stretches while such blocks come within a few steps of each other
+    int32_t chain_left = 0, stretch = 1;
     int64_t done_steps = 0;
     for (;;) {
         int32_t k = chunk;
         if (max_steps > 0) k = (int32_t)std::min<int64_t>(k, max_steps - done_steps);
         if (k <= 0) break;
+        bool tiled = false;
         if (resident) {
             if ((r = enqueue_resident(c, eta, k, c->stream)) != NB_OK) return r;
             c->predicted = false;  // the j-particle stream was not written
-        } else if ((r = nb_step(c, eta, k, use_graph)) != NB_OK) {
-            return r;
+        } else {
+            if (tiles && chain_left == 0 && c->tiles_ok)
+                if ((r = enqueue_tiles(c, eta, k, c->stream, tiled)) != NB_OK) return r;
+            if (tiled) {
+                c->predicted = true;
+            } else {
+                if (chain_left > 0) k = std::min(k, chain_left);
+                if ((r = nb_step(c, eta, k, use_graph)) != NB_OK) return r;
+                chain_left = std::max(0, chain_left - k);
+            }
         }
-        done_steps += k;
+        if (!tiled) {
+            done_steps += k;
+            if (tiles && k == 1 && chain_left == 0) continue;  // the next tiled launch sees `done`
+        }
         DevControl h;
         HIP_OK(c, hipMemcpyAsync(&h, c->ctl, sizeof h, hipMemcpyDeviceToHost, c->stream));
         HIP_OK(c, hipStreamSynchronize(c->stream));
         if (h.flag_nonfinite) return fail(c, NB_ENONFINITE, "non-finite force or state on device");
+        if (h.flag_wait) return fail(c, NB_EDEVICE, "the workgroups of a tiled run did not meet");
         if (h.done) break;
+        if (tiled) {
+            done_steps += h.tile_steps;
+            if (h.tile_steps < k) {
+                stretch = h.tile_steps < 8 ? std::min(stretch * 2, 1024) : 1;
+                chain_left = stretch;
+            }
+        }
     }
     // leave the scheduler open-ended again
     set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, INT64_MAX);
