@@ -54,7 +54,7 @@ struct EnsView {
 // Lanes per block particle of a cluster's force items: the lane split of its block, at least
 // smin (smaller items, for balance across the GPU).
 __host__ __device__ __forceinline__ int32_t ens_split(int32_t n_act, int32_t smin) {
-    const int32_t S = lane_split(n_act, true);
+    const int32_t S = lane_split(n_act);
     return S < smin ? smin : S;
 }
 

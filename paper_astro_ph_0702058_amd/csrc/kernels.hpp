@@ -59,12 +59,12 @@ struct ForcePlan {
     int64_t P;   // padded i rows of one partial plane
 };
 
-// Lanes per i-particle for a list of n_i with one i per work-item: the whole workgroup is
+// Lanes per i-particle for a list of n_i with one i per work-item: a workgroup of wg lanes is
 // spread over the list, up to smax lanes (at most one wave) per i.
-__host__ __device__ inline int32_t lane_split(int32_t n_i, bool allowed, int32_t smax = 64) {
-    if (!allowed || n_i >= WG) return 1;
-    // WG over the least power of two not below n_i
-    const int32_t S = n_i > 1 ? WG >> (32 - __builtin_clz((uint32_t)n_i - 1)) : WG;
+__host__ __device__ inline int32_t lane_split(int32_t n_i, int32_t smax = 64, int32_t wg = WG) {
+    if (n_i >= wg) return 1;
+    // wg over the least power of two not below n_i
+    const int32_t S = n_i > 1 ? wg >> (32 - __builtin_clz((uint32_t)n_i - 1)) : wg;
     return S > smax ? smax : S;
 }
 
@@ -78,11 +78,12 @@ struct Spread {
     int32_t smax;     // most slices
     int32_t hmax;     // 4: helper lanes keep the order of the sums (FP32); 1: none
     int32_t fill;     // lanes per tile that fill the chip (0: lane_split alone)
+    int32_t wg = WG;  // lanes that lane_split spreads over a list
 };
 
 // Slices S and helper lanes H of each of n_i rows.
 __host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, int32_t &H) {
-    S = lane_split(n_i, true, sp.smax);
+    S = lane_split(n_i, sp.smax, sp.wg);
     H = 1;
     if (n_i > sp.fill) return;  // also keeps the products below in range
     if (sp.hmax > 1) {

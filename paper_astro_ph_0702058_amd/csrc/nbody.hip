@@ -562,11 +562,18 @@ nb_status enqueue_resident(nb_ctx *c, double eta, int32_t steps, hipStream_t s) 
     return NB_OK;
 }
 
-// nb_run's tiled path: contexts of more particles than one workgroup holds and of at most one
-// tile per compute unit, softened, in the FP32, double-single or FP64 arithmetic.
+// nb_run's tiled path: softened contexts of at most one tile per compute unit in the FP32,
+// double-single or FP64 arithmetic; from tiles_least(prec) particles, below which one resident
+// workgroup steps faster, or where that path is switched off, from the first it does not hold.
+// Per block step in one workgroup and tiled (MI355X): FP32 N = 512 10.5 and 11.6 us, N = 513
+// (other blocks) 13.6 and 11.9, N = 1024 21.5 and 12.6; FP64 N = 300 10.9 and 12.8, N = 400 15.1
+// and 14.5; double-single N = 256 22.6 and 24.8, N = 300 26.3 and 16.3.
+int32_t tiles_least(int prec) { return prec == NB_DS ? 257 : prec == NB_FP64 ? 401 : 513; }
+
 bool use_tiles(const nb_ctx *c) {
-    return c->tiles_ok && c->resident_max > 0 && c->n > RES_MAX && !c->profile &&
-           (c->n + TJ - 1) / TJ <= std::min<int32_t>(TL_TILES, c->num_cu) && c->eps > 0.0 &&
+    return c->tiles_ok && c->resident_max > 0 && !c->profile && c->eps > 0.0 &&
+           c->n >= (c->n <= c->resident_max ? tiles_least(c->prec) : RES_MAX + 1) &&
+           (c->n + TJ - 1) / TJ <= std::min<int32_t>(TL_TILES, c->num_cu) &&
            (c->prec == NB_FP32 || c->prec == NB_DS || c->prec == NB_FP64);
 }
 
@@ -590,6 +597,7 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     a.active = c->active; a.js = c->js; a.ctl = c->ctl;
     a.eps2 = c->eps * c->eps; a.eta = eta; a.lmin = c->lmin; a.lmax = c->lmax;
     a.sp = spread_of(c, Variant{1, 2, 0, 0, 0});
+    if (c->n <= RES_MAX) a.sp.wg = WGL;  // the slices of the resident workgroup
     a.g = state_rw(c);
     void *args[] = {&a};
     const void *f = c->prec == NB_FP32 ? (const void *)run_tiles<ModeF32, 4>
@@ -657,6 +665,11 @@ void ctx_plan(nb_ctx *c) {
         const ForcePlan pv = make_plan(n, n, WG, c->num_cu * BLOCK_ITEMS_PER_CU, 1 << 16);
         rows = std::max<int64_t>(rows, (int64_t)pv.K * pv.P);
     }
+    // the tiled path: the partial sums of every block row on every tile, held twice, up to 64
+    // tiles (larger contexts take the room there is)
+    const int64_t T = (n + TJ - 1) / TJ;
+    if (T <= 64)
+        rows = std::max<int64_t>(rows, (2 * T * std::min<int64_t>(n, TL_ROWS) * TL_WORDS + 6) / 7);
     c->partial_rows = rows;
     const int64_t N = n;
     c->sched_groups = (int32_t)std::min<int64_t>(std::max<int64_t>((N + 4095) / 4096, 1), 1024);
@@ -971,13 +984,13 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
     if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, NB_EINVAL, "eta must be > 0");
     set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, t_end);
     LAUNCH_OK(c);
+    const bool tiles = use_tiles(c) && (use_graph || c->n <= RES_MAX);
     const bool resident = use_resident(c) && !c->profile;
-    if (resident) {  // new levels of a block corrected by a separate nb_correct
+    if (resident || tiles) {  // new levels of a block corrected by a separate nb_correct
         sched_newlevel<<<grid_for(c->n, 2048), WG, 0, c->stream>>>(state_rw(c), c->active, c->crit,
                                                                     eta, c->lmin, c->lmax, c->ctl);
         LAUNCH_OK(c);
     }
-    const bool tiles = use_graph && use_tiles(c);
     // a block too large for the tiled path ends its launch and takes the launch chain: for one
     // step, or for ever longer stretches while such blocks come within a few steps of each other
     int32_t chain_left = 0, stretch = 1;
@@ -987,20 +1000,19 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
         if (max_steps > 0) k = (int32_t)std::min<int64_t>(k, max_steps - done_steps);
         if (k <= 0) break;
         bool tiled = false;
-        if (resident) {
-            if ((r = enqueue_resident(c, eta, k, c->stream)) != NB_OK) return r;
-            c->predicted = false;  // the j-particle stream was not written
-        } else {
-            if (tiles && chain_left == 0 && c->tiles_ok)
-                if ((r = enqueue_tiles(c, eta, k, c->stream, tiled)) != NB_OK) return r;
-            if (tiled) {
-                c->predicted = true;
-            } else {
-                if (chain_left > 0) k = std::min(k, chain_left);
-                if ((r = nb_step(c, eta, k, use_graph)) != NB_OK) return r;
-                chain_left = std::max(0, chain_left - k);
-            }
+        if (tiles && chain_left == 0 && c->tiles_ok &&
+            (r = enqueue_tiles(c, eta, k, c->stream, tiled)) != NB_OK)
+            return r;
+        if (!tiled) {
+            if (chain_left > 0) k = std::min(k, chain_left);
+            if ((r = resident ? enqueue_resident(c, eta, k, c->stream)
+                              : nb_step(c, eta, k, use_graph)) != NB_OK)
+                return r;
+            chain_left = std::max(0, chain_left - k);
         }
+        // the resident workgroup does not write the j-particle stream; nor may a force follow a
+        // run that could have taken it
+        c->predicted = !resident;
         if (!tiled) {
             done_steps += k;
             if (tiles && k == 1 && chain_left == 0) continue;  // the next tiled launch sees `done`

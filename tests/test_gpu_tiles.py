@@ -66,6 +66,55 @@ def test_blocks_too_large_for_the_tiled_path(n, lmin):
     _same(a, _run(n, "fp32", 0, lmin, calls))
 
 
+@pytest.mark.parametrize("n", [1300, 9000])
+def test_pending_levels_before_a_tiled_run(n):
+    """A block corrected by the separate calls has its new levels before the first tiled step."""
+    out = []
+    for resident in (1024, 0):
+        x, v, m = plummer(n, 5)
+        st = nbody.DeviceState(x, v, m)
+        with nbody.Context(n, 1 / 256, precision="fp64") as ctx:
+            ctx.nb_set_resident(resident)
+            ctx.nb_bind(st)
+            ctx.nb_init(0.01)
+            acc = torch.zeros((3, n), dtype=torch.float64, device="cuda")
+            jerk, pot = torch.zeros_like(acc), torch.zeros(n, dtype=torch.float64, device="cuda")
+            idx, cnt = ctx.nb_active()
+            ctx.nb_predict()
+            ctx.nb_force(acc, jerk, pot, i_idx=idx, n_i=cnt, n_i_max=n)
+            ctx.nb_correct(acc, jerk, pot)
+            ctx.nb_run(0.01, 1 / 256)
+            c = ctx.nb_read_control()
+            out.append((c.n_steps, c.n_active_sum, st.numpy()))
+    (sa, aa, ga), (sb, ab, gb) = out
+    assert sa == sb > 5 and aa == ab
+    for key in ga:
+        assert np.array_equal(ga[key], gb[key]), key
+
+
+@pytest.mark.parametrize("prec,n", [("ds", 257), ("fp64", 401), ("fp64", 1024), ("ds", 1000)])
+def test_small_sets_tiled(prec, n):
+    """Sets that one workgroup could hold take its slices (1024 lanes over the block) on the tiled
+    path, so their sums differ from the launch chain's in order: the same steps, and coordinates
+    within 8 ulp of the largest (16: 1.8e-15), far above what the forces' rounding moves them in
+    t = 1/64 (1e-14 of an acceleration of order 10 over t^2 / 2: 1e-17)."""
+    out = []
+    for resident in (1024, 0):
+        x, v, m = plummer(n, 17)
+        st = nbody.DeviceState(x, v, m)
+        with nbody.Context(n, 1 / 256, lmin=6, precision=prec) as ctx:
+            ctx.nb_set_resident(resident)
+            ctx.nb_bind(st)
+            ctx.nb_init(0.01)
+            ctx.nb_run(0.01, 1 / 64)
+            c = ctx.nb_read_control()
+            out.append((c.n_steps, c.n_active_sum, st.numpy()))
+    (sa, aa, ga), (sb, ab, gb) = out
+    assert sa == sb > 10 and aa == ab
+    assert np.array_equal(ga["tick"], gb["tick"]) and np.array_equal(ga["level"], gb["level"])
+    assert np.max(np.abs(ga["x"] - gb["x"])) < 1.5e-14
+
+
 def test_tiled_runs_from_two_threads():
     """Two contexts on streams of their own, each wanting every compute unit: the cooperative
     launches never wait for each other half resident, and each run ends as it does alone."""
