@@ -741,84 +741,72 @@ __global__ void __launch_bounds__(WG) ens_force(EnsView e, StateRW st) {
     }
 }
 
-// Energy of every cluster at its current time (FP64): one workgroup per cluster, pair sums
-// with Neumaier compensation; cluster particles predicted to the cluster's t_cur.
-__global__ void __launch_bounds__(WG) ens_energy(EnsView e, StateRW s, double *ekin,
-                                                 double *epot) {
-    __shared__ double sx[TJ], sy[TJ], sz[TJ], smm[TJ];
-    __shared__ double rk[WG], rp[WG];
-    const int32_t c = blockIdx.x;
-    if (c >= e.C) return;
-    const int32_t p0 = e.off[c], n_c = e.off[c + 1] - p0;
+// Energy of every cluster at its current time (FP64), particles predicted to the cluster's t_cur
+// as they are loaded.  ens_energy_items: workgroup (x, y) takes the blocks y, y + gridDim.y, ...
+// of WG rows of the x-th largest cluster, each row against the particles j > i of its cluster
+// (each pair once), and leaves the compensated sums of m_i |v_i|^2 / 2 and m_i m_j s^-1/2 per
+// block in the cluster's partial planes; ens_energy_sum adds a cluster's blocks in order.  (One
+// workgroup per cluster over every ordered pair: 7.4 ms for 512 clusters of up to 4096.)
+__global__ void __launch_bounds__(WG) ens_energy_items(EnsView e, StateRW s) {
+    __shared__ double4 sm[TJ];
+    __shared__ Sum2 red[WG / 64];
+    const int32_t c = e.order[blockIdx.x];
+    const int32_t p0 = e.off[c], n_c = e.off[c + 1] - p0, T = (n_c + TJ - 1) / TJ;
     const int64_t t = e.cl[c].t_cur;
     const double eps2 = e.eps2[c];
-    double kin = 0.0, kc = 0.0, pot = 0.0, pc = 0.0;
-    for (int32_t i0 = 0; i0 < n_c; i0 += WG) {
-        const int32_t il = i0 + threadIdx.x;
-        const int32_t i = p0 + (il < n_c ? il : 0);
-        const double D = (double)(t - s.tick[i]) * s.tick_len;
-        double xi[3], vi[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const int64_t ix = k * (int64_t)s.n + i;
-            predict_one(D, s.x[ix], s.v[ix], s.a[ix], s.k[ix], xi[k], vi[k]);
-        }
-        double w = 0.0, wc = 0.0;
-        for (int32_t j0 = 0; j0 < n_c; j0 += TJ) {
+    for (int32_t blk = blockIdx.y; blk < T; blk += gridDim.y) {
+        const int32_t i[1] = {blk * WG + (int32_t)threadIdx.x};
+        const int32_t g = p0 + (i[0] < n_c ? i[0] : 0);
+        double xi[1][3], vi[3];
+        predicted(s, g, t, xi[0], vi);
+        Sum2 w{0.0, 0.0};
+        for (int32_t tj = blk; tj < T; ++tj) {
             __syncthreads();
-            const int32_t jl = j0 + threadIdx.x;
+            const int32_t jl = tj * TJ + (int32_t)threadIdx.x;
+            double xj[3] = {0.0, 0.0, 0.0}, vj[3], mj = 0.0;
             if (jl < n_c) {
-                const int32_t j = p0 + jl;
-                const double Dj = (double)(t - s.tick[j]) * s.tick_len;
-                double xj[3], vj[3];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const int64_t ix = k * (int64_t)s.n + j;
-                    predict_one(Dj, s.x[ix], s.v[ix], s.a[ix], s.k[ix], xj[k], vj[k]);
-                }
-                sx[threadIdx.x] = xj[0]; sy[threadIdx.x] = xj[1]; sz[threadIdx.x] = xj[2];
-                smm[threadIdx.x] = s.m[j];
-            } else {
-                sx[threadIdx.x] = 0.0; sy[threadIdx.x] = 0.0; sz[threadIdx.x] = 0.0;
-                smm[threadIdx.x] = 0.0;
+                predicted(s, p0 + jl, t, xj, vj);
+                mj = s.m[p0 + jl];
             }
+            sm[threadIdx.x] = double4{xj[0], xj[1], xj[2], mj};
             __syncthreads();
-            double ts = 0.0;
-            const int32_t cnt = n_c - j0 < TJ ? n_c - j0 : TJ;
-            for (int jj = 0; jj < cnt; ++jj) {
-                const double dx = sx[jj] - xi[0], dy = sy[jj] - xi[1], dz = sz[jj] - xi[2];
-                const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, __builtin_fma(dx, dx, eps2)));
-                ts += (j0 + jj == il) ? 0.0 : smm[jj] * rsqrt_f64(r2);
-            }
-            const double y = w + ts;
-            wc += __builtin_fabs(w) >= __builtin_fabs(ts) ? (w - y) + ts : (ts - y) + w;
-            w = y;
+            double ts[1] = {0.0};
+            if (tj == blk) energy_tile<1, true, true>(sm, tj * TJ, 0, 1, xi, i, eps2, ts);
+            else energy_tile<1, true, false>(sm, tj * TJ, 0, 1, xi, i, eps2, ts);
+            w.add(ts[0]);
         }
-        if (il < n_c) {
-            const double mi = s.m[i];
-            const double pe = mi * (w + wc);
-            const double ke = 0.5 * mi * __builtin_fma(vi[2], vi[2], __builtin_fma(vi[1], vi[1], vi[0] * vi[0]));
-            double y = pot + pe;
-            pc += __builtin_fabs(pot) >= __builtin_fabs(pe) ? (pot - y) + pe : (pe - y) + pot;
-            pot = y;
-            y = kin + ke;
-            kc += __builtin_fabs(kin) >= __builtin_fabs(ke) ? (kin - y) + ke : (ke - y) + kin;
-            kin = y;
+        Sum2 kin{0.0, 0.0}, pot{0.0, 0.0};
+        if (i[0] < n_c) {
+            const double mi = s.m[g];
+            kin.s = 0.5 * mi * __builtin_fma(vi[2], vi[2], __builtin_fma(vi[1], vi[1], vi[0] * vi[0]));
+            pot.s = mi * (w.s + w.c);
         }
+        kin = wg_sum2<WG>(kin, red);
+        pot = wg_sum2<WG>(pot, red);
+        if (threadIdx.x == 0) {
+            Sum2 *out = (Sum2 *)(e.partial + e.part_off[c]) + 2 * blk;  // 7 n_c T FP64 are there
+            out[0] = kin;
+            out[1] = pot;
+        }
+        __syncthreads();  // red and sm are written again
     }
-    rk[threadIdx.x] = kin + kc;
-    rp[threadIdx.x] = pot + pc;
-    __syncthreads();
-    for (int o = WG / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            rk[threadIdx.x] += rk[threadIdx.x + o];
-            rp[threadIdx.x] += rp[threadIdx.x + o];
-        }
-        __syncthreads();
+}
+
+__global__ void __launch_bounds__(64) ens_energy_sum(EnsView e, double *ekin, double *epot) {
+    const int32_t c = blockIdx.x;
+    const int32_t T = (e.off[c + 1] - e.off[c] + TJ - 1) / TJ;
+    const Sum2 *in = (const Sum2 *)(e.partial + e.part_off[c]);
+    Sum2 kin{0.0, 0.0}, pot{0.0, 0.0};
+    __shared__ Sum2 red[1];
+    for (int32_t b = threadIdx.x; b < T; b += 64) {
+        kin.join(in[2 * b]);
+        pot.join(in[2 * b + 1]);
     }
+    kin = wg_sum2<64>(kin, red);
+    pot = wg_sum2<64>(pot, red);
     if (threadIdx.x == 0) {
-        ekin[c] = rk[0];
-        epot[c] = -0.5 * rp[0];
+        ekin[c] = kin.s + kin.c;
+        epot[c] = -(pot.s + pot.c);
     }
 }
 

@@ -1785,87 +1785,177 @@ __global__ void __launch_bounds__(WG) fma_probe(int32_t iters, float m, float dm
 // ------------------------------------------------------------------------------------------
 // Sec. 4.2 energy diagnostic (FP64).
 // ------------------------------------------------------------------------------------------
+// A compensated sum s + c.  add: Neumaier's step; join: the sum of two.
+struct Sum2 {
+    double s, c;
+    __device__ __forceinline__ void add(double v) {
+        const double y = s + v;
+        c += __builtin_fabs(s) >= __builtin_fabs(v) ? (s - y) + v : (v - y) + s;
+        s = y;
+    }
+    __device__ __forceinline__ void join(Sum2 o) {
+        add(o.s);
+        c += o.c;
+    }
+};
+
+// The sum of every work-item's v, in a fixed order; valid in work-item 0.
+template <int BS>
+__device__ __forceinline__ Sum2 wg_sum2(Sum2 v, Sum2 *red) {
+    v.join(Sum2{lane_xor<32>(v.s), lane_xor<32>(v.c)});
+    v.join(Sum2{lane_xor<16>(v.s), lane_xor<16>(v.c)});
+    v.join(Sum2{lane_xor<8>(v.s), lane_xor<8>(v.c)});
+    v.join(Sum2{lane_xor<4>(v.s), lane_xor<4>(v.c)});
+    v.join(Sum2{lane_xor<2>(v.s), lane_xor<2>(v.c)});
+    v.join(Sum2{lane_xor<1>(v.s), lane_xor<1>(v.c)});
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < BS / 64; ++w) v.join(red[w]);
+    return v;
+}
+
+// Predicted positions and, per workgroup, the sum of m_i |v_i|^2 / 2.
 __global__ void __launch_bounds__(WG) energy_predict(StateView s, const DevControl *ctl,
-                                                     double *xp, double *vp) {
+                                                     double *xp, Sum2 *kin) {
+    __shared__ Sum2 red[WG / 64];
     const int32_t n = s.n;
     const int64_t t = ctl->t_cur;
+    Sum2 sum{0.0, 0.0};
     for (int32_t i = blockIdx.x * WG + threadIdx.x; i < n; i += gridDim.x * WG) {
         const double D = (double)(t - s.tick[i]) * s.tick_len;
+        double x[3], v[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const int64_t e = c * (int64_t)n + i;
-            predict_one(D, s.x[e], s.v[e], s.a[e], s.k[e], xp[e], vp[e]);
+            predict_one(D, s.x[e], s.v[e], s.a[e], s.k[e], x[c], v[c]);
+            xp[e] = x[c];
+        }
+        sum.add(0.5 * s.m[i] * __builtin_fma(v[2], v[2], __builtin_fma(v[1], v[1], v[0] * v[0])));
+    }
+    sum = wg_sum2<WG>(sum, red);
+    if (threadIdx.x == 0) kin[blockIdx.x] = sum;
+}
+
+// Work of the pair sum: row blocks of `rows` particles (WG * IPL, or WG / S with S lanes sharing
+// a row), each against its own tiles and the later ones.  Row block u and the u-th from the end
+// have about T + 1 tiles together whatever u; an item is a range of `tps` of a pair's tiles
+// (item blockIdx.x: pair blockIdx.x / ranges), so that items are alike and none is empty (a
+// plain grid of row blocks and ranges left half of them empty, more on some XCDs than on others:
+// 2.0 against 1.2 ms at N = 65536).
+struct EnergyPlan {
+    int32_t ipl, S, rows, blocks, tps, ranges, items;
+};
+
+// Two rows a lane (which halve the LDS reads a pair) from 128 tiles on; below, one row a lane,
+// shared by up to 16 lanes while the items would not fill the chip.  At most about 8192 items.
+__host__ __device__ inline EnergyPlan energy_plan(int32_t n, int32_t num_cu) {
+    EnergyPlan p;
+    const int32_t T = (n + TJ - 1) / TJ;
+    p.ipl = T >= 128 ? 2 : 1;
+    p.S = 1;
+    if (p.ipl == 1)
+        while (p.S < 16 && (int64_t)T * T * p.S <= (int64_t)num_cu * 8) p.S *= 2;
+    p.rows = p.ipl == 2 ? 2 * WG : WG / p.S;
+    p.blocks = (n + p.rows - 1) / p.rows;
+    const int32_t pairs = (p.blocks + 1) / 2;
+    const int32_t total = 2 * T + 1 - (int32_t)((int64_t)(p.blocks - 1) * p.rows / TJ);  // most tiles of a pair
+    const int32_t want = num_cu * 32 / pairs;
+    p.tps = want < 1 ? total : (total + want - 1) / want;
+    p.ranges = (total + p.tps - 1) / p.tps;
+    p.items = pairs * p.ranges;
+    return p;
+}
+
+// One staged tile: the terms m_j s^-1/2 of rows i with j > i (each pair once).  MASK: the tile may
+// hold j <= i (or padding j, whose mass is zero).
+template <int IPL, bool SOFT, bool MASK>
+__device__ __forceinline__ void energy_tile(const double4 *sm, int32_t j0, int32_t slice, int32_t S,
+                                            const double (&xi)[IPL][3], const int32_t (&i)[IPL],
+                                            double eps2, double (&ts)[IPL]) {
+#pragma unroll 2
+    for (int32_t jj = slice; jj < TJ; jj += S) {
+        const double4 q = sm[jj];
+#pragma unroll
+        for (int p = 0; p < IPL; ++p) {
+            const double dx = q.x - xi[p][0], dy = q.y - xi[p][1], dz = q.z - xi[p][2];
+            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, __builtin_fma(dx, dx, eps2)));
+            double rinv = rsqrt_f64(r2);
+            if (MASK) rinv = j0 + jj > i[p] ? rinv : 0.0;
+            if (!SOFT) rinv = r2 > 0.0 ? rinv : 0.0;
+            ts[p] = __builtin_fma(q.w, rinv, ts[p]);
         }
     }
 }
 
-// Per particle: m_i sum_{j != i} m_j s^(-1/2) (tile sums folded with Neumaier compensation)
-// and m_i |v_i|^2 / 2.
-__global__ void __launch_bounds__(WG) energy_pairs(const double *xp, const double *vp,
-                                                   const double *m, int32_t n, double eps2,
-                                                   double *w_out, double *k_out) {
-    __shared__ double sx[TJ], sy[TJ], sz[TJ], sm[TJ];
-    const int32_t ntiles = (n + TJ - 1) / TJ;
-    for (int32_t ib = blockIdx.x; ib * WG < n; ib += gridDim.x) {
-        const int32_t i = ib * WG + threadIdx.x;
-        const int32_t ic = i < n ? i : 0;
-        const double xi = xp[ic], yi = xp[(int64_t)n + ic], zi = xp[2 * (int64_t)n + ic];
-        double s = 0.0, comp = 0.0;
-        for (int32_t t = 0; t < ntiles; ++t) {
-            __syncthreads();
-            const int32_t j = t * TJ + threadIdx.x;
-            sx[threadIdx.x] = j < n ? xp[j] : 0.0;
-            sy[threadIdx.x] = j < n ? xp[(int64_t)n + j] : 0.0;
-            sz[threadIdx.x] = j < n ? xp[2 * (int64_t)n + j] : 0.0;
-            sm[threadIdx.x] = j < n ? m[j] : 0.0;
-            __syncthreads();
-            double ts = 0.0;
-            for (int jj = 0; jj < TJ; ++jj) {
-                const double dx = sx[jj] - xi, dy = sy[jj] - yi, dz = sz[jj] - zi;
-                const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, __builtin_fma(dx, dx, eps2)));
-                const double term = sm[jj] * rsqrt_f64(r2);
-                ts += (t * TJ + jj == i || !(r2 > 0.0)) ? 0.0 : term;
-            }
-            const double y = s + ts;  // Neumaier step
-            comp += __builtin_fabs(s) >= __builtin_fabs(ts) ? (s - y) + ts : (ts - y) + s;
-            s = y;
+// Per item, the compensated sum of m_i m_j s^-1/2 over its pairs i < j.  FP64 VALU bound: 13
+// instructions a pair and the quarter-rate reciprocal square root, 70 cycles a wave at N = 65536
+// (1.08 ms with both ends of the call; rows against every j, one workgroup per 256 rows over all
+// tiles: 3.69 ms, and at N = 1024 81 against 32 us).
+template <int IPL, bool SOFT>
+__global__ void __launch_bounds__(WG) energy_pairs(const double *xp, const double *m, int32_t n,
+                                                   double eps2, EnergyPlan pl, Sum2 *out) {
+    __shared__ double4 sm[TJ];
+    __shared__ Sum2 red[WG / 64];
+    const int32_t T = (n + TJ - 1) / TJ, S = pl.S, slice = (int32_t)threadIdx.x % S;
+    const int32_t u = (int32_t)blockIdx.x / pl.ranges, v = pl.blocks - 1 - u;
+    int32_t r0 = ((int32_t)blockIdx.x - u * pl.ranges) * pl.tps, r1 = r0 + pl.tps;
+    Sum2 sum{0.0, 0.0};
+    for (int32_t part = 0; part < (u < v ? 2 : 1); ++part) {
+        const int32_t first = (part ? v : u) * pl.rows, last = first + pl.rows - 1;
+        const int32_t f = first / TJ, c = T - f;  // the block's tiles f ... T - 1: 0 ... c - 1 of the range
+        const int32_t t0 = f + r0, t1 = f + (r1 < c ? r1 : c);
+        r0 = r0 > c ? r0 - c : 0;
+        r1 = r1 > c ? r1 - c : 0;
+        if (t0 >= t1) continue;
+        Sum2 w[IPL];
+        double xi[IPL][3];
+        int32_t i[IPL];
+#pragma unroll
+        for (int p = 0; p < IPL; ++p) {
+            i[p] = first + p * WG + (int32_t)threadIdx.x / S;
+            const int32_t ic = i[p] < n ? i[p] : n - 1;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) xi[p][d] = xp[d * (int64_t)n + ic];
+            w[p] = Sum2{0.0, 0.0};
         }
-        if (i < n) {
-            const double mi = m[i];
-            w_out[i] = mi * (s + comp);
-            const double vx = vp[i], vy = vp[(int64_t)n + i], vz = vp[2 * (int64_t)n + i];
-            k_out[i] = 0.5 * mi * __builtin_fma(vz, vz, __builtin_fma(vy, vy, vx * vx));
+        for (int32_t t = t0; t < t1; ++t) {
+            __syncthreads();
+            const int32_t j = t * TJ + (int32_t)threadIdx.x;
+            sm[threadIdx.x] = j < n ? double4{xp[j], xp[(int64_t)n + j], xp[2 * (int64_t)n + j], m[j]}
+                                    : double4{0.0, 0.0, 0.0, 0.0};
+            __syncthreads();
+            double ts[IPL] = {};
+            if (t * TJ <= last) energy_tile<IPL, SOFT, true>(sm, t * TJ, slice, S, xi, i, eps2, ts);
+            else energy_tile<IPL, SOFT, false>(sm, t * TJ, slice, S, xi, i, eps2, ts);
+#pragma unroll
+            for (int p = 0; p < IPL; ++p) w[p].add(ts[p]);
         }
+#pragma unroll
+        for (int p = 0; p < IPL; ++p)
+            if (i[p] < n) sum.add(m[i[p]] * (w[p].s + w[p].c));
     }
+    sum = wg_sum2<WG>(sum, red);
+    if (threadIdx.x == 0) out[blockIdx.x] = sum;
 }
 
-// One workgroup of 1024: fixed-order compensated sums of both arrays.
-__global__ void __launch_bounds__(1024) energy_reduce(const double *w, const double *kin,
-                                                      int32_t n, double *out) {
-    __shared__ double sw[1024], sk[1024];
-    double a = 0.0, ca = 0.0, b = 0.0, cb = 0.0;
-    for (int32_t i = threadIdx.x; i < n; i += 1024) {
-        double y = a + w[i];
-        ca += __builtin_fabs(a) >= __builtin_fabs(w[i]) ? (a - y) + w[i] : (w[i] - y) + a;
-        a = y;
-        y = b + kin[i];
-        cb += __builtin_fabs(b) >= __builtin_fabs(kin[i]) ? (b - y) + kin[i] : (kin[i] - y) + b;
-        b = y;
-    }
-    sw[threadIdx.x] = a + ca;
-    sk[threadIdx.x] = b + cb;
-    __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            sw[threadIdx.x] += sw[threadIdx.x + s];
-            sk[threadIdx.x] += sk[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[0] = sk[0];
-        out[1] = -0.5 * sw[0];
-    }
+// One workgroup: the totals and the latched flags, for one copy to the host.
+struct EnergyOut {
+    double kin, pot;
+    int32_t nonfinite, wait, sched, dtmin;
+};
+__global__ void __launch_bounds__(1024) energy_reduce(const Sum2 *w, int32_t nw, const Sum2 *kin,
+                                                      int32_t nk, const DevControl *ctl, EnergyOut *out) {
+    __shared__ Sum2 red[1024 / 64];
+    Sum2 a{0.0, 0.0}, b{0.0, 0.0};
+    for (int32_t e = threadIdx.x; e < nw; e += 1024) a.join(w[e]);
+    for (int32_t e = threadIdx.x; e < nk; e += 1024) b.join(kin[e]);
+    a = wg_sum2<1024>(a, red);
+    b = wg_sum2<1024>(b, red);
+    if (threadIdx.x == 0)
+        *out = EnergyOut{b.s + b.c, -(a.s + a.c), ctl->flag_nonfinite, ctl->flag_wait,
+                         ctl->flag_sched, ctl->flag_dtmin};
 }
 
 }  // namespace nbody

@@ -96,7 +96,8 @@ struct nb_ctx {
     int64_t *wgmin = nullptr;
     int32_t *cnt = nullptr;
     DevControl *ctl = nullptr;
-    double *exp_ = nullptr, *evp = nullptr, *ew = nullptr, *ek = nullptr, *eout = nullptr;
+    double *exp_ = nullptr, *ew = nullptr;
+    EnergyOut *eout = nullptr;
     int64_t *t_zero = nullptr;
     double *adj = nullptr;  // a1_bar, k1_bar, xp_bar, vp_bar (3n each) for the step VJP
     int32_t *adj_flag = nullptr;
@@ -611,16 +612,21 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     return NB_OK;
 }
 
+// The error a latched device flag reports at a synchronising call.
+nb_status latched_status(nb_ctx *c, int32_t nonfinite, int32_t wait, int32_t sched, int32_t dtmin) {
+    if (nonfinite) return fail(c, NB_ENONFINITE, "non-finite force or state on device");
+    if (wait) return fail(c, NB_EDEVICE, "the workgroups of a tiled run did not meet");
+    if (sched)
+        return fail(c, NB_ESTATE, "block selection: a particle's next time preceded the block time");
+    if (dtmin) return fail(c, NB_EDTMIN, "time step below 2^-%d requested (clamped)", c->lmax);
+    return NB_OK;
+}
+
 nb_status latched(nb_ctx *c) {
     DevControl h;
     HIP_OK(c, hipMemcpyAsync(&h, c->ctl, sizeof h, hipMemcpyDeviceToHost, c->stream));
     HIP_OK(c, hipStreamSynchronize(c->stream));
-    if (h.flag_nonfinite) return fail(c, NB_ENONFINITE, "non-finite force or state on device");
-    if (h.flag_wait) return fail(c, NB_EDEVICE, "the workgroups of a tiled run did not meet");
-    if (h.flag_sched)
-        return fail(c, NB_ESTATE, "block selection: a particle's next time preceded the block time");
-    if (h.flag_dtmin) return fail(c, NB_EDTMIN, "time step below 2^-%d requested (clamped)", c->lmax);
-    return NB_OK;
+    return latched_status(c, h.flag_nonfinite, h.flag_wait, h.flag_sched, h.flag_dtmin);
 }
 
 void drop_graph(nb_ctx *c) {
@@ -689,7 +695,7 @@ void ctx_plan(nb_ctx *c) {
 //   block force outputs acc, jerk (3 n each), pot (n), FP64
 //   j-split partials    7 * partial_rows FP64
 //   block list (n int32), criterion inputs (2 n FP64), per-workgroup minima and counts,
-//   scheduler record, energy scratch (8 n + 2 FP64), adjoint scratch (12 n FP64) and flags,
+//   scheduler record, energy scratch (8 n FP64), adjoint scratch (12 n FP64) and flags,
 //   the zero tick and the tuner's device count.
 size_t ctx_layout(nb_ctx *c, char *base) {
     Carver k{base};
@@ -722,10 +728,9 @@ size_t ctx_layout(nb_ctx *c, char *base) {
     c->wgmin = k.take<int64_t>(ngroups);
     c->cnt = k.take<int32_t>(ngroups);
     c->ctl = k.take<DevControl>(1);
-    c->exp_ = k.take<double>(8 * N + 2);
-    if (base) {
-        c->evp = c->exp_ + 3 * N; c->ew = c->evp + 3 * N; c->ek = c->ew + N; c->eout = c->ek + N;
-    }
+    c->exp_ = k.take<double>(8 * N);  // energy: predicted positions (3 n), then kinetic sums
+    c->ew = base ? c->exp_ + 3 * N : nullptr;
+    c->eout = k.take<EnergyOut>(1);
     c->adj = k.take<double>(12 * N);
     c->adj_flag = k.take<int32_t>(4);
     c->t_zero = k.take<int64_t>(1);
@@ -1042,19 +1047,30 @@ nb_status nb_energy(nb_ctx *c, double *ekin, double *epot) {
     if ((r = need(c)) != NB_OK) return r;
     if (!ekin || !epot) return fail(c, NB_EINVAL, "nb_energy: host outputs required");
     hipStream_t s = c->stream;
-    energy_predict<<<grid_for(c->n, 8192), WG, 0, s>>>(state_view(c), c->ctl, c->exp_, c->evp);
+    const EnergyPlan pl = energy_plan(c->n, c->num_cu);
+    const int32_t items = pl.items, kg = grid_for(c->n, 1024);
+    Sum2 *w = (Sum2 *)c->partial, *kin = (Sum2 *)c->ew;
+    if ((int64_t)items * 2 > c->partial_rows * 7 || kg > c->n)  // the workspace holds them
+        return fail(c, NB_ESTATE, "energy plan exceeds the workspace");
+    energy_predict<<<kg, WG, 0, s>>>(state_view(c), c->ctl, c->exp_, kin);
     LAUNCH_OK(c);
-    energy_pairs<<<grid_for(c->n, 1 << 20), WG, 0, s>>>(c->exp_, c->evp, c->st.m, c->n,
-                                                         c->eps * c->eps, c->ew, c->ek);
+    const double e2 = c->eps * c->eps;
+    if (pl.ipl == 2) {
+        if (e2 > 0.0) energy_pairs<2, true><<<items, WG, 0, s>>>(c->exp_, c->st.m, c->n, e2, pl, w);
+        else energy_pairs<2, false><<<items, WG, 0, s>>>(c->exp_, c->st.m, c->n, e2, pl, w);
+    } else {
+        if (e2 > 0.0) energy_pairs<1, true><<<items, WG, 0, s>>>(c->exp_, c->st.m, c->n, e2, pl, w);
+        else energy_pairs<1, false><<<items, WG, 0, s>>>(c->exp_, c->st.m, c->n, e2, pl, w);
+    }
     LAUNCH_OK(c);
-    energy_reduce<<<1, 1024, 0, s>>>(c->ew, c->ek, c->n, c->eout);
+    energy_reduce<<<1, 1024, 0, s>>>(w, items, kin, kg, c->ctl, c->eout);
     LAUNCH_OK(c);
-    double h[2];
-    HIP_OK(c, hipMemcpyAsync(h, c->eout, sizeof h, hipMemcpyDeviceToHost, s));
+    EnergyOut h;
+    HIP_OK(c, hipMemcpyAsync(&h, c->eout, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_OK(c, hipStreamSynchronize(s));
-    *ekin = h[0];
-    *epot = h[1];
-    return latched(c);
+    *ekin = h.kin;
+    *epot = h.pot;
+    return latched_status(c, h.nonfinite, h.wait, h.sched, h.dtmin);
 }
 
 nb_status nb_read_control(nb_ctx *c, nb_control *out) {
@@ -1067,11 +1083,7 @@ nb_status nb_read_control(nb_ctx *c, nb_control *out) {
     out->t_cur = h.t_cur; out->t_next = h.t_next; out->t_end = h.t_end;
     out->n_steps = h.n_steps; out->n_active_sum = h.n_active_sum; out->n_act = h.n_act;
     out->flags = (h.flag_nonfinite ? 1 : 0) | (h.flag_dtmin ? 2 : 0) | (h.flag_sched ? 4 : 0);
-    if (h.flag_nonfinite) return fail(c, NB_ENONFINITE, "non-finite force or state on device");
-    if (h.flag_sched)
-        return fail(c, NB_ESTATE, "block selection: a particle's next time preceded the block time");
-    if (h.flag_dtmin) return fail(c, NB_EDTMIN, "time step below 2^-%d requested (clamped)", c->lmax);
-    return NB_OK;
+    return latched_status(c, h.flag_nonfinite, h.flag_wait, h.flag_sched, h.flag_dtmin);
 }
 
 static nb_status check_shared_dt(nb_ctx *c, double dt, int64_t *dt_ticks) {
@@ -1910,7 +1922,13 @@ nb_status nb_ens_energy(nb_ens *e, double *ekin, double *epot) {
     if (!e || !ekin || !epot) return NB_EINVAL;
     if (!e->initialised) return fail(e, NB_ESTATE, "nb_ens_energy before nb_ens_init");
     EHIP_OK(e, hipSetDevice(e->device));
-    ens_energy<<<e->C, WG, 0, e->stream>>>(ens_view(e, INT64_MAX), ens_state(e), e->ek, e->ep);
+    int32_t most = 1;  // row blocks of the largest cluster
+    for (int32_t c = 0; c < e->C; ++c)
+        most = std::max(most, (e->off_h[c + 1] - e->off_h[c] + TJ - 1) / TJ);
+    const EnsView view = ens_view(e, INT64_MAX);
+    ens_energy_items<<<dim3(e->C, std::min(most, 64)), WG, 0, e->stream>>>(view, ens_state(e));
+    ELAUNCH_OK(e);
+    ens_energy_sum<<<e->C, 64, 0, e->stream>>>(view, e->ek, e->ep);
     ELAUNCH_OK(e);
     EHIP_OK(e, hipMemcpyAsync(ekin, e->ek, e->C * sizeof(double), hipMemcpyDeviceToHost, e->stream));
     EHIP_OK(e, hipMemcpyAsync(epot, e->ep, e->C * sizeof(double), hipMemcpyDeviceToHost, e->stream));
