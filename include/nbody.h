@@ -321,7 +321,9 @@ nb_status nb_sync(nb_ctx *ctx);
  * clusters' blocks spread over the whole GPU (j- and i-particles predicted as they are
  * loaded), then one workgroup per cluster for the corrector, the new levels and the next
  * block.  A run replays a HIP
- * graph of steps_per_launch global steps until every cluster is done.
+ * graph of steps_per_launch global steps until every cluster is done; or, where every cluster
+ * has at most 8192 particles, one cooperative launch in which teams of resident workgroups, one
+ * workgroup per 256 particles of a cluster, integrate a cluster each and then take the next.
  * The state is one nb_state over all particles, clusters stored contiguously.
  * ------------------------------------------------------------------------------------------ */
 typedef struct nb_ens nb_ens;
@@ -336,8 +338,8 @@ nb_status nb_ens_create(nb_ens **out, int32_t n_clusters, const int32_t *offsets
 
 /* Bytes of device workspace an ensemble of these clusters needs (offsets as for
  * nb_ens_create, HOST array): cluster tables, per-cluster records, block lists, criterion and
- * energy scratch, and one plane set of j-split partial sums per cluster (7 doubles per
- * particle per 256-particle j-tile).  0 if the arguments are invalid. */
+ * energy scratch, one plane set of j-split partial sums per cluster (8 doubles per particle per
+ * 256-particle j-tile) and two records of 8 doubles per particle.  0 if the arguments are invalid. */
 size_t nb_ens_scratch_bytes(int32_t n_clusters, const int32_t *offsets, int32_t precision);
 
 /* Bind the ensemble's workspace (as nb_bind_scratch: caller-owned, 256-byte aligned, at least
@@ -399,8 +401,11 @@ nb_status nb_ens_init(nb_ens *ens, double eta);
  * batch, synchronising after each to test for completion; at most max_steps global steps
  * (<= 0: no limit).  A global step is the GPU-wide force of every cluster's selected block that
  * is not a local block (nb_ens_set_local), then one workgroup per cluster: the corrector of
- * that block, the next block, and the cluster's local block steps.  Returns NB_OK or a latched
- * device error. */
+ * that block, the next block, and the cluster's local block steps.  Graph runs without local
+ * steps, with at least 8 lanes per block particle (nb_ens_set_split) and clusters of at most
+ * 8192 particles need no global steps: teams of workgroups advance every cluster by itself (the
+ * same block steps and limits; lanes and tiles per item change nothing then).  Returns NB_OK or
+ * a latched device error. */
 nb_status nb_ens_run(nb_ens *ens, double eta, int64_t t_end, int32_t steps_per_launch,
                      int64_t max_steps, int32_t use_graph);
 

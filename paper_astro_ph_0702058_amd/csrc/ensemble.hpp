@@ -38,7 +38,8 @@ struct EnsView {
     int32_t *active;            // global indices, cluster c's block at active[off[c]...]
     double *partial;
     double *crit;
-    int32_t *flags;             // [0]: non-finite seen, [1]: step clamped at 2^-lmax
+    int32_t *flags;             // [0]: non-finite seen, [1]: step clamped at 2^-lmax, [2]: a
+                                // particle behind the block time, [3]: a team did not meet
     int32_t lmin, lmax;
     double tick_len;
     int64_t t_end;
@@ -71,7 +72,7 @@ __host__ __device__ __forceinline__ bool ens_local_block(int32_t n_act, int32_t 
 __global__ void __launch_bounds__(WG) ens_clear(EnsCluster *cl, int32_t C, int32_t *flags) {
     const int32_t c = blockIdx.x * WG + threadIdx.x;
     if (c < C) cl[c] = EnsCluster{0, 0, 0, 0, 0, 0, 0, 0};
-    if (c < 2) flags[c] = 0;
+    if (c < 4) flags[c] = 0;
 }
 
 // Ordered compaction of the particles of [lo, hi) that satisfy `pred` into out[base ...],

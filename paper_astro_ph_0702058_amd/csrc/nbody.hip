@@ -17,6 +17,7 @@
 
 #include "../../include/nbody.h"
 #include "adjoint.hpp"
+#include "ens_tiles.hpp"
 #include "ensemble.hpp"
 #include "kernels.hpp"
 #include "tiles.hpp"
@@ -156,10 +157,19 @@ struct nb_ens {
     int64_t local_limit = 0, local_work = 1 << 21;
     int32_t local_steps = 64;
     int32_t smin = 8;  // fewest lanes per block particle in a force item
+    // runs in one launch of teams (ens_tiles.hpp)
+    bool teams_ok = true;         // cleared when the device refuses the launch
+    uint64_t tile_epoch = 1, turn = 1;
+    int32_t n_wgs = 0;
+    std::vector<int32_t> tile_off_h, tables_h;
+    int32_t *tile_off = nullptr, *tables = nullptr;
+    uint64_t *assign = nullptr, *word = nullptr;
+    double *rec = nullptr;
     hipGraphExec_t gexec = nullptr;
     hipGraph_t graph = nullptr;
     double g_eta = -1.0;
-    int64_t g_tend = -1;
+    int64_t g_tend = -1;    // of the captured graph
+    int64_t run_tend = -1;  // of the last graph run (nb_ens_control)
     int32_t g_steps = 0;
     // independent lanes (nb_ens_set_lanes): lane l advances the clusters at places
     // [lane_start_h[l], lane_start_h[l + 1]) of order_h by a graph of its own on a stream of its
@@ -1517,8 +1527,12 @@ void ens_plan(nb_ens *e, int32_t n_clusters, const int32_t *offsets, int32_t pre
     for (int32_t c = 0; c < n_clusters; ++c) {
         const int32_t n_c = offsets[c + 1] - offsets[c];
         e->prow_h[c] = n_c;
-        e->part_off_h[c + 1] = e->part_off_h[c] + (int64_t)((n_c + TJ - 1) / TJ) * 7 * n_c;
+        // 7 sums per row and tile, and one word of padding where a run's teams keep them
+        e->part_off_h[c + 1] = e->part_off_h[c] + (int64_t)((n_c + TJ - 1) / TJ) * TL_WORDS * n_c;
     }
+    e->tile_off_h.assign(1, 0);
+    for (int32_t c = 0; c < n_clusters; ++c)
+        e->tile_off_h.push_back(e->tile_off_h[c] + (offsets[c + 1] - offsets[c] + TJ - 1) / TJ);
     // the cluster-local kernel's workgroup order: decreasing size (ties by index)
     e->order_h.resize(n_clusters);
     for (int32_t c = 0; c < n_clusters; ++c) e->order_h[c] = c;
@@ -1547,21 +1561,159 @@ size_t ens_layout(nb_ens *e, char *base) {
     e->eps2 = k.take<double>(C);
     e->cl = k.take<EnsCluster>(C);
     e->active = k.take<int32_t>(N);
-    e->flags = k.take<int32_t>(2);
+    e->flags = k.take<int32_t>(4);
     e->partial = k.take<double>((size_t)e->part_off_h[C]);
     e->crit = k.take<double>(2 * N);
     e->ek = k.take<double>(2 * C);
     e->ep = base ? e->ek + C : nullptr;
+    // the teams of a run: tables, words, published records
+    e->tile_off = k.take<int32_t>(C + 1);
+    e->tables = k.take<int32_t>(EnsTables::words(e->C));
+    e->assign = k.take<uint64_t>(ET_WGS);
+    e->word = k.take<uint64_t>(3 * (size_t)e->tile_off_h[C]);
+    e->rec = k.take<double>(2 * N * TL_WORDS);
     return k.off;
 }
 
 nb_status ens_flags(nb_ens *e) {
-    int32_t f[2];
+    int32_t f[4];
     EHIP_OK(e, hipMemcpyAsync(f, e->flags, sizeof f, hipMemcpyDeviceToHost, e->stream));
     EHIP_OK(e, hipStreamSynchronize(e->stream));
     if (f[0]) return fail(e, NB_ENONFINITE, "non-finite force or state on device");
+    if (f[3]) return fail(e, NB_EDEVICE, "a team of an ensemble run did not meet");
+    if (f[2])
+        return fail(e, NB_ESTATE, "block selection: a particle's next time preceded the block time");
     if (f[1]) return fail(e, NB_EDTMIN, "time step below 2^-%d requested (clamped)", e->lmax);
     return NB_OK;
+}
+
+// The kernel of a run in teams.
+const void *ens_tiles_kernel(int prec) {
+    return prec == NB_FP32 ? (const void *)ens_tiles<ModeF32, 4>
+         : prec == NB_DS ? (const void *)ens_tiles<ModeDS, 3> : (const void *)ens_tiles<ModeF64, 3>;
+}
+
+// Teams and queues of a run from the clusters' records: a cluster's work is about the number of
+// its present finest step left to t_end, times its tiles.  Clusters queue by their number of
+// tiles, the most work first; every queue gets one team of that many workgroups, and the queue
+// whose clusters would take longest (work over teams) another one as long as the device holds
+// all workgroups at once.  False if it cannot hold one team per queue.
+bool ens_plan_teams(nb_ens *e, const std::vector<EnsCluster> &cl, int64_t t_end) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ens_tiles_kernel(e->prec), WG, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const int32_t room = std::min<int32_t>(ET_WGS, per_cu * e->num_cu);
+    std::vector<double> steps(e->C), load(ET_TILES + 1, 0.0);
+    std::vector<std::vector<int32_t>> cls(ET_TILES + 1);
+    for (int32_t c : e->size_order_h) {
+        const int32_t T = e->tile_off_h[c + 1] - e->tile_off_h[c];
+        if (T > ET_TILES) return false;
+        const double dt = (double)std::max<int64_t>(cl[c].t_next - cl[c].t_cur, 1);
+        steps[c] = cl[c].done ? 0.0 : 1.0 + (double)(t_end - cl[c].t_cur) / dt;
+        cls[T].push_back(c);
+        load[T] += steps[c];
+    }
+    std::vector<int32_t> teams(ET_TILES + 1, 0);
+    int32_t used = 0;
+    for (int32_t T = 1; T <= ET_TILES; ++T)
+        if (!cls[T].empty()) {
+            std::stable_sort(cls[T].begin(), cls[T].end(), [&](int32_t p, int32_t q) { return steps[p] > steps[q]; });
+            teams[T] = 1;
+            used += T;
+        }
+    if (used > room) return false;
+    for (;;) {
+        int32_t best = 0;
+        double most = 0.0;
+        for (int32_t T = 1; T <= ET_TILES; ++T) {
+            if (teams[T] >= (int32_t)cls[T].size() || used + T > room) continue;
+            // measured on a full device: 17 us a step for one tile, 24-31 us from four on
+            const double l = load[T] / teams[T] * std::min(13.0 + 4.0 * T, 28.0);
+            if (l > most) {
+                most = l;
+                best = T;
+            }
+        }
+        if (best == 0) break;
+        teams[best] += 1;
+        used += best;
+    }
+    e->n_wgs = used;
+    e->tables_h.assign(EnsTables::words(e->C), 0);
+    const EnsTables t(e->tables_h.data(), e->C);
+    int32_t place = 0, wg = 0, team = 0;
+    for (int32_t T = ET_TILES; T >= 1; --T) {
+        const int32_t begin = place, end = begin + (int32_t)cls[T].size();
+        for (int32_t c : cls[T]) t.queue[place++] = c;
+        for (int32_t k = 0; k < teams[T]; ++k, ++team) {
+            for (int32_t w = 0; w < T; ++w, ++wg) {
+                t.wg_team[wg] = team;
+                t.wg_tile[wg] = w;
+            }
+            t.team[team] = EnsTeam{T, begin + k, T, end};
+        }
+        t.next[T] = begin + teams[T];
+    }
+    return true;
+}
+
+// nb_ens_run in one cooperative launch (per at most 2^20 block steps of a cluster).  done = false:
+// not taken (the caller goes on with global steps).
+nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64_t max_steps, bool &done) {
+    done = false;
+    nb_status r = NB_OK;
+    // global steps come in batches of spl
+    int64_t left = max_steps > 0 ? (max_steps + spl - 1) / spl * spl : INT64_MAX;
+    std::vector<EnsCluster> h(e->C);
+    auto records = [&]() -> nb_status {
+        EHIP_OK(e, hipMemcpyAsync(h.data(), e->cl, e->C * sizeof(EnsCluster), hipMemcpyDeviceToHost, e->stream));
+        EHIP_OK(e, hipStreamSynchronize(e->stream));
+        return NB_OK;
+    };
+    if ((r = records()) != NB_OK) return r;
+    int64_t prev = -1;
+    while (left > 0) {
+        if (!ens_plan_teams(e, h, t_end)) {
+            e->teams_ok = false;
+            return NB_OK;
+        }
+        EHIP_OK(e, hipMemcpyAsync(e->tables, e->tables_h.data(), e->tables_h.size() * sizeof(int32_t),
+                                  hipMemcpyHostToDevice, e->stream));
+        EnsTilesArgs a;
+        a.e = ens_view(e, t_end);
+        a.s = ens_state(e);
+        a.eta = eta;
+        a.steps = (int32_t)std::min<int64_t>(left, 1 << 20);
+        a.epoch = e->tile_epoch;
+        a.t = EnsTables(e->tables, e->C);
+        a.assign = e->assign; a.turn = e->turn; a.tile_off = e->tile_off;
+        a.word = e->word; a.rec = e->rec;
+        e->tile_epoch += (uint64_t)a.steps + 3;
+        e->turn += (uint64_t)e->C + 2;
+        void *args[] = {&a};
+        if (hipLaunchCooperativeKernel(ens_tiles_kernel(e->prec), dim3(e->n_wgs), dim3(WG), args, 0,
+                                       e->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            e->teams_ok = false;
+            return NB_OK;
+        }
+        done = true;
+        if ((r = records()) != NB_OK) return r;
+        left -= a.steps;
+        bool all = true;
+        int64_t total = 0;
+        for (const auto &x : h) {
+            all = all && x.done;
+            total += x.n_steps;
+        }
+        if (all) break;
+        if ((r = ens_flags(e)) != NB_OK) return r;
+        if (total == prev) return fail(e, NB_ESTATE, "ensemble made no progress over %d block steps", a.steps);
+        prev = total;
+    }
+    return ens_flags(e);
 }
 
 // nb_ens_run with independent lanes: each lane replays its own graph of global steps on its own
@@ -1708,13 +1860,19 @@ nb_status nb_ens_bind_scratch(nb_ens *e, void *scratch, size_t bytes) {
     EHIP_OK(e, hipMemcpyAsync(e->off, e->off_h.data(), (C + 1) * sizeof(int32_t), hipMemcpyHostToDevice, e->stream));
     EHIP_OK(e, hipMemcpyAsync(e->prow, e->prow_h.data(), C * sizeof(int32_t), hipMemcpyHostToDevice, e->stream));
     EHIP_OK(e, hipMemcpyAsync(e->order, e->order_h.data(), C * sizeof(int32_t), hipMemcpyHostToDevice, e->stream));
+    EHIP_OK(e, hipMemcpyAsync(e->tile_off, e->tile_off_h.data(), (C + 1) * sizeof(int32_t), hipMemcpyHostToDevice, e->stream));
     EHIP_OK(e, hipMemcpyAsync(e->part_off, e->part_off_h.data(), (C + 1) * sizeof(int64_t), hipMemcpyHostToDevice, e->stream));
     EHIP_OK(e, hipMemcpyAsync(e->eps2, e->eps2_h.data(), C * sizeof(double), hipMemcpyHostToDevice, e->stream));
     EHIP_OK(e, hipMemcpyAsync(e->K, e->K_h.data(), C * sizeof(int32_t), hipMemcpyHostToDevice, e->stream));
     EHIP_OK(e, hipMemcpyAsync(e->tpi, e->tpi_h.data(), C * sizeof(int32_t), hipMemcpyHostToDevice, e->stream));
     ens_clear<<<std::max<int32_t>(1, (int32_t)((C + WG - 1) / WG)), WG, 0, e->stream>>>(e->cl, e->C, e->flags);
     ELAUNCH_OK(e);
+    zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->word, 3 * e->tile_off_h[e->C], nullptr, 0);
+    ELAUNCH_OK(e);
+    zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->assign, ET_WGS, nullptr, 0);
+    ELAUNCH_OK(e);
     EHIP_OK(e, hipStreamSynchronize(e->stream));
+    e->tile_epoch = 1; e->turn = 1;
     e->scratch_ok = true;
     e->initialised = false;
     return NB_OK;
@@ -1842,7 +2000,7 @@ nb_status nb_ens_init(nb_ens *e, double eta) {
     if (!e->bound) return fail(e, NB_ESTATE, "state not bound");
     if (!(eta > 0.0) || !std::isfinite(eta)) return fail(e, NB_EINVAL, "eta must be > 0");
     EHIP_OK(e, hipSetDevice(e->device));
-    zero_words<<<1, WG, 0, e->stream>>>(nullptr, 0, e->flags, 2);
+    zero_words<<<1, WG, 0, e->stream>>>(nullptr, 0, e->flags, 4);
     ELAUNCH_OK(e);
     nb_status r;
     if ((r = ens_enqueue_local(e, eta, 0, INT64_MAX, e->stream, false)) != NB_OK) return r;
@@ -1858,6 +2016,13 @@ nb_status nb_ens_run(nb_ens *e, double eta, int64_t t_end, int32_t steps_per_lau
     if (!e->initialised) return fail(e, NB_ESTATE, "nb_ens_run before nb_ens_init");
     if (!(eta > 0.0) || steps_per_launch < 1) return fail(e, NB_EINVAL, "bad arguments");
     EHIP_OK(e, hipSetDevice(e->device));
+    if (use_graph) e->run_tend = t_end;
+    // teams: graph runs (eager ones keep the launches apart) without local steps, at least 8 lanes a row
+    if (use_graph && e->teams_ok && e->local_limit == 0 && e->smin >= 8) {
+        bool done = false;
+        const nb_status r = ens_run_teams(e, eta, t_end, steps_per_launch, max_steps, done);
+        if (r != NB_OK || done) return r;
+    }
     if (e->lanes > 1) return ens_run_lanes(e, eta, t_end, steps_per_launch, max_steps, use_graph);
     if (use_graph && (!e->gexec || e->g_eta != eta || e->g_tend != t_end ||
                       e->g_steps != steps_per_launch)) {
@@ -1911,7 +2076,7 @@ nb_status nb_ens_control(nb_ens *e, nb_control *out) {
     EHIP_OK(e, hipMemcpyAsync(h.data(), e->cl, e->C * sizeof(EnsCluster), hipMemcpyDeviceToHost, e->stream));
     EHIP_OK(e, hipStreamSynchronize(e->stream));
     for (int32_t c = 0; c < e->C; ++c) {
-        out[c].t_cur = h[c].t_cur; out[c].t_next = h[c].t_next; out[c].t_end = e->g_tend;
+        out[c].t_cur = h[c].t_cur; out[c].t_next = h[c].t_next; out[c].t_end = e->run_tend;
         out[c].n_steps = h[c].n_steps; out[c].n_active_sum = h[c].n_active_sum;
         out[c].n_act = h[c].n_act; out[c].flags = h[c].done;
     }
