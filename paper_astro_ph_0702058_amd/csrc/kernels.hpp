@@ -79,6 +79,7 @@ struct Spread {
     int32_t hmax;     // 4: helper lanes keep the order of the sums (FP32); 1: none
     int32_t fill;     // lanes per tile that fill the chip (0: lane_split alone)
     int32_t wg = WG;  // lanes that lane_split spreads over a list
+    int32_t pack = 0; // lists longer than a workgroup take slices that leave less padding
 };
 
 // Slices S and helper lanes H of each of n_i rows.
@@ -93,6 +94,23 @@ __host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, in
     }
 }
 
+// Slices of a list longer than a workgroup that takes S: more, up to 4, where the i-blocks of
+// fewer rows that they give leave at least 1/16 less padding (a padded row costs as much as a
+// true one; below 1/16 the tile staging shared by fewer rows takes the gain).  FP64 and
+// double-single only: FP32's tile sums fix the slices, and fixed point would leave its scalar
+// j-loads (881 rows at N = 65536 105 and 111 us).  Without and with it: 520 rows at N = 65536
+// FP64 106 and 92 us, double-single 335 and 246; 881 rows 127 and 118, 400 and 356; 257 rows at
+// N = 524288 390 and 292, 1340 and 937 (calls one after the other, launches included).
+__host__ __device__ inline int32_t pack_lanes(int32_t n_i, int32_t S) {
+    const auto padded = [n_i](int32_t ib) { return (n_i + ib - 1) & -ib; };  // ib a power of two
+    const int32_t r1 = padded(WG), r2 = padded(WG / 2), r4 = padded(WG / 4);
+    int32_t rows = S == 1 ? r1 : S == 2 ? r2 : r4;
+    const int32_t least = rows >> 4;
+    if (S < 2 && rows - r2 >= least) { rows = r2; S = 2; }
+    if (S < 4 && rows - r4 >= least) S = 4;
+    return S;
+}
+
 // ib_max: WG * (i-particles per work-item).  Lists shorter than a workgroup take the lane
 // split whatever the variant (one i per group of lanes), so that a short block costs work in
 // proportion to its length.  Where the rows' lanes, on every tile, leave the chip unfilled (no
@@ -105,6 +123,7 @@ __host__ __device__ inline ForcePlan make_plan(int32_t n_i, int32_t n, int32_t i
     p.n_i = n_i;
     p.ntiles = (n + TJ - 1) / TJ;
     row_lanes(n_i, sp, p.S, p.H);
+    if (sp.pack && n_i > WG && ib_max == WG) p.S = pack_lanes(n_i, p.S);
     const int32_t L = p.S * p.H;
     const int32_t ib = L > 1 ? WG / L : ib_max;
     p.ib = ib;

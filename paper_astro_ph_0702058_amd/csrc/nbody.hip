@@ -375,7 +375,7 @@ Spread spread_of(const nb_ctx *c, const Variant &v) {
     const int32_t fill = c->num_cu * 1024 / ((c->n + TJ - 1) / TJ);
     if (c->prec == NB_FP32) return Spread{64, v.ipl == 1 && v.unroll == 2 ? 4 : 1, v.ipl == 1 && v.unroll == 2 ? fill : 0};
     if (c->prec == NB_FP32_ALL) return Spread{64, 1, 0};
-    return Spread{smax_of(c->prec), 1, fill};
+    return Spread{smax_of(c->prec), 1, fill, WG, c->prec == NB_FP64 || c->prec == NB_DS};
 }
 
 // Largest K * P over every i-count up to n_i_max against n j-particles, for one variant (the

@@ -55,3 +55,29 @@ def test_short_lists_against_oracle(prec, eps):
     for idx, (acc, jerk, pot) in zip(lists, out):
         ref, scale = reference(x, v, m, eps * eps, idx=idx)
         check(prec, (acc.T, jerk.T, pot), ref, scale, f"{prec} eps={eps} {len(idx)} rows")
+
+
+@pytest.mark.parametrize("prec", ["fp64", "ds"])
+def test_lists_of_several_blocks_leave_little_padding(prec):
+    """Lists longer than a workgroup in a system large enough that they fill the chip: one slice
+    (1024 rows), two (881), four (300, 700, 1030, 2100) of the j-slots, host and device counts."""
+    n, eps = 40000, 1 / 256
+    x, v, m = plummer(n, 72)
+    st = nbody.DeviceState(x, v, m)
+    with nbody.Context(n, eps, precision=prec) as ctx:
+        ctx.nb_bind(st)
+        ctx.nb_predict(torch.zeros(1, dtype=torch.int64, device="cuda"))
+        for k in (300, 700, 881, 1024, 1030, 2100):
+            idx = sample_indices(n, k, k)
+            ii = torch.as_tensor(idx.astype(np.int32), device="cuda")
+            got = []
+            for cnt in (None, torch.tensor([k], dtype=torch.int32, device="cuda")):
+                acc = torch.zeros((3, k), dtype=torch.float64, device="cuda")
+                jerk, pot = torch.zeros_like(acc), torch.zeros(k, dtype=torch.float64, device="cuda")
+                ctx.nb_force(acc, jerk, pot, i_idx=ii, n_i=cnt)
+                ctx.nb_sync()
+                got.append([q.cpu().numpy() for q in (acc, jerk, pot)])
+            assert all(np.array_equal(a, b) for a, b in zip(*got))
+            acc, jerk, pot = got[0]
+            ref, scale = reference(x, v, m, eps * eps, idx=idx)
+            check(prec, (acc.T, jerk.T, pot), ref, scale, f"{prec} {k} rows of {n}")
