@@ -268,23 +268,31 @@ __global__ void __launch_bounds__(WG) force_vjp_kernel(VjpArgs a) {
 }
 
 // Sums the K partial planes (fixed order): x_bar, v_bar of the predicted state written to
-// (accumulate = 0) or added to (accumulate = 1) xpb, vpb; m_bar added to mb.
+// (accumulate = 0) or added to (accumulate = 1) xpb, vpb; m_bar added to mb.  Bound by the
+// planes' bytes: one workgroup per (64 rows, one of the 7 sums), as force_reduce spreads them.
+constexpr int VRW = WG / 64;
 __global__ void __launch_bounds__(WG) vjp_reduce(int32_t n, const double *partial, int32_t target,
                                                  int32_t kmax, double *xpb, double *vpb,
                                                  double *mb, int32_t accumulate) {
+    __shared__ double part[VRW][64];
     const ForcePlan pl = make_plan(n, n, WG, target, kmax);
-    for (int32_t p = blockIdx.x * WG + threadIdx.x; p < n; p += gridDim.x * WG) {
-        double o[7] = {0, 0, 0, 0, 0, 0, 0};
-        for (int32_t k = 0; k < pl.K; ++k)
+    const int32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int32_t units = ((n + 63) >> 6) * 7;
+    for (int32_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const int32_t rb = u / 7, c = u - rb * 7;
+        const int32_t p = rb * 64 + lane;
+        part[w][lane] = p < n ? wave_planes_sum<VRW>(partial + (int64_t)c * pl.P + p, 7 * pl.P, w, pl.K)
+                              : 0.0;
+        __syncthreads();
+        if (w == 0 && p < n) {
+            double t = part[0][lane];
 #pragma unroll
-            for (int c = 0; c < 7; ++c) o[c] += partial[((int64_t)k * 7 + c) * pl.P + p];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const int64_t e = c * (int64_t)n + p;
-            xpb[e] = (accumulate ? xpb[e] : 0.0) + o[c];
-            vpb[e] = (accumulate ? vpb[e] : 0.0) + o[3 + c];
+            for (int r = 1; r < VRW; ++r) t += part[r][lane];
+            double *o = c < 3 ? xpb + c * (int64_t)n + p
+                      : c < 6 ? vpb + (c - 3) * (int64_t)n + p : mb + p;
+            *o = (c == 6 || accumulate ? *o : 0.0) + t;
         }
-        mb[p] += o[6];
+        __syncthreads();
     }
 }
 

@@ -1112,6 +1112,22 @@ __global__ void __launch_bounds__(WG) force_kernel_helped(typename M::Args pa, F
 constexpr int RW = 16;               // waves per reduce workgroup
 constexpr int WG_REDUCE = 64 * RW;
 
+// Wave w's share of NW waves: planes k = w + NW (4 m + r), `plane` doubles apart, go to sum r,
+// and the four sums are added in the order 0..3.
+template <int NW>
+__device__ __forceinline__ double wave_planes_sum(const double *src, int64_t plane, int32_t w,
+                                                  int32_t K) {
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    const int64_t st = NW * plane;
+    int32_t k = w;
+    for (; k + 3 * NW < K; k += 4 * NW) {
+        const double *b = src + k * plane;
+        s0 += b[0]; s1 += b[st]; s2 += b[2 * st]; s3 += b[3 * st];
+    }
+    for (; k < K; k += NW) s0 += src[k * plane];
+    return ((s0 + s1) + s2) + s3;
+}
+
 // FIXED: the planes hold the raw int64 fixed-point sums of ModeF32Fixed; they are added as
 // integers (exact), converted with the mode's scales and the potential negated.
 template <bool FIXED>
@@ -1146,19 +1162,7 @@ __global__ void __launch_bounds__(WG_REDUCE) force_reduce(ForceCommon fc, int32_
             ipart[w][lane] = s;
             ibad[w][lane] = bad;
         } else {
-            // four planes in flight per lane: planes k = w + RW (4 m + r) go to sum r, and the
-            // four sums are added in the order 0..3 (the order depends only on K)
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-            if (q < n_i) {
-                const int64_t st = (int64_t)RW * 7 * pl.P;
-                int32_t k = w;
-                for (; k + 3 * RW < pl.K; k += 4 * RW) {
-                    const double *b = src + (int64_t)k * 7 * pl.P;
-                    s0 += b[0]; s1 += b[st]; s2 += b[2 * st]; s3 += b[3 * st];
-                }
-                for (; k < pl.K; k += RW) s0 += src[(int64_t)k * 7 * pl.P];
-            }
-            part[w][lane] = ((s0 + s1) + s2) + s3;
+            part[w][lane] = q < n_i ? wave_planes_sum<RW>(src, 7 * pl.P, w, pl.K) : 0.0;
         }
         __syncthreads();
         if (w == 0 && q < n_i) {

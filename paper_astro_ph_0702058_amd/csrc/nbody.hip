@@ -1128,8 +1128,8 @@ static nb_status enqueue_force_vjp(nb_ctx *c, const double *ab, const double *kb
         else force_vjp_kernel<2, false><<<grid, WG, 0, s>>>(a);
     }
     LAUNCH_OK(c);
-    vjp_reduce<<<grid_for(c->n, 4096), WG, 0, s>>>(c->n, c->partial, a.target, a.kmax, xb, vb, mb,
-                                                   accumulate);
+    vjp_reduce<<<std::min(((c->n + 63) >> 6) * 7, 1 << 16), WG, 0, s>>>(
+        c->n, c->partial, a.target, a.kmax, xb, vb, mb, accumulate);
     LAUNCH_OK(c);
     return NB_OK;
 }
