@@ -15,6 +15,7 @@
 // j-side terms (A_q, B_q of q against p).
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -112,9 +113,13 @@ template <> __device__ __forceinline__ double fma_t<double>(double a, double b, 
 // and each product with a negated operand is a plain two-operand multiply or FMA rather than
 // one carrying a negation modifier (which takes the slower three-operand encoding).
 template <class T>
-__device__ __forceinline__ void vjp_pair(T dx, T dy, T dz, T ux, T uy, T uz, T rinv, T mp, T mq,
-                                         const T nA[3], const T nB[3], const T Aq[3],
-                                         const T Bq[3], T gx[3], T gu[3], T &ngm) {
+struct VjpTerms {
+    T r3, C1, C2, c3, d[3], u[3], Ab[3], Bb[3], abq, bdq;  // abq = Aq.d + Bq.u, bdq = Bq.d
+};
+template <class T>
+__device__ __forceinline__ VjpTerms<T> vjp_terms(T dx, T dy, T dz, T ux, T uy, T uz, T rinv, T mp,
+                                                 T mq, const T nA[3], const T nB[3],
+                                                 const T Aq[3], const T Bq[3]) {
     const T r2 = rinv * rinv, r3 = rinv * r2, r5 = r3 * r2, r7 = r5 * r2;
     const T du = fma_t(dz, uz, fma_t(dy, uy, dx * ux));
     const T m3r5 = T(-3) * r5;
@@ -128,19 +133,96 @@ __device__ __forceinline__ void vjp_pair(T dx, T dy, T dz, T ux, T uy, T uz, T r
     const T Adq = fma_t(Aq[2], dz, fma_t(Aq[1], dy, Aq[0] * dx));
     const T Bdq = fma_t(Bq[2], dz, fma_t(Bq[1], dy, Bq[0] * dx));
     const T Buq = fma_t(Bq[2], uz, fma_t(Bq[1], uy, Bq[0] * ux));
-    const T c1q = fma_t(f15, Bdq, m3r5 * (Adq + Buq));
+    const T abq = Adq + Buq;
+    const T c1q = fma_t(f15, Bdq, m3r5 * abq);
     const T c2q = m3r5 * Bdq;
-    const T C1 = fma_t(mp, c1q, mq * nc1);
-    const T C2 = fma_t(mp, c2q, mq * nc2);
-    const T d[3] = {dx, dy, dz}, u[3] = {ux, uy, uz};
+    VjpTerms<T> o{r3, fma_t(mp, c1q, mq * nc1), fma_t(mp, c2q, mq * nc2), c3,
+                  {dx, dy, dz}, {ux, uy, uz}, {}, {}, abq, Bdq};
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const T Ab = fma_t(mp, Aq[k], mq * nA[k]);
-        const T Bb = fma_t(mp, Bq[k], mq * nB[k]);
-        gx[k] = fma_t(r3, Ab, fma_t(C1, d[k], fma_t(C2, u[k], fma_t(c3, Bb, gx[k]))));
-        gu[k] = fma_t(r3, Bb, fma_t(C2, d[k], gu[k]));
+        o.Ab[k] = fma_t(mp, Aq[k], mq * nA[k]);
+        o.Bb[k] = fma_t(mp, Bq[k], mq * nB[k]);
     }
-    ngm = fma_t(Adq + Buq, r3, fma_t(c3, Bdq, ngm));
+    return o;
+}
+
+template <class T>
+struct VjpSum {
+    T gx[3] = {0, 0, 0}, gu[3] = {0, 0, 0}, ngm = 0;
+    __device__ __forceinline__ void add(const VjpTerms<T> &o) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            gx[k] = fma_t(o.r3, o.Ab[k], fma_t(o.C1, o.d[k], fma_t(o.C2, o.u[k], fma_t(o.c3, o.Bb[k], gx[k]))));
+            gu[k] = fma_t(o.r3, o.Bb[k], fma_t(o.C2, o.d[k], gu[k]));
+        }
+        ngm = fma_t(o.abq, o.r3, fma_t(o.c3, o.bdq, ngm));
+    }
+};
+
+// Adds the terms of the four lanes of a quad to every lane's g, in lane order: each addition is
+// the one VjpSum::add makes, with the other lane's values as DPP operands.  The four lanes hold
+// the same g.  (A DPP operand is read two wait states after it was written: the s_nop.)
+#define NB_QUAD(n) " quad_perm:[" n "," n "," n "," n "] row_mask:0xf bank_mask:0xf\n"
+#define NB_F3(a, b, c, x, y, z, m, n)                                                         \
+    "v_fmac_f32_dpp %" a ", %" x ", %" m NB_QUAD(n) "v_fmac_f32_dpp %" b ", %" y ", %" m      \
+    NB_QUAD(n) "v_fmac_f32_dpp %" c ", %" z ", %" m NB_QUAD(n)
+#define NB_VJP_GX(n)                                                                          \
+    "v_mov_b32_dpp %3, %22" NB_QUAD(n) "v_mov_b32_dpp %4, %21" NB_QUAD(n)                     \
+    "v_mov_b32_dpp %5, %20" NB_QUAD(n) "v_mov_b32_dpp %6, %19" NB_QUAD(n)                     \
+    NB_F3("0", "1", "2", "16", "17", "18", "3", n) NB_F3("0", "1", "2", "10", "11", "12", "4", n) \
+    NB_F3("0", "1", "2", "7", "8", "9", "5", n) NB_F3("0", "1", "2", "13", "14", "15", "6", n)
+#define NB_VJP_GU(n)                                                                          \
+    "v_mov_b32_dpp %4, %17" NB_QUAD(n) "v_mov_b32_dpp %5, %16" NB_QUAD(n)                     \
+    "v_mov_b32_dpp %6, %15" NB_QUAD(n)                                                        \
+    NB_F3("0", "1", "2", "7", "8", "9", "5", n) "v_fmac_f32_dpp %3, %14, %4" NB_QUAD(n)       \
+    NB_F3("0", "1", "2", "10", "11", "12", "6", n) "v_fmac_f32_dpp %3, %13, %6" NB_QUAD(n)
+__device__ __forceinline__ void vjp_add_quad(VjpSum<float> &g, const VjpTerms<float> &o) {
+    float m0, m1, m2, m3;
+    asm("s_nop 1\n" NB_VJP_GX("0") NB_VJP_GX("1") NB_VJP_GX("2") NB_VJP_GX("3")
+        : "+v"(g.gx[0]), "+v"(g.gx[1]), "+v"(g.gx[2]), "=&v"(m0), "=&v"(m1), "=&v"(m2), "=&v"(m3)
+        : "v"(o.d[0]), "v"(o.d[1]), "v"(o.d[2]), "v"(o.u[0]), "v"(o.u[1]), "v"(o.u[2]),
+          "v"(o.Ab[0]), "v"(o.Ab[1]), "v"(o.Ab[2]), "v"(o.Bb[0]), "v"(o.Bb[1]), "v"(o.Bb[2]),
+          "v"(o.r3), "v"(o.C1), "v"(o.C2), "v"(o.c3));
+    asm("s_nop 1\n" NB_VJP_GU("0") NB_VJP_GU("1") NB_VJP_GU("2") NB_VJP_GU("3")
+        : "+v"(g.gu[0]), "+v"(g.gu[1]), "+v"(g.gu[2]), "+v"(g.ngm), "=&v"(m0), "=&v"(m1), "=&v"(m2)
+        : "v"(o.d[0]), "v"(o.d[1]), "v"(o.d[2]), "v"(o.Bb[0]), "v"(o.Bb[1]), "v"(o.Bb[2]),
+          "v"(o.abq), "v"(o.bdq), "v"(o.r3), "v"(o.C2), "v"(o.c3));
+}
+#undef NB_VJP_GU
+#undef NB_VJP_GX
+#undef NB_F3
+#undef NB_QUAD
+
+// How a force VJP is split: i-blocks of ib rows with L lanes each times K ranges of tps j-tiles.
+struct VjpPlan {
+    int32_t L, ib, n_iblk, ntiles, tps, K, items;
+    int64_t P;  // padded rows of one partial plane
+};
+// A lane's tile of 256 pairs is a serial chain (one wave issues an instruction every four cycles:
+// 70 us whatever the size up to 16 tiles), so where the rows' lanes on all tiles leave the chip
+// unfilled, rows take more: up to 64 slices in FP64 while they are at most four waves per SIMD
+// (fill); in FP32, whose tile sums fix the slots' order, four helpers (vjp_add_quad, 177
+// instructions per four pairs instead of 364, 108 of them half-rate DPP) up to 2/3 of that.
+// With one lane and with more: N = 1000 FP32 75 and 37 us, FP64 71 and 17; N = 3276 77 and 72,
+// 78 and 55; N = 4096 FP32 77 and 89 (hence the 2/3), FP64 81 and 68.
+inline VjpPlan vjp_plan(int32_t n, bool fp32, int32_t num_cu, int32_t target) {
+    VjpPlan p;
+    p.ntiles = (n + TJ - 1) / TJ;
+    const int64_t fill = (int64_t)num_cu * 1024 / p.ntiles;
+    p.L = 1;
+    if (fp32) {
+        if ((int64_t)n * 6 <= fill) p.L = 4;
+    } else {
+        while (p.L < 64 && (int64_t)n * p.L * 2 <= fill) p.L *= 2;
+    }
+    p.ib = WG / p.L;
+    p.n_iblk = (n + p.ib - 1) / p.ib;
+    const int32_t K = std::max(1, std::min(target / p.n_iblk, p.ntiles));
+    p.tps = (p.ntiles + K - 1) / K;
+    p.K = (p.ntiles + p.tps - 1) / p.tps;
+    p.items = p.n_iblk * p.K;
+    p.P = (int64_t)p.n_iblk * p.ib;
+    return p;
 }
 
 struct VjpArgs {
@@ -151,7 +233,7 @@ struct VjpArgs {
     const double *ab, *kb;       // adjoints of acc and jerk, 3 x n
     double eps2;
     double *partial;             // [K][7][P]
-    int32_t target, kmax;
+    VjpPlan pl;
 };
 
 template <class T>
@@ -161,105 +243,151 @@ struct VjpSmem {
     T A[3][TJ], B[3][TJ];
 };
 
-// One staged tile of the force VJP for one particle p (position xp, velocity vp, mass mp,
-// negated adjoints nA, nB).  SOFT (eps > 0): every separation is positive, and only a tile
-// holding p's own slot (MASK, slot rel) needs a test, taken in a copy of the loop that masks
-// that slot; without softening every pair at zero separation (the self pair among them) adds
-// nothing.  Padding slots carry zero mass and zero adjoints and add exact zeros.
+template <int MODE>
+using VjpT = typename std::conditional<MODE == 0, float, double>::type;
+
+// Stages the j-particles of tile t (one per lane; padding carries zero mass and zero adjoints and
+// adds exact zeros).
+template <int MODE>
+__device__ __forceinline__ void vjp_stage(const VjpArgs &a, VjpSmem<VjpT<MODE>> &sm, int32_t t) {
+    using T = VjpT<MODE>;
+    const int32_t n = a.n, x = threadIdx.x, j = t * TJ + x;
+    const bool ok = j < n;
+    const int32_t jc = ok ? j : 0;
+    sm.x[x] = a.px[jc]; sm.y[x] = a.py[jc]; sm.z[x] = a.pz[jc];
+    if (MODE == 0) {
+        const float4 q = a.vm[jc];
+        sm.vx[x] = q.x; sm.vy[x] = q.y; sm.vz[x] = q.z;
+        sm.m[x] = ok ? q.w : 0.f;
+    } else {
+        sm.vx[x] = a.vx[jc]; sm.vy[x] = a.vy[jc];
+        sm.vz[x] = a.vz[jc]; sm.m[x] = ok ? a.pm[jc] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        sm.A[k][x] = ok ? (T)a.ab[k * (int64_t)n + jc] : T(0);
+        sm.B[k][x] = ok ? (T)a.kb[k * (int64_t)n + jc] : T(0);
+    }
+}
+
+// Particle p of the force VJP: position, velocity, mass and negated adjoints.
+template <class T>
+struct VjpRow {
+    double x, y, z;
+    T vx, vy, vz, m, nA[3], nB[3];
+};
+template <int MODE>
+__device__ __forceinline__ VjpRow<VjpT<MODE>> vjp_row(const VjpArgs &a, int32_t p) {
+    using T = VjpT<MODE>;
+    VjpRow<T> r;
+    r.x = a.px[p]; r.y = a.py[p]; r.z = a.pz[p];
+    if (MODE == 0) {
+        const float4 q = a.vm[p];
+        r.vx = q.x; r.vy = q.y; r.vz = q.z; r.m = q.w;
+    } else {
+        r.vx = a.vx[p]; r.vy = a.vy[p]; r.vz = a.vz[p]; r.m = a.pm[p];
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        r.nA[k] = -(T)a.ab[k * (int64_t)a.n + p];
+        r.nB[k] = -(T)a.kb[k * (int64_t)a.n + p];
+        // opaque to the optimiser, which would otherwise fold the negation back into
+        // modifiers on the products inside the pair loop
+        asm volatile("" : "+v"(r.nA[k]), "+v"(r.nB[k]));
+    }
+    return r;
+}
+
+// The pair of row r with slot jj of the staged tile.  SOFT (eps > 0): every separation is
+// positive, and only a tile holding the row's own slot (MASK, slot rel) needs a test; without
+// softening every pair at zero separation (the self pair among them) adds nothing.
 template <class T, bool SOFT, bool MASK>
-__device__ __forceinline__ void vjp_tile(const VjpSmem<T> &sm, int32_t rel, double xp, double yp,
-                                         double zp, T vxp, T vyp, T vzp, T mp, T eps2,
-                                         const T nA[3], const T nB[3], T gx[3], T gu[3],
-                                         T &ngm) {
+__device__ __forceinline__ VjpTerms<T> vjp_slot(const VjpSmem<T> &sm, int32_t jj, int32_t rel,
+                                                const VjpRow<T> &r, T eps2) {
+    const T dx = (T)(sm.x[jj] - r.x), dy = (T)(sm.y[jj] - r.y), dz = (T)(sm.z[jj] - r.z);
+    const T ux = sm.vx[jj] - r.vx, uy = sm.vy[jj] - r.vy, uz = sm.vz[jj] - r.vz;
+    const T s = dx * dx + dy * dy + dz * dz + eps2;
+    T rinv;
+    if (std::is_same<T, float>::value) rinv = (T)__builtin_amdgcn_rsqf((float)s);
+    else rinv = (T)rsqrt_f64((double)s);
+    if (MASK && jj == rel) rinv = T(0);
+    if (!SOFT && !(s > T(0))) rinv = T(0);
+    const T Aq[3] = {sm.A[0][jj], sm.A[1][jj], sm.A[2][jj]};
+    const T Bq[3] = {sm.B[0][jj], sm.B[1][jj], sm.B[2][jj]};
+    return vjp_terms<T>(dx, dy, dz, ux, uy, uz, rinv, r.m, sm.m[jj], r.nA, r.nB, Aq, Bq);
+}
+
+// One staged tile for the lane `slice` of a row's L lanes: double takes every L-th slot; float,
+// whose sums keep the slots' order, evaluates every fourth and adds all four lanes' (LANES: L
+// is 4).  LANES = false: one lane a row.
+template <class T, bool SOFT, bool MASK, bool LANES>
+__device__ __forceinline__ void vjp_tile(const VjpSmem<T> &sm, int32_t slice, int32_t L,
+                                         int32_t rel, const VjpRow<T> &r, T eps2, VjpSum<T> &g) {
+    if constexpr (!LANES) {
 #pragma unroll 1
-    for (int jj = 0; jj < TJ; ++jj) {
-        const T dx = (T)(sm.x[jj] - xp), dy = (T)(sm.y[jj] - yp), dz = (T)(sm.z[jj] - zp);
-        const T ux = sm.vx[jj] - vxp, uy = sm.vy[jj] - vyp, uz = sm.vz[jj] - vzp;
-        const T s = dx * dx + dy * dy + dz * dz + eps2;
-        T rinv;
-        if (std::is_same<T, float>::value) rinv = (T)__builtin_amdgcn_rsqf((float)s);
-        else rinv = (T)rsqrt_f64((double)s);
-        if (MASK && jj == rel) rinv = T(0);
-        if (!SOFT && !(s > T(0))) rinv = T(0);
-        const T Aq[3] = {sm.A[0][jj], sm.A[1][jj], sm.A[2][jj]};
-        const T Bq[3] = {sm.B[0][jj], sm.B[1][jj], sm.B[2][jj]};
-        vjp_pair<T>(dx, dy, dz, ux, uy, uz, rinv, mp, sm.m[jj], nA, nB, Aq, Bq, gx, gu, ngm);
+        for (int jj = 0; jj < TJ; ++jj) g.add(vjp_slot<T, SOFT, MASK>(sm, jj, rel, r, eps2));
+    } else if constexpr (std::is_same<T, float>::value) {
+        for (int jj = slice; jj < TJ; jj += 4)
+            vjp_add_quad(g, vjp_slot<T, SOFT, MASK>(sm, jj, rel, r, eps2));
+    } else {
+#pragma unroll 1
+        for (int jj = slice; jj < TJ; jj += L) g.add(vjp_slot<T, SOFT, MASK>(sm, jj, rel, r, eps2));
     }
 }
 
 // Force VJP over all particles; j-split into K ranges, partial sums (7 per particle: x_bar,
 // v_bar, m_bar) per range, summed by vjp_reduce.  MODE 0: float arithmetic on separations
 // formed in double (tile sums folded into double); MODE 2: double throughout.  SOFT: eps > 0
-// in the arithmetic type.
-template <int MODE, bool SOFT>
+// in the arithmetic type.  LANES: the plan gives a row more than one lane.
+template <int MODE, bool SOFT, bool LANES>
 __global__ void __launch_bounds__(WG) force_vjp_kernel(VjpArgs a) {
-    using T = typename std::conditional<MODE == 0, float, double>::type;
+    using T = VjpT<MODE>;
     __shared__ VjpSmem<T> sm;
     const int32_t n = a.n;
-    const ForcePlan pl = make_plan(n, n, WG, a.target, a.kmax);
+    const VjpPlan &pl = a.pl;
+    const int32_t L = LANES ? pl.L : 1, slice = LANES ? (int32_t)threadIdx.x & (L - 1) : 0;
     for (int32_t w = blockIdx.x; w < pl.items; w += gridDim.x) {
         const int32_t iblk = w / pl.K, ks = w - (w / pl.K) * pl.K;
-        const int32_t p = iblk * WG + (int32_t)threadIdx.x;
-        const int32_t pc = p < n ? p : 0;
+        const int32_t p = LANES ? iblk * pl.ib + (int32_t)threadIdx.x / L
+                                : iblk * WG + (int32_t)threadIdx.x;
         const int32_t own = p < n ? p : -1;  // p's own j-slot (none on padding lanes)
-        const double xp = a.px[pc], yp = a.py[pc], zp = a.pz[pc];
-        T vxp, vyp, vzp, mp;
-        if (MODE == 0) {
-            const float4 q = a.vm[pc];
-            vxp = q.x; vyp = q.y; vzp = q.z; mp = q.w;
-        } else {
-            vxp = a.vx[pc]; vyp = a.vy[pc]; vzp = a.vz[pc]; mp = a.pm[pc];
-        }
-        T nA[3], nB[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            nA[k] = -(T)a.ab[k * (int64_t)n + pc];
-            nB[k] = -(T)a.kb[k * (int64_t)n + pc];
-            // opaque to the optimiser, which would otherwise fold the negation back into
-            // modifiers on the products inside the pair loop
-            asm volatile("" : "+v"(nA[k]), "+v"(nB[k]));
-        }
+        const VjpRow<T> r = vjp_row<MODE>(a, p < n ? p : 0);
         double S[7] = {0, 0, 0, 0, 0, 0, 0};
         const T eps2 = (T)a.eps2;
         const int32_t t0 = ks * pl.tps;
         const int32_t t1 = t0 + pl.tps < pl.ntiles ? t0 + pl.tps : pl.ntiles;
         for (int32_t t = t0; t < t1; ++t) {
             __syncthreads();
-            {
-                const int32_t j = t * TJ + (int32_t)threadIdx.x;
-                const bool ok = j < n;
-                const int32_t jc = ok ? j : 0;
-                sm.x[threadIdx.x] = a.px[jc]; sm.y[threadIdx.x] = a.py[jc]; sm.z[threadIdx.x] = a.pz[jc];
-                if (MODE == 0) {
-                    const float4 q = a.vm[jc];
-                    sm.vx[threadIdx.x] = q.x; sm.vy[threadIdx.x] = q.y; sm.vz[threadIdx.x] = q.z;
-                    sm.m[threadIdx.x] = ok ? q.w : 0.f;
-                } else {
-                    sm.vx[threadIdx.x] = a.vx[jc]; sm.vy[threadIdx.x] = a.vy[jc];
-                    sm.vz[threadIdx.x] = a.vz[jc]; sm.m[threadIdx.x] = ok ? a.pm[jc] : 0.0;
-                }
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    sm.A[k][threadIdx.x] = ok ? (T)a.ab[k * (int64_t)n + jc] : T(0);
-                    sm.B[k][threadIdx.x] = ok ? (T)a.kb[k * (int64_t)n + jc] : T(0);
-                }
-            }
+            vjp_stage<MODE>(a, sm, t);
             __syncthreads();
-            T gx[3] = {0, 0, 0}, gu[3] = {0, 0, 0}, ngm = 0;
+            VjpSum<T> g;
             const int32_t rel = own - t * TJ;
             // a tile holding some lane's own slot takes the masked loop (wave-uniform branch)
             if (SOFT && __ballot((uint32_t)rel < (uint32_t)TJ) != 0)
-                vjp_tile<T, SOFT, true>(sm, rel, xp, yp, zp, vxp, vyp, vzp, mp, eps2, nA, nB, gx, gu, ngm);
+                vjp_tile<T, SOFT, true, LANES>(sm, slice, L, rel, r, eps2, g);
             else
-                vjp_tile<T, SOFT, false>(sm, rel, xp, yp, zp, vxp, vyp, vzp, mp, eps2, nA, nB, gx, gu, ngm);
+                vjp_tile<T, SOFT, false, LANES>(sm, slice, L, rel, r, eps2, g);
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                S[k] += (double)gx[k];
-                S[3 + k] += (double)gu[k];
+                S[k] += (double)g.gx[k];
+                S[3 + k] += (double)g.gu[k];
             }
-            S[6] -= (double)ngm;
+            S[6] -= (double)g.ngm;
         }
-        if (p < n) {
+        if (LANES && MODE != 0) {  // the slices' sums (the four lanes of a float row hold the same)
+            const auto swap_add = [&](auto off) {
+                if (decltype(off)::value < L)
+#pragma unroll
+                    for (int k = 0; k < 7; ++k) S[k] += lane_xor<decltype(off)::value>(S[k]);
+            };
+            swap_add(std::integral_constant<int, 1>{});
+            swap_add(std::integral_constant<int, 2>{});
+            swap_add(std::integral_constant<int, 4>{});
+            swap_add(std::integral_constant<int, 8>{});
+            swap_add(std::integral_constant<int, 16>{});
+            swap_add(std::integral_constant<int, 32>{});
+        }
+        if (p < n && slice == 0) {
             double *base = a.partial + (int64_t)ks * 7 * pl.P + p;
 #pragma unroll
             for (int k = 0; k < 7; ++k) base[(int64_t)k * pl.P] = S[k];
@@ -271,11 +399,10 @@ __global__ void __launch_bounds__(WG) force_vjp_kernel(VjpArgs a) {
 // (accumulate = 0) or added to (accumulate = 1) xpb, vpb; m_bar added to mb.  Bound by the
 // planes' bytes: one workgroup per (64 rows, one of the 7 sums), as force_reduce spreads them.
 constexpr int VRW = WG / 64;
-__global__ void __launch_bounds__(WG) vjp_reduce(int32_t n, const double *partial, int32_t target,
-                                                 int32_t kmax, double *xpb, double *vpb,
-                                                 double *mb, int32_t accumulate) {
+__global__ void __launch_bounds__(WG) vjp_reduce(int32_t n, const double *partial, VjpPlan pl,
+                                                 double *xpb, double *vpb, double *mb,
+                                                 int32_t accumulate) {
     __shared__ double part[VRW][64];
-    const ForcePlan pl = make_plan(n, n, WG, target, kmax);
     const int32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int32_t units = ((n + 63) >> 6) * 7;
     for (int32_t u = blockIdx.x; u < units; u += gridDim.x) {

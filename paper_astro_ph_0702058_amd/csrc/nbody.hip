@@ -678,7 +678,7 @@ void ctx_plan(nb_ctx *c) {
     }
     // the force VJP writes K * P rows of its plan even when K = 1
     {
-        const ForcePlan pv = make_plan(n, n, WG, c->num_cu * BLOCK_ITEMS_PER_CU, 1 << 16);
+        const VjpPlan pv = vjp_plan(n, precision == NB_FP32, c->num_cu, c->num_cu * BLOCK_ITEMS_PER_CU);
         rows = std::max<int64_t>(rows, (int64_t)pv.K * pv.P);
     }
     // the tiled path: the partial sums of every block row on every tile, held twice, up to 64
@@ -1113,23 +1113,27 @@ static nb_status enqueue_force_vjp(nb_ctx *c, const double *ab, const double *kb
     a.px = c->js.px; a.py = c->js.py; a.pz = c->js.pz; a.vm = c->js.vm;
     a.pm = c->js.pm; a.vx = c->js.vx; a.vy = c->js.vy; a.vz = c->js.vz;
     a.ab = ab; a.kb = kb; a.eps2 = c->eps * c->eps; a.partial = c->partial;
-    a.target = c->num_cu * BLOCK_ITEMS_PER_CU; a.kmax = 1 << 16;
-    const ForcePlan pl = make_plan(c->n, c->n, WG, a.target, a.kmax);
-    if ((int64_t)pl.K * pl.P > c->partial_rows)  // the workspace is sized for this plan
+    a.pl = vjp_plan(c->n, c->prec == NB_FP32, c->num_cu, c->num_cu * BLOCK_ITEMS_PER_CU);
+    if ((int64_t)a.pl.K * a.pl.P > c->partial_rows)  // the workspace is sized for this plan
         return fail(c, NB_ESTATE, "force VJP plan exceeds the partial planes");
-    const int32_t grid = std::max(1, std::min(pl.items, 1 << 20));
+    const int32_t grid = std::max(1, std::min(a.pl.items, 1 << 20));
     // softened: every separation is positive in the arithmetic type, only the self pair masked
     const bool soft = c->prec == NB_FP32 ? (float)a.eps2 > 0.0f : a.eps2 > 0.0;
+    const bool lanes = a.pl.L > 1;
     if (c->prec == NB_FP32) {
-        if (soft) force_vjp_kernel<0, true><<<grid, WG, 0, s>>>(a);
-        else force_vjp_kernel<0, false><<<grid, WG, 0, s>>>(a);
+        if (soft && lanes) force_vjp_kernel<0, true, true><<<grid, WG, 0, s>>>(a);
+        else if (soft) force_vjp_kernel<0, true, false><<<grid, WG, 0, s>>>(a);
+        else if (lanes) force_vjp_kernel<0, false, true><<<grid, WG, 0, s>>>(a);
+        else force_vjp_kernel<0, false, false><<<grid, WG, 0, s>>>(a);
     } else {
-        if (soft) force_vjp_kernel<2, true><<<grid, WG, 0, s>>>(a);
-        else force_vjp_kernel<2, false><<<grid, WG, 0, s>>>(a);
+        if (soft && lanes) force_vjp_kernel<2, true, true><<<grid, WG, 0, s>>>(a);
+        else if (soft) force_vjp_kernel<2, true, false><<<grid, WG, 0, s>>>(a);
+        else if (lanes) force_vjp_kernel<2, false, true><<<grid, WG, 0, s>>>(a);
+        else force_vjp_kernel<2, false, false><<<grid, WG, 0, s>>>(a);
     }
     LAUNCH_OK(c);
     vjp_reduce<<<std::min(((c->n + 63) >> 6) * 7, 1 << 16), WG, 0, s>>>(
-        c->n, c->partial, a.target, a.kmax, xb, vb, mb, accumulate);
+        c->n, c->partial, a.pl, xb, vb, mb, accumulate);
     LAUNCH_OK(c);
     return NB_OK;
 }
