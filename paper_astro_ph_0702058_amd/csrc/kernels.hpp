@@ -82,18 +82,6 @@ struct Spread {
     int32_t pack = 0; // lists longer than a workgroup take slices that leave less padding
 };
 
-// Slices S and helper lanes H of each of n_i rows.
-__host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, int32_t &H) {
-    S = lane_split(n_i, sp.smax, sp.wg);
-    H = 1;
-    if (n_i > sp.fill) return;  // also keeps the products below in range
-    if (sp.hmax > 1) {
-        if (S * 4 <= 64 && n_i * S * 4 <= sp.fill) H = 4;
-    } else {
-        while (S < sp.smax && n_i * S * 2 <= sp.fill) S *= 2;
-    }
-}
-
 // Slices of a list longer than a workgroup that takes S: more, up to 4, where the i-blocks of
 // fewer rows that they give leave at least 1/16 less padding (a padded row costs as much as a
 // true one; below 1/16 the tile staging shared by fewer rows takes the gain).  FP64 and
@@ -111,6 +99,20 @@ __host__ __device__ inline int32_t pack_lanes(int32_t n_i, int32_t S) {
     return S;
 }
 
+// Slices S and helper lanes H of each of n_i rows.
+__host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, int32_t &H) {
+    S = lane_split(n_i, sp.smax, sp.wg);
+    H = 1;
+    if (n_i <= sp.fill) {  // also keeps the products below in range
+        if (sp.hmax > 1) {
+            if (S * 4 <= 64 && n_i * S * 4 <= sp.fill) H = 4;
+        } else {
+            while (S < sp.smax && n_i * S * 2 <= sp.fill) S *= 2;
+        }
+    }
+    if (sp.pack && n_i > WG) S = pack_lanes(n_i, S);
+}
+
 // ib_max: WG * (i-particles per work-item).  Lists shorter than a workgroup take the lane
 // split whatever the variant (one i per group of lanes), so that a short block costs work in
 // proportion to its length.  Where the rows' lanes, on every tile, leave the chip unfilled (no
@@ -123,7 +125,6 @@ __host__ __device__ inline ForcePlan make_plan(int32_t n_i, int32_t n, int32_t i
     p.n_i = n_i;
     p.ntiles = (n + TJ - 1) / TJ;
     row_lanes(n_i, sp, p.S, p.H);
-    if (sp.pack && n_i > WG && ib_max == WG) p.S = pack_lanes(n_i, p.S);
     const int32_t L = p.S * p.H;
     const int32_t ib = L > 1 ? WG / L : ib_max;
     p.ib = ib;

@@ -375,7 +375,8 @@ Spread spread_of(const nb_ctx *c, const Variant &v) {
     const int32_t fill = c->num_cu * 1024 / ((c->n + TJ - 1) / TJ);
     if (c->prec == NB_FP32) return Spread{64, v.ipl == 1 && v.unroll == 2 ? 4 : 1, v.ipl == 1 && v.unroll == 2 ? fill : 0};
     if (c->prec == NB_FP32_ALL) return Spread{64, 1, 0};
-    return Spread{smax_of(c->prec), 1, fill, WG, c->prec == NB_FP64 || c->prec == NB_DS};
+    const bool pack = v.ipl == 1 && (c->prec == NB_FP64 || c->prec == NB_DS);
+    return Spread{smax_of(c->prec), 1, fill, WG, pack};
 }
 
 // Largest K * P over every i-count up to n_i_max against n j-particles, for one variant (the
@@ -608,7 +609,10 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     a.active = c->active; a.js = c->js; a.ctl = c->ctl;
     a.eps2 = c->eps * c->eps; a.eta = eta; a.lmin = c->lmin; a.lmax = c->lmax;
     a.sp = spread_of(c, Variant{1, 2, 0, 0, 0});
-    if (c->n <= RES_MAX) a.sp.wg = WGL;  // the slices of the resident workgroup
+    if (c->n <= RES_MAX) {  // the slices of the resident workgroup
+        a.sp.wg = WGL;
+        a.sp.pack = 0;
+    }
     a.g = state_rw(c);
     void *args[] = {&a};
     const void *f = c->prec == NB_FP32 ? (const void *)run_tiles<ModeF32, 4>
