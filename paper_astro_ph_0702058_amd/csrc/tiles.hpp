@@ -28,7 +28,11 @@
 //
 // What bounds a step (MI355X, N = 16384 FP32, mean block 230, cycles at 2.15 GHz): the rows' tile
 // sums 11000 (one wave's serial chain over 256 j), the two meetings 8000, record and partial-sum
-// loads 4000, selection, prediction and the corrector 10000.  Per block step against the launch
+// loads 4000, selection, prediction and the corrector 10000.  Only the waves that hold the tile
+// select and only they and the row mappers read the owners' words (every wave for itself: 1000
+// cycles of issue more); the corrector's addresses are formed where they are used (hoisted out of
+// the step loop they spilled 32 registers): together 10.80 against 10.96 ms for the N = 16384 FP32
+// run to t = 1/32, 8.18 against 8.36 ms for N = 5000 FP64 to 1/16.  Per block step against the launch
 // chain: N = 2048 FP32 15 and 26 us, N = 5000 FP64 15 and 25 us, N = 16384 FP32 21 and 31 us,
 // N = 65536 56 and 66 us.
 #pragma once
@@ -177,7 +181,8 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     __shared__ uint8_t row_tile[TL_ROWS];
     __shared__ int32_t row_base[TL_TILES];
     __shared__ int32_t owner[TL_TILES];       // level << 16 | count of every owner
-    __shared__ int32_t late;
+    __shared__ int32_t late, plan_rows;       // block rows and time, for every wave
+    __shared__ int64_t plan_t;
     DevControl *ctl = a.ctl;
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -227,47 +232,48 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     while (stepped < a.steps) {
         const uint64_t epoch = a.epoch + (uint64_t)stepped;
         const int32_t par = (int32_t)(epoch & 1);
-        // select: the tile's own next block time and its members; every wave finds the finest
-        // level and the member counts for itself
-        const int32_t lf = 63 - __builtin_clzll(__ballot(hist[lane] > 0) | 1ull);
-        const int64_t t_own = level_time(t_cur, lf, lmax);
-        int32_t n_own = 0, below = 0;
-        bool member = false;
-        uint64_t mask = 0;
+        uint64_t own_word = 0;
+        // select: the tile's own next block time and its members (the waves that hold them)
+        if (wave < TJ / 64) {
+            const int32_t lf = 63 - __builtin_clzll(__ballot(hist[lane] > 0) | 1ull);
+            const int64_t t_own = level_time(t_cur, lf, lmax);
+            int32_t n_own = 0, below = 0;
+            bool member = false;
+            uint64_t mask = 0;
 #pragma unroll
-        for (int k = 0; k < TJ / 64; ++k) {
-            const bool f = lnext[k * 64 + lane] == t_own;
-            const uint64_t mk = __ballot(f);
-            if (k == wave) {
-                member = f;
-                mask = mk;
-                below = n_own;
-            }
-            n_own += __popcll(mk);
-        }
-        if (member) {
-            const int32_t m = below + __popcll(mask & ((1ull << lane) - 1ull));
-            lmem[par][m] = tid;
-            if (rep == 0) {
-                double xp[3], vp[3];
-                predicted(s, tid, t_own, xp, vp);
-                double *r = a.rec[par] + ((int64_t)p0 + m) * TL_WORDS;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    agent_store(r + c, xp[c]);
-                    agent_store(r + 3 + c, vp[c]);
+            for (int k = 0; k < TJ / 64; ++k) {
+                const bool f = lnext[k * 64 + lane] == t_own;
+                const uint64_t mk = __ballot(f);
+                if (k == wave) {
+                    member = f;
+                    mask = mk;
+                    below = n_own;
                 }
-                agent_store(r + 6, lm[tid]);
-                agent_store((uint64_t *)(r + 7), (uint64_t)(p0 + tid));
+                n_own += __popcll(mk);
             }
+            if (tid == 0) own_word = epoch << TL_SHIFT | (uint64_t)lf << 16 | (uint64_t)n_own;
+            if (member) {
+                const int32_t m = below + __popcll(mask & ((1ull << lane) - 1ull));
+                lmem[par][m] = tid;
+                if (rep == 0) {
+                    double xp[3], vp[3];
+                    predicted(s, tid, t_own, xp, vp);
+                    double *r = a.rec[par] + ((int64_t)p0 + m) * TL_WORDS;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        agent_store(r + c, xp[c]);
+                        agent_store(r + 3 + c, vp[c]);
+                    }
+                    agent_store(r + 6, lm[tid]);
+                    agent_store((uint64_t *)(r + 7), (uint64_t)(p0 + tid));
+                }
+            }
+            stores_done();
         }
-        stores_done();
         __syncthreads();
-        if (rep == 0 && tid == 0)
-            agent_store(a.word + par * T + tile,
-                        epoch << TL_SHIFT | (uint64_t)lf << 16 | (uint64_t)n_own);
-        // gather: every owner's word, then (each wave for itself, four owners a lane) the block
-        // time and the block size
+        if (rep == 0 && tid == 0) agent_store(a.word + par * T + tile, own_word);
+        // gather: every owner's word, then (the waves that predict the tile and those that map
+        // the rows, each for itself, four owners a lane) the block time and the block size
         if (tid < T) {
             uint64_t w;
             if (!wait_epoch(a.word + par * T + tid, epoch, w)) late = 1;
@@ -278,44 +284,53 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
             lost = true;
             break;
         }
-        const int4 ow = ((const int4 *)owner)[lane];
-        const int32_t o4[4] = {ow.x, ow.y, ow.z, ow.w};
-        int32_t fine = 0;
+        if (wave < TJ / 64 || wave >= 12) {
+            const int4 ow = ((const int4 *)owner)[lane];
+            const int32_t o4[4] = {ow.x, ow.y, ow.z, ow.w};
+            int32_t fine = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) fine = o4[k] >> 16 > fine ? o4[k] >> 16 : fine;
-        fine = wave_max(fine);
-        const int64_t t_next = level_time(t_cur, fine, lmax);
+            for (int k = 0; k < 4; ++k) fine = o4[k] >> 16 > fine ? o4[k] >> 16 : fine;
+            fine = wave_max(fine);
+            const int64_t tn = level_time(t_cur, fine, lmax);
+            int32_t c4[4], sum = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                c4[k] = level_time(t_cur, o4[k] >> 16, lmax) == tn ? o4[k] & 0xffff : 0;
+                sum += c4[k];
+            }
+            const int32_t inc = wave_scan_add(sum);
+            const int32_t rows = __builtin_amdgcn_readlane(inc, 63);
+            const bool taken = tn <= t_end && rows <= a.limit;
+            if (wave >= 12) {  // the row map, one owner of each lane per wave
+                if (tid == 12 * 64) {
+                    plan_t = tn;
+                    plan_rows = rows;
+                }
+                int32_t b4[4];
+                b4[0] = inc - sum;
+#pragma unroll
+                for (int k = 1; k < 4; ++k) b4[k] = b4[k - 1] + c4[k - 1];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (taken && wave == 12 + k) {
+                        row_base[4 * lane + k] = b4[k];
+                        for (int32_t m = 0; m < c4[k]; ++m) row_tile[b4[k] + m] = (uint8_t)(4 * lane + k);
+                    }
+            } else if (taken) {  // predict the tile
+                double xp[3], vp[3];
+                behind = behind || lnext[tid] < tn;
+                predicted(s, tid, tn, xp, vp);
+                M::put(sm, tid, xp, vp, lm[tid]);
+            }
+        }
+        __syncthreads();
+        const int64_t t_next = plan_t;
         if (t_next > t_end) {
             done = true;
             break;
         }
-        int32_t c4[4], sum = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            c4[k] = level_time(t_cur, o4[k] >> 16, lmax) == t_next ? o4[k] & 0xffff : 0;
-            sum += c4[k];
-        }
-        const int32_t inc = wave_scan_add(sum);
-        const int32_t n_act = __builtin_amdgcn_readlane(inc, 63);
+        const int32_t n_act = __builtin_amdgcn_readfirstlane(plan_rows);
         if (n_act > a.limit) break;
-        int32_t b4[4];
-        b4[0] = inc - sum;
-#pragma unroll
-        for (int k = 1; k < 4; ++k) b4[k] = b4[k - 1] + c4[k - 1];
-        if (wave >= 12) {  // the row map, one owner of each lane per wave
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (wave == 12 + k) {
-                    row_base[4 * lane + k] = b4[k];
-                    for (int32_t m = 0; m < c4[k]; ++m) row_tile[b4[k] + m] = (uint8_t)(4 * lane + k);
-                }
-        } else if (tid < TJ) {  // predict the tile
-            double xp[3], vp[3];
-            behind = behind || lnext[tid] < t_next;
-            predicted(s, tid, t_next, xp, vp);
-            M::put(sm, tid, xp, vp, lm[tid]);
-        }
-        __syncthreads();
         // force: i-blocks of WG / L rows against the tile, TL_SUB at a time
         int32_t S, H;
         row_lanes(n_act, a.sp, S, H);
@@ -362,7 +377,8 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
         stores_done();
         __syncthreads();
         if (tid == 0) agent_store(a.arrive + blockIdx.x, epoch << TL_SHIFT);
-        const int32_t cnt = t_own == t_next ? n_own : 0;
+        const int32_t mine = __builtin_amdgcn_readfirstlane(owner[tile]);
+        const int32_t cnt = level_time(t_cur, mine >> 16, lmax) == t_next ? mine & 0xffff : 0;
         const int32_t base = __builtin_amdgcn_readfirstlane(row_base[tile]);
         if (cnt > 0) {
             uint64_t v;
@@ -376,28 +392,30 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
             // adds the planes k = w mod RW of up to TL_UNITS units, and wave u adds unit u's RW
             // wave sums in order.  More rows: a wave takes whole units, the same sums in the
             // same order.
-            const int32_t units = (cnt + 7) / 8, c = lane & 7;
+            int32_t lane_c = lane;  // opaque: addresses are formed here, not spilled all launch
+            asm volatile("" : "+v"(lane_c));
+            const int32_t units = (cnt + 7) / 8, c = lane_c & 7;
             const int64_t stride = (int64_t)a.limit * TL_WORDS;
             const double *src0 = a.part + (int64_t)par * T * stride + (int64_t)base * TL_WORDS + c;
             const bool spread = units <= TL_UNITS;
             if (spread) {
 #pragma unroll
                 for (int u = 0; u < TL_UNITS; ++u) {
-                    const int32_t m = u * 8 + (lane >> 3);
+                    const int32_t m = u * 8 + (lane_c >> 3);
                     if (u < units)
-                        stage[wave][u * 64 + lane] =
+                        stage[wave][u * 64 + lane_c] =
                             m < cnt && c < 7 ? planes_sum(src0 + m * TL_WORDS, stride, wave, T) : 0.0;
                 }
                 __syncthreads();
             }
             for (int32_t u = wave; u < units; u += RW) {
-                const int32_t m = u * 8 + (lane >> 3);
+                const int32_t m = u * 8 + (lane_c >> 3);
                 const bool live = m < cnt && c < 7;
                 double t = 0.0;
                 if (spread) {
-                    t = stage[0][u * 64 + lane];
+                    t = stage[0][u * 64 + lane_c];
 #pragma unroll
-                    for (int k = 1; k < RW; ++k) t += stage[k][u * 64 + lane];
+                    for (int k = 1; k < RW; ++k) t += stage[k][u * 64 + lane_c];
                 } else if (live) {
                     const double *src = src0 + m * TL_WORDS;
                     t = planes_sum(src, stride, 0, T);
@@ -407,7 +425,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
                 bad = bad || (live && !__builtin_isfinite(t));
                 double v7[7];
 #pragma unroll
-                for (int k = 0; k < 7; ++k) v7[k] = __shfl(t, (lane & ~7) + k, 64);
+                for (int k = 0; k < 7; ++k) v7[k] = __shfl(t, (lane_c & ~7) + k, 64);
                 if (c == 0 && m < cnt) {
                     const int32_t i = lmem[par][m];
                     // the step is a power of two (its level's), so is its reciprocal
