@@ -338,8 +338,8 @@ nb_status nb_ens_create(nb_ens **out, int32_t n_clusters, const int32_t *offsets
 
 /* Bytes of device workspace an ensemble of these clusters needs (offsets as for
  * nb_ens_create, HOST array): cluster tables, per-cluster records, block lists, criterion and
- * energy scratch, one plane set of j-split partial sums per cluster (8 doubles per particle per
- * 256-particle j-tile) and two records of 8 doubles per particle.  0 if the arguments are invalid. */
+ * energy scratch, and one plane set of j-split partial sums per cluster (7 doubles per
+ * particle per 256-particle j-tile).  0 if the arguments are invalid. */
 size_t nb_ens_scratch_bytes(int32_t n_clusters, const int32_t *offsets, int32_t precision);
 
 /* Bind the ensemble's workspace (as nb_bind_scratch: caller-owned, 256-byte aligned, at least

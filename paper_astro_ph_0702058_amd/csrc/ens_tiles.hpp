@@ -12,8 +12,10 @@
 // clusters of 64 to 4096 particles (2411 tiles, 1024 workgroups resident) to t = 1/16, FP32: 33
 // against 68 ms with the energies, to t = 1: 463 against 660 ms in two lanes.  A step takes a lone
 // team 17-19 us (the meetings and loads of tiles.hpp, 32 rows per pass of 32 j a lane); with the
-// device full 24-31 us, four waves a SIMD sharing its issue.  Four waves per SIMD in FP32 (97
-// spilled registers, outside the pair loop) against three: 35 and 38 ms; FP64 43 and 40 ms.
+// device full 24-31 us, four waves a SIMD sharing its issue.  Four waves per SIMD in FP32 (103
+// spilled registers, outside the pair loop) against three: 35 and 38 ms; FP64 43 and 40 ms.  The
+// records and the partial sums share the planes that the global steps had (padded records and
+// sums of their own took 1.3 times the workspace and 5 % less time).
 #pragma once
 
 #include "tiles.hpp"
@@ -21,7 +23,7 @@
 namespace nbody {
 
 constexpr int ET_TILES = 32;   // most tiles of a cluster (a byte of LDS per possible block row)
-constexpr int ET_WGS = 2048;   // most workgroups of a launch
+constexpr int ET_WGS = 1024;   // most workgroups of a launch
 constexpr int ET_ROWS = ET_TILES * TJ;
 
 struct EnsTeam {
@@ -57,7 +59,6 @@ struct EnsTilesArgs {
     uint64_t turn;               // first turn (above every turn published before)
     const int32_t *tile_off;     // tiles before each cluster
     uint64_t *word;              // [total tiles][3]: words by epoch parity, then the arrival
-    double *rec;                 // [2][ntot][TL_WORDS] published records
 };
 
 // The kernel's arguments read again from the kernel-argument segment (tiles_args).
@@ -69,8 +70,15 @@ __device__ __forceinline__ EnsTilesArgs ens_tiles_args() {
     return a;
 }
 
-// Sum over the T partial planes of one of a row's sums, in plane order (ens_row_sums).
-__device__ __forceinline__ double ens_planes_sum(const double *src, int64_t stride, int32_t T) {
+// A cluster's partial planes in a run by a team: [T][n_c] rows of 7 sums, the row of member m of
+// tile t at t TJ + m.  A tile's pull on its own rows stays in its workgroup's LDS, and those rows
+// of its plane hold the records that it publishes (7 words each).
+constexpr int ET_WORDS = 7;
+
+// Sum over the T partial planes of one of a row's sums, in plane order (ens_row_sums); own: that
+// of plane `tile`.
+__device__ __forceinline__ double ens_planes_sum(const double *src, int64_t stride, int32_t T,
+                                                 int32_t tile, double own) {
     double o = 0.0;
     int32_t k = 0;
     for (; k + 8 <= T; k += 8) {
@@ -78,9 +86,12 @@ __device__ __forceinline__ double ens_planes_sum(const double *src, int64_t stri
 #pragma unroll
         for (int r = 0; r < 8; ++r) v[r] = agent_load(src + (k + r) * stride);
 #pragma unroll
-        for (int r = 0; r < 8; ++r) o += v[r];
+        for (int r = 0; r < 8; ++r) o += k + r == tile ? own : v[r];
     }
-    for (; k < T; ++k) o += agent_load(src + k * stride);
+    for (; k < T; ++k) {
+        const double v = agent_load(src + k * stride);
+        o += k == tile ? own : v;
+    }
     return o;
 }
 
@@ -88,7 +99,9 @@ template <class M>
 struct EnsTilesSmem {
     typename M::Smem sm;
     double stage[WG / 64][64 * TL_WORDS / 8];  // at least 8 lanes share a row
-    double sums[64][TL_WORDS - 1];
+    double sums[64][ET_WORDS];
+    double own[TJ][ET_WORDS];                  // the tile's pull on its own block rows
+    uint8_t mem[TJ];                           // the tile's block members
     uint8_t row_tile[ET_ROWS];
     int32_t row_base[64];
     int32_t owner[64];
@@ -112,7 +125,8 @@ __device__ bool ens_tiles_cluster(const EnsTilesArgs &a, EnsTilesSmem<M> &z, int
     const bool selected = cl->n_act > 0;  // a block selected before is stepped whatever t_end
     uint64_t *word = a.word + (int64_t)a.tile_off[c] * 3;  // [2][T], then arrivals [T]
     uint64_t *arrive = word + 2 * T;
-    double *part = e.partial + e.part_off[c];              // [T][n_c][TL_WORDS]
+    double *part = e.partial + e.part_off[c];              // [T][n_c][ET_WORDS]
+    const int64_t stride = (int64_t)n_c * ET_WORDS;
     const auto eps2 = eps_as<M>(e.eps2[c]);
     // the particle of this work-item
     const bool in = tid < n_t;
@@ -148,7 +162,6 @@ __device__ bool ens_tiles_cluster(const EnsTilesArgs &a, EnsTilesSmem<M> &z, int
     while (!skip) {
         const uint64_t epoch = a.epoch + (uint64_t)stepped;
         const int32_t par = (int32_t)(epoch & 1);
-        double *rec = a.rec + (int64_t)par * a.s.n * TL_WORDS;
         // select: the tile's own next block time and members
         const int32_t lf = 63 - __builtin_clzll(__ballot(z.hist[lane] > 0) | 1ull);
         const int64_t t_own = level_time(t_cur, lf, lmax);
@@ -165,7 +178,10 @@ __device__ bool ens_tiles_cluster(const EnsTilesArgs &a, EnsTilesSmem<M> &z, int
         row += __popcll(mask & ((1ull << lane) - 1ull));  // of a member, among the tile's
         if (member) {
             const double D = (double)(t_own - tick) * a.s.tick_len;
-            double *r = rec + ((int64_t)p0 + row) * TL_WORDS;
+            // one set of records: if the tile had rows in the last block it waited until every
+            // workgroup had read them, and else nobody reads them
+            double *r = part + tile * (stride + TJ * ET_WORDS) + row * ET_WORDS;
+            z.mem[row] = (uint8_t)tid;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 double xp, vp;
@@ -174,7 +190,6 @@ __device__ bool ens_tiles_cluster(const EnsTilesArgs &a, EnsTilesSmem<M> &z, int
                 agent_store(r + 3 + d, vp);
             }
             agent_store(r + 6, m);
-            agent_store((uint64_t *)(r + 7), (uint64_t)(p0 + tid));
         }
         stores_done();
         __syncthreads();
@@ -222,20 +237,24 @@ __device__ bool ens_tiles_cluster(const EnsTilesArgs &a, EnsTilesSmem<M> &z, int
         // force: 64 / S rows a wave
         const int32_t S = ens_split(n_act, e.smin), ls = 31 - __builtin_clz(S);
         const int32_t slice = lane & (S - 1);
+        double *plane = part + tile * stride;
         for (int32_t q0 = wave << (6 - ls); q0 < n_act; q0 += 4 << (6 - ls)) {
             const int32_t q = q0 + (lane >> ls);
+            int64_t to = 0;   // the row of the plane, or -1 - m for the tile's own member m
             double xi[3] = {0.0, 0.0, 0.0}, vi[3] = {0.0, 0.0, 0.0}, mi = 0.0;
             int32_t own = -1;  // the row's own slot in the tile (none on padding)
             if (q < n_act) {
                 const int32_t rt = z.row_tile[q];
-                const double *r = rec + ((int64_t)lo + rt * TJ + (q - z.row_base[rt])) * TL_WORDS;
+                const int32_t m = q - z.row_base[rt];
+                const double *r = part + rt * (stride + TJ * ET_WORDS) + m * ET_WORDS;
+                to = rt == tile ? -1 - m : rt * TJ + m;
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
                     xi[d] = agent_load(r + d);
                     vi[d] = agent_load(r + 3 + d);
                 }
                 mi = agent_load(r + 6);
-                own = (int32_t)agent_load((const uint64_t *)(r + 7)) - p0;
+                if (rt == tile) own = z.mem[m];
             }
             const typename M::I ii = M::make_i(xi, vi, mi);
             typename M::Sum F = M::sum_zero();
@@ -246,12 +265,15 @@ __device__ bool ens_tiles_cluster(const EnsTilesArgs &a, EnsTilesSmem<M> &z, int
                 const Out7 o = M::out(F);
 #pragma unroll
                 for (int d = 0; d < 7; ++d) st[(lane >> ls) * TL_WORDS + d] = o.v[d];
-                st[(lane >> ls) * TL_WORDS + 7] = 0.0;
+                st[(lane >> ls) * TL_WORDS + 7] = __longlong_as_double((long long)to);
             }
             __builtin_amdgcn_wave_barrier();
-            for (int32_t w = lane; w < (64 >> ls) * TL_WORDS; w += 64)
-                if (q0 + w / TL_WORDS < n_act)
-                    agent_store(part + ((int64_t)tile * n_c + q0) * TL_WORDS + w, st[w]);
+            for (int32_t w = lane; w < (64 >> ls) * TL_WORDS; w += 64) {
+                const int32_t d = w & 7, at = (int32_t)__double_as_longlong(st[w | 7]);
+                if (q0 + (w >> 3) >= n_act || d == 7) continue;
+                if (at < 0) z.own[-1 - at][d] = st[w];
+                else agent_store(plane + at * ET_WORDS + d, st[w]);
+            }
             __builtin_amdgcn_wave_barrier();
         }
         stores_done();
@@ -265,12 +287,12 @@ __device__ bool ens_tiles_cluster(const EnsTilesArgs &a, EnsTilesSmem<M> &z, int
             // 64 rows at a time: lane 8 r + d of a unit of 8 rows takes sum d of row r, then the
             // row's own work-item corrects its particle
             const int32_t d = lane & 7;
-            const double *src = part + (int64_t)base * TL_WORDS + d;
             for (int32_t c0 = 0; c0 < n_own; c0 += 64) {
                 for (int32_t r0 = wave * 8; r0 < 64 && c0 + r0 < n_own; r0 += 32) {
                     const int32_t r = r0 + (lane >> 3);
                     if (c0 + r < n_own && d < 7)
-                        z.sums[r][d] = ens_planes_sum(src + (int64_t)(c0 + r) * TL_WORDS, (int64_t)n_c * TL_WORDS, T);
+                        z.sums[r][d] = ens_planes_sum(part + (tile * TJ + c0 + r) * ET_WORDS + d, stride, T,
+                                                      tile, z.own[c0 + r][d]);
                 }
                 __syncthreads();
                 if (member && row >= c0 && row < c0 + 64) {

@@ -164,7 +164,6 @@ struct nb_ens {
     std::vector<int32_t> tile_off_h, tables_h;
     int32_t *tile_off = nullptr, *tables = nullptr;
     uint64_t *assign = nullptr, *word = nullptr;
-    double *rec = nullptr;
     hipGraphExec_t gexec = nullptr;
     hipGraph_t graph = nullptr;
     double g_eta = -1.0;
@@ -596,7 +595,9 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     a.T = (c->n + TJ - 1) / TJ;
     a.R = std::max(1, std::min(c->num_cu / a.T, TL_REPS));
     // blocks of more rows (in LDS: the row map; in the partial planes, held twice) go to the chain
-    const int64_t room = c->partial_rows * 7 / (2 * (int64_t)a.T * TL_WORDS);
+    // (past 64 tiles the chain's items join tiles for blocks that large: 7/8 of the room keeps the
+    // sums of both in one order)
+    const int64_t room = c->partial_rows * (a.T > 64 ? 7 : 8) / (16 * (int64_t)a.T);
     a.limit = (int32_t)std::min<int64_t>(room, TL_ROWS);
     a.steps = steps;
     a.epoch = c->tile_epoch;
@@ -688,8 +689,7 @@ void ctx_plan(nb_ctx *c) {
     // the tiled path: the partial sums of every block row on every tile, held twice, up to 64
     // tiles (larger contexts take the room there is)
     const int64_t T = (n + TJ - 1) / TJ;
-    if (T <= 64)
-        rows = std::max<int64_t>(rows, (2 * T * std::min<int64_t>(n, TL_ROWS) * TL_WORDS + 6) / 7);
+    if (T <= 64) rows = std::max<int64_t>(rows, 2 * T * std::min<int64_t>(n, TL_ROWS));
     c->partial_rows = rows;
     const int64_t N = n;
     c->sched_groups = (int32_t)std::min<int64_t>(std::max<int64_t>((N + 4095) / 4096, 1), 1024);
@@ -1536,7 +1536,7 @@ void ens_plan(nb_ens *e, int32_t n_clusters, const int32_t *offsets, int32_t pre
         const int32_t n_c = offsets[c + 1] - offsets[c];
         e->prow_h[c] = n_c;
         // 7 sums per row and tile, and one word of padding where a run's teams keep them
-        e->part_off_h[c + 1] = e->part_off_h[c] + (int64_t)((n_c + TJ - 1) / TJ) * TL_WORDS * n_c;
+        e->part_off_h[c + 1] = e->part_off_h[c] + (int64_t)((n_c + TJ - 1) / TJ) * 7 * n_c;
     }
     e->tile_off_h.assign(1, 0);
     for (int32_t c = 0; c < n_clusters; ++c)
@@ -1574,12 +1574,11 @@ size_t ens_layout(nb_ens *e, char *base) {
     e->crit = k.take<double>(2 * N);
     e->ek = k.take<double>(2 * C);
     e->ep = base ? e->ek + C : nullptr;
-    // the teams of a run: tables, words, published records
+    // the teams of a run: tables and words (records and partial sums take the partial planes)
     e->tile_off = k.take<int32_t>(C + 1);
     e->tables = k.take<int32_t>(EnsTables::words(e->C));
     e->assign = k.take<uint64_t>(ET_WGS);
     e->word = k.take<uint64_t>(3 * (size_t)e->tile_off_h[C]);
-    e->rec = k.take<double>(2 * N * TL_WORDS);
     return k.off;
 }
 
@@ -1697,7 +1696,7 @@ nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64
         a.epoch = e->tile_epoch;
         a.t = EnsTables(e->tables, e->C);
         a.assign = e->assign; a.turn = e->turn; a.tile_off = e->tile_off;
-        a.word = e->word; a.rec = e->rec;
+        a.word = e->word;
         e->tile_epoch += (uint64_t)a.steps + 3;
         e->turn += (uint64_t)e->C + 2;
         void *args[] = {&a};

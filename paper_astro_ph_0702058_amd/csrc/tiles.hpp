@@ -48,7 +48,8 @@ constexpr int TL_SUB = TL_WG / WG;   // force items a workgroup works on at a ti
 constexpr int TL_TILES = 256;        // most tiles (one workgroup per compute unit)
 constexpr int TL_REPS = 16;          // most workgroups per tile
 constexpr int TL_ROWS = 8192;        // most block rows of a step (row map in LDS)
-constexpr int TL_WORDS = 8;          // doubles of a published record and of a partial sum
+constexpr int TL_WORDS = 8;          // doubles of a published record
+constexpr int TL_SUMS = 7;           // doubles of a row's partial sums
 constexpr int TL_SHIFT = 24;         // a published word: epoch << 24 | level << 16 | count
 constexpr uint32_t TL_POLLS = 1u << 24;  // about a quarter of a minute
 
@@ -63,7 +64,7 @@ struct TilesArgs {
     uint64_t *word;      // [2][T] published words, by epoch parity
     uint64_t *arrive;    // [T * R] epoch whose partial sums a workgroup has stored
     double *rec[2];      // [T][TJ][TL_WORDS] published records, by epoch parity
-    double *part;        // [2][T][limit][TL_WORDS] partial sums, by epoch parity
+    double *part;        // [2][T][limit][TL_SUMS] partial sums, by epoch parity
     DevControl *ctl;
     double eps2, eta;
     int32_t lmin, lmax;
@@ -338,7 +339,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
         const int32_t ib = WG >> ls, n_iblk = (n_act + ib - 1) >> (8 - ls);
         const int32_t sub = wave >> 2, tt = tid & (WG - 1);
         const int32_t slice = (tt & (L - 1)) >> (H > 1 ? 2 : 0);  // H is 4 or 1
-        double *part = a.part + ((int64_t)par * T + tile) * a.limit * TL_WORDS;
+        double *part = a.part + ((int64_t)par * T + tile) * a.limit * TL_SUMS;
         for (int32_t iblk = rep + R * sub; iblk < n_iblk; iblk += R * TL_SUB) {
             const int32_t q = iblk * ib + (tt >> ls);
             const int32_t q0 = iblk * ib + ((tt & ~63) >> ls);    // the wave's first row
@@ -360,18 +361,19 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
             typename M::Sum F = M::sum_zero();
             tile_sums<M, UNR, true, std::is_same<M, ModeF32>::value>(ii, sm, slice, S, H, own, eps2, F);
             lanes_add<M>(F, L, H);
-            // the wave's rows, transposed through its own LDS slice: 64-byte records stored whole
+            // the wave's rows, transposed through its own LDS slice: lanes store consecutive words
             double *st = stage[wave];
             if ((lane & (L - 1)) == 0) {
                 const Out7 o = M::out(F);
 #pragma unroll
                 for (int c = 0; c < 6; ++c) st[(lane >> ls) * TL_WORDS + c] = o.v[c];
                 st[(lane >> ls) * TL_WORDS + 6] = -o.v[6];
-                st[(lane >> ls) * TL_WORDS + 7] = 0.0;
             }
             __builtin_amdgcn_wave_barrier();
-            for (int32_t e = lane; e < (64 >> ls) * TL_WORDS; e += 64)
-                if (q0 + e / TL_WORDS < n_act) agent_store(part + (int64_t)q0 * TL_WORDS + e, st[e]);
+            for (int32_t e = lane; e < (64 >> ls) * TL_WORDS; e += 64) {
+                const int32_t r = q0 + e / TL_WORDS, c = e % TL_WORDS;
+                if (r < n_act && c < TL_SUMS) agent_store(part + (int64_t)r * TL_SUMS + c, st[e]);
+            }
             __builtin_amdgcn_wave_barrier();
         }
         stores_done();
@@ -395,8 +397,8 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
             int32_t lane_c = lane;  // opaque: addresses are formed here, not spilled all launch
             asm volatile("" : "+v"(lane_c));
             const int32_t units = (cnt + 7) / 8, c = lane_c & 7;
-            const int64_t stride = (int64_t)a.limit * TL_WORDS;
-            const double *src0 = a.part + (int64_t)par * T * stride + (int64_t)base * TL_WORDS + c;
+            const int64_t stride = (int64_t)a.limit * TL_SUMS;
+            const double *src0 = a.part + (int64_t)par * T * stride + (int64_t)base * TL_SUMS + c;
             const bool spread = units <= TL_UNITS;
             if (spread) {
 #pragma unroll
@@ -404,7 +406,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
                     const int32_t m = u * 8 + (lane_c >> 3);
                     if (u < units)
                         stage[wave][u * 64 + lane_c] =
-                            m < cnt && c < 7 ? planes_sum(src0 + m * TL_WORDS, stride, wave, T) : 0.0;
+                            m < cnt && c < 7 ? planes_sum(src0 + m * TL_SUMS, stride, wave, T) : 0.0;
                 }
                 __syncthreads();
             }
@@ -417,7 +419,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
 #pragma unroll
                     for (int k = 1; k < RW; ++k) t += stage[k][u * 64 + lane_c];
                 } else if (live) {
-                    const double *src = src0 + m * TL_WORDS;
+                    const double *src = src0 + m * TL_SUMS;
                     t = planes_sum(src, stride, 0, T);
 #pragma unroll 1
                     for (int32_t k = 1; k < RW; ++k) t += planes_sum(src, stride, k, T);
