@@ -44,6 +44,7 @@ struct DevControl {
     // word); zero between steps
     uint64_t sel;
     int32_t tile_steps;     // block steps the last tiled launch took
+    int32_t tile_end;       // why it ended (TL_RAN, TL_MOVED)
 };
 
 // ------------------------------------------------------------------------------------------
@@ -1288,6 +1289,7 @@ __global__ void __launch_bounds__(WG) reset_control(DevControl *ctl) {
         ctl->n_active_sum = 0; ctl->n_act = 0; ctl->flags = 0; ctl->t_cand = 0;
         ctl->n_pending = 0; ctl->done = 0; ctl->flag_nonfinite = 0; ctl->flag_dtmin = 0;
         ctl->flag_sched = 0; ctl->flag_wait = 0; ctl->sel = 0; ctl->tile_steps = 0;
+        ctl->tile_end = 0;
     }
 }
 
@@ -1296,6 +1298,11 @@ __global__ void __launch_bounds__(WG) set_t_end(DevControl *ctl, int64_t t_end) 
         ctl->t_end = t_end;
         ctl->done = 0;
     }
+}
+
+// The block corrected last has its new levels (sched_newlevel's launch is over).
+__global__ void __launch_bounds__(WG) levels_done(DevControl *ctl) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->n_pending = 0;
 }
 
 struct StateRW {

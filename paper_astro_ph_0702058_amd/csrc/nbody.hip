@@ -545,6 +545,18 @@ nb_status enqueue_step(nb_ctx *c, double eta, hipStream_t s) {
     return NB_OK;
 }
 
+// One block step by the separate launches: the block is every particle at the smallest t_i + dt_i,
+// which holds for any particle times (the fused steps count on times that fit the scheduler's).
+nb_status enqueue_apart_step(nb_ctx *c, double eta, hipStream_t s) {
+    nb_status r;
+    if ((r = enqueue_schedule(c, eta, s)) != NB_OK) return r;
+    if ((r = enqueue_predict(c, nullptr, 1, s)) != NB_OK) return r;
+    if ((r = enqueue_force(c, c->var_block, 1, c->active, &c->ctl->n_act, c->n, c->acc1, c->jerk1,
+                           c->pot1, c->n, s)) != NB_OK)
+        return r;
+    return enqueue_correct(c, c->acc1, c->jerk1, c->pot1, s);
+}
+
 // nb_run's resident path: contexts of at most resident_max softened particles in the FP32,
 // double-single or FP64 arithmetic.
 bool use_resident(const nb_ctx *c) {
@@ -1003,7 +1015,7 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
     if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, NB_EINVAL, "eta must be > 0");
     set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, t_end);
     LAUNCH_OK(c);
-    const bool tiles = use_tiles(c) && (use_graph || c->n <= RES_MAX);
+    bool tiles = use_tiles(c) && (use_graph || c->n <= RES_MAX);
     const bool resident = use_resident(c) && !c->profile;
     if (resident || tiles) {  // new levels of a block corrected by a separate nb_correct
         sched_newlevel<<<grid_for(c->n, 2048), WG, 0, c->stream>>>(state_rw(c), c->active, c->crit,
@@ -1014,6 +1026,10 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
     // step, or for ever longer stretches while such blocks come within a few steps of each other
     int32_t chain_left = 0, stretch = 1;
     int64_t done_steps = 0;
+    // particle times that do not fit the scheduler's (nb_shared_step moves them, a state may be
+    // bound in mid-run): the resident workgroup, whose blocks are the smallest t_i + dt_i, takes a
+    // set that it holds; a larger one takes tiles from the state's own time, or steps apart
+    bool retimed = false, apart = false;
     for (;;) {
         int32_t k = chunk;
         if (max_steps > 0) k = (int32_t)std::min<int64_t>(k, max_steps - done_steps);
@@ -1024,8 +1040,10 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
             return r;
         if (!tiled) {
             if (chain_left > 0) k = std::min(k, chain_left);
-            if ((r = resident ? enqueue_resident(c, eta, k, c->stream)
-                              : nb_step(c, eta, k, use_graph)) != NB_OK)
+            for (int32_t i = 0; apart && i < k; ++i)
+                if ((r = enqueue_apart_step(c, eta, c->stream)) != NB_OK) return r;
+            if (!apart && (r = resident ? enqueue_resident(c, eta, k, c->stream)
+                                        : nb_step(c, eta, k, use_graph)) != NB_OK)
                 return r;
             chain_left = std::max(0, chain_left - k);
         }
@@ -1041,14 +1059,29 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
         HIP_OK(c, hipStreamSynchronize(c->stream));
         if (h.flag_nonfinite) return fail(c, NB_ENONFINITE, "non-finite force or state on device");
         if (h.flag_wait) return fail(c, NB_EDEVICE, "the workgroups of a tiled run did not meet");
-        if (h.done) break;
-        if (tiled) {
+        if (h.done || (retimed && h.flag_sched)) break;
+        if (tiled && h.tile_end == TL_MOVED) {
+            tiles = !resident && !retimed;
+            apart = !resident && retimed;
+            if (tiles) {
+                tiles_time<<<1, WG, 0, c->stream>>>(state_rw(c), c->lmax, c->ctl);
+                LAUNCH_OK(c);
+                retimed = true;
+            }
+        } else if (tiled) {
             done_steps += h.tile_steps;
             if (h.tile_steps < k) {
                 stretch = h.tile_steps < 8 ? std::min(stretch * 2, 1024) : 1;
                 chain_left = stretch;
             }
         }
+    }
+    if (apart) {  // the last block has its new levels, as after the other steps
+        sched_newlevel<<<grid_for(c->n, 2048), WG, 0, c->stream>>>(state_rw(c), c->active, c->crit, eta,
+                                                                    c->lmin, c->lmax, c->ctl);
+        LAUNCH_OK(c);
+        levels_done<<<1, WG, 0, c->stream>>>(c->ctl);
+        LAUNCH_OK(c);
     }
     // leave the scheduler open-ended again
     set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, INT64_MAX);

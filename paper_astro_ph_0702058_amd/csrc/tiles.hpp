@@ -26,6 +26,13 @@
 // wait gives up after TL_POLLS polls; the run then reports an error and leaves the state as it
 // was before the launch.
 //
+// The histogram gives the block time only while every particle's t_i is the last multiple of its
+// step not after the scheduler's time; then a block is never empty, somebody waits for all
+// arrivals in every step, and no workgroup can be two epochs ahead of another (what the reuse of
+// words, records and sums every second epoch needs).  The correctors keep it so; a launch checks it
+// of the state it is given, which calls other than the block steps may have moved, and ends without
+// a step if it does not hold (tile_end TL_MOVED).
+//
 // What bounds a step (MI355X, N = 16384 FP32, mean block 230, cycles at 2.15 GHz): the rows' tile
 // sums 11000 (one wave's serial chain over 256 j), the two meetings 8000, record and partial-sum
 // loads 4000, selection, prediction and the corrector 10000.  Only the waves that hold the tile
@@ -52,6 +59,10 @@ constexpr int TL_WORDS = 8;          // doubles of a published record
 constexpr int TL_SUMS = 7;           // doubles of a row's partial sums
 constexpr int TL_SHIFT = 24;         // a published word: epoch << 24 | level << 16 | count
 constexpr uint32_t TL_POLLS = 1u << 24;  // about a quarter of a minute
+
+// How a launch ended (DevControl::tile_end).
+constexpr int32_t TL_RAN = 0;    // its steps, t_end, or a block of more rows than its limit
+constexpr int32_t TL_MOVED = 1;  // without a step: a particle's time does not fit the scheduler's
 
 struct TilesArgs {
     StateRW g;           // the state
@@ -167,6 +178,28 @@ __device__ __forceinline__ TilesArgs tiles_args() {
     return a;
 }
 
+// The scheduler's time moved on to the state's (its latest particle time), for a launch that ended
+// with TL_MOVED.  A particle whose next time lies before the first multiple of the finest step
+// after the scheduler's time is behind it, as the launch chain reports.  One workgroup.
+__global__ void __launch_bounds__(WG) tiles_time(StateRW s, int32_t lmax, DevControl *ctl) {
+    __shared__ int64_t red[WG / 64];
+    int64_t late = -ctl->t_cur, next = INT64_MAX, fine = 0;
+    for (int32_t i = threadIdx.x; i < s.n; i += WG) {
+        const int32_t l = s.level[i] < lmax ? s.level[i] : lmax;
+        const int64_t tn = s.tick[i] + ((int64_t)1 << (lmax - l));
+        late = -s.tick[i] < late ? -s.tick[i] : late;
+        next = tn < next ? tn : next;
+        fine = -(int64_t)l < fine ? -(int64_t)l : fine;
+    }
+    late = wg_min_i64(late, red);
+    next = wg_min_i64(next, red);
+    fine = wg_min_i64(fine, red);
+    if (threadIdx.x == 0) {
+        if (next < level_time(ctl->t_cur, (int32_t)-fine, lmax)) ctl->flag_sched = 1;
+        else ctl->t_cur = -late;
+    }
+}
+
 // Rows of 8 block rows a wave corrects at a time when the waves share the planes (below).
 constexpr int TL_UNITS = 4;
 
@@ -188,11 +221,15 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (ctl->done) {  // the same for every workgroup
-        if (blockIdx.x == 0 && tid == 0) ctl->tile_steps = 0;
+        if (blockIdx.x == 0 && tid == 0) {
+            ctl->tile_steps = 0;
+            ctl->tile_end = TL_RAN;
+        }
         return;
     }
     const int32_t T = a.T, R = a.R, G = T * R, lmax = a.lmax;
     const int32_t tile = (int32_t)blockIdx.x % T, rep = (int32_t)blockIdx.x / T;
+    int64_t t_cur = ctl->t_cur, act_sum = 0;
     int32_t p0, n_t;
     if (tid < NLEV) hist[tid] = 0;
     if (tid < TL_TILES) owner[tid] = 0;
@@ -211,13 +248,18 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
         }
         if (tid < TJ) {
             const bool in = tid < n_t;
-            const int32_t l = in ? g.level[p0 + tid] & (NLEV - 1) : 0;
+            const int32_t lg = in ? g.level[p0 + tid] : 0;
+            const bool held = lg >= 0 && lg <= lmax;
+            const int32_t l = held ? lg : 0;
             lm[tid] = in ? g.m[p0 + tid] : 0.0;
             lpot[tid] = in ? g.pot[p0 + tid] : 0.0;
             ltick[tid] = in ? g.tick[p0 + tid] : 0;
             lnext[tid] = in ? ltick[tid] + ((int64_t)1 << (lmax - l)) : INT64_MAX;  // never a member
             llevel[tid] = l;
-            if (in) atomicAdd(&hist[l], 1);
+            // a particle out of step with the scheduler counts on a level that there is not, finer
+            // than all
+            const bool fits = held && lnext[tid] == level_time(t_cur, l, lmax);
+            if (in) atomicAdd(&hist[fits ? l : NLEV - 1], 1);
         }
     }
     StateRW s;
@@ -225,10 +267,9 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     s.n = TJ;
     s.tick_len = a.g.tick_len;
     const auto eps2 = eps_as<M>(a.eps2);
-    int64_t t_cur = ctl->t_cur, act_sum = 0;
     const int64_t t_end = ctl->t_end;
     int32_t stepped = 0, n_last = 0, last_base = 0, last_cnt = 0, last_par = 0;
-    bool done = false, bad = false, clamp = false, behind = false, lost = false;
+    bool done = false, bad = false, clamp = false, behind = false, lost = false, moved = false;
     __syncthreads();
     while (stepped < a.steps) {
         const uint64_t epoch = a.epoch + (uint64_t)stepped;
@@ -237,7 +278,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
         // select: the tile's own next block time and its members (the waves that hold them)
         if (wave < TJ / 64) {
             const int32_t lf = 63 - __builtin_clzll(__ballot(hist[lane] > 0) | 1ull);
-            const int64_t t_own = level_time(t_cur, lf, lmax);
+            const int64_t t_own = lf > lmax ? INT64_MIN : level_time(t_cur, lf, lmax);
             int32_t n_own = 0, below = 0;
             bool member = false;
             uint64_t mask = 0;
@@ -292,15 +333,16 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) fine = o4[k] >> 16 > fine ? o4[k] >> 16 : fine;
             fine = wave_max(fine);
-            const int64_t tn = level_time(t_cur, fine, lmax);
+            const bool odd = fine > lmax;  // first step only: no time, and more rows than any limit
+            const int64_t tn = odd ? INT64_MIN : level_time(t_cur, fine, lmax);
             int32_t c4[4], sum = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                c4[k] = level_time(t_cur, o4[k] >> 16, lmax) == tn ? o4[k] & 0xffff : 0;
+                c4[k] = !odd && level_time(t_cur, o4[k] >> 16, lmax) == tn ? o4[k] & 0xffff : 0;
                 sum += c4[k];
             }
             const int32_t inc = wave_scan_add(sum);
-            const int32_t rows = __builtin_amdgcn_readlane(inc, 63);
+            const int32_t rows = odd ? INT32_MAX : __builtin_amdgcn_readlane(inc, 63);
             const bool taken = tn <= t_end && rows <= a.limit;
             if (wave >= 12) {  // the row map, one owner of each lane per wave
                 if (tid == 12 * 64) {
@@ -331,7 +373,10 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
             break;
         }
         const int32_t n_act = __builtin_amdgcn_readfirstlane(plan_rows);
-        if (n_act > a.limit) break;
+        if (n_act > a.limit) {
+            moved = t_next == INT64_MIN;
+            break;
+        }
         // force: i-blocks of WG / L rows against the tile, TL_SUB at a time
         int32_t S, H;
         row_lanes(n_act, a.sp, S, H);
@@ -476,6 +521,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     if (blockIdx.x == 0 && tid == 0) {
         ctl->n_pending = 0;  // levels are current
         ctl->tile_steps = stepped;
+        ctl->tile_end = moved ? TL_MOVED : TL_RAN;
         if (stepped > 0) {
             ctl->t_cur = t_cur;
             ctl->t_next = t_cur;
