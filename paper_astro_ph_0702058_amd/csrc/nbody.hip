@@ -20,6 +20,7 @@
 #include "ens_tiles.hpp"
 #include "ensemble.hpp"
 #include "kernels.hpp"
+#include "run_loop.hpp"
 #include "tiles.hpp"
 
 using namespace nbody;
@@ -1015,68 +1016,52 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
     if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, NB_EINVAL, "eta must be > 0");
     set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, t_end);
     LAUNCH_OK(c);
-    bool tiles = use_tiles(c) && (use_graph || c->n <= RES_MAX);
-    const bool resident = use_resident(c) && !c->profile;
-    if (resident || tiles) {  // new levels of a block corrected by a separate nb_correct
+    RunLoop loop{chunk, max_steps, use_tiles(c) && (use_graph || c->n <= RES_MAX),
+                 use_resident(c) && !c->profile};
+    if (loop.resident || loop.tiles) {  // new levels of a block corrected by a separate nb_correct
         sched_newlevel<<<grid_for(c->n, 2048), WG, 0, c->stream>>>(state_rw(c), c->active, c->crit,
                                                                     eta, c->lmin, c->lmax, c->ctl);
         LAUNCH_OK(c);
     }
-    // a block too large for the tiled path ends its launch and takes the launch chain: for one
-    // step, or for ever longer stretches while such blocks come within a few steps of each other
-    int32_t chain_left = 0, stretch = 1;
-    int64_t done_steps = 0;
-    // particle times that do not fit the scheduler's (nb_shared_step moves them, a state may be
-    // bound in mid-run): the resident workgroup, whose blocks are the smallest t_i + dt_i, takes a
-    // set that it holds; a larger one takes tiles from the state's own time, or steps apart
-    bool retimed = false, apart = false;
-    for (;;) {
-        int32_t k = chunk;
-        if (max_steps > 0) k = (int32_t)std::min<int64_t>(k, max_steps - done_steps);
-        if (k <= 0) break;
-        bool tiled = false;
-        if (tiles && chain_left == 0 && c->tiles_ok &&
-            (r = enqueue_tiles(c, eta, k, c->stream, tiled)) != NB_OK)
-            return r;
-        if (!tiled) {
-            if (chain_left > 0) k = std::min(k, chain_left);
-            for (int32_t i = 0; apart && i < k; ++i)
-                if ((r = enqueue_apart_step(c, eta, c->stream)) != NB_OK) return r;
-            if (!apart && (r = resident ? enqueue_resident(c, eta, k, c->stream)
-                                        : nb_step(c, eta, k, use_graph)) != NB_OK)
-                return r;
-            chain_left = std::max(0, chain_left - k);
+    RunLoop::Path path;
+    for (int32_t k; loop.next(path, k);) {
+        switch (path) {
+            case RunLoop::TILES: {
+                bool launched = false;
+                if ((r = enqueue_tiles(c, eta, k, c->stream, launched)) != NB_OK) return r;
+                if (!launched) {
+                    loop.refused();
+                    continue;
+                }
+                break;
+            }
+            case RunLoop::RESIDENT: r = enqueue_resident(c, eta, k, c->stream); break;
+            case RunLoop::CHAIN: r = nb_step(c, eta, k, use_graph); break;
+            case RunLoop::APART:
+                for (int32_t i = 0; i < k && r == NB_OK; ++i) r = enqueue_apart_step(c, eta, c->stream);
+                break;
         }
+        if (r != NB_OK) return r;
         // the resident workgroup does not write the j-particle stream; nor may a force follow a
         // run that could have taken it
-        c->predicted = !resident;
-        if (!tiled) {
-            done_steps += k;
-            if (tiles && k == 1 && chain_left == 0) continue;  // the next tiled launch sees `done`
-        }
+        c->predicted = !loop.resident;
+        if (!loop.enqueued(path, k)) continue;
         DevControl h;
         HIP_OK(c, hipMemcpyAsync(&h, c->ctl, sizeof h, hipMemcpyDeviceToHost, c->stream));
         HIP_OK(c, hipStreamSynchronize(c->stream));
         if (h.flag_nonfinite) return fail(c, NB_ENONFINITE, "non-finite force or state on device");
         if (h.flag_wait) return fail(c, NB_EDEVICE, "the workgroups of a tiled run did not meet");
-        if (h.done || (retimed && h.flag_sched)) break;
-        if (tiled && h.tile_end == TL_MOVED) {
-            tiles = !resident && !retimed;
-            apart = !resident && retimed;
-            if (tiles) {
+        if (h.done || (loop.retimed && h.flag_sched)) break;
+        if (path == RunLoop::TILES && h.tile_end == TL_MOVED) {
+            if (loop.moved()) {
                 tiles_time<<<1, WG, 0, c->stream>>>(state_rw(c), c->lmax, c->ctl);
                 LAUNCH_OK(c);
-                retimed = true;
             }
-        } else if (tiled) {
-            done_steps += h.tile_steps;
-            if (h.tile_steps < k) {
-                stretch = h.tile_steps < 8 ? std::min(stretch * 2, 1024) : 1;
-                chain_left = stretch;
-            }
+        } else if (path == RunLoop::TILES) {
+            loop.tiled(k, h.tile_steps);
         }
     }
-    if (apart) {  // the last block has its new levels, as after the other steps
+    if (loop.apart) {  // the last block has its new levels, as after the other steps
         sched_newlevel<<<grid_for(c->n, 2048), WG, 0, c->stream>>>(state_rw(c), c->active, c->crit, eta,
                                                                     c->lmin, c->lmax, c->ctl);
         LAUNCH_OK(c);
