@@ -109,7 +109,7 @@ struct nb_ctx {
     int32_t resident_max = 1024;         // nb_run: one resident workgroup up to this n
     // nb_run above that: one cooperative launch of tile owners (tiles.hpp)
     bool tiles_ok = true;                // cleared when the device refuses the launch
-    uint64_t tile_epoch = 1;             // first epoch of the next launch
+    Epochs epochs;                       // of its launches
     uint64_t *tile_word = nullptr, *tile_arrive = nullptr;
     Variant var_full{2, 2, 4096, 256, 16};   // calls on (nearly) all particles
     Variant var_block{2, 2, 4096, 256, 16};  // block-step calls (device-resident count)
@@ -160,7 +160,7 @@ struct nb_ens {
     int32_t smin = 8;  // fewest lanes per block particle in a force item
     // runs in one launch of teams (ens_tiles.hpp)
     bool teams_ok = true;         // cleared when the device refuses the launch
-    uint64_t tile_epoch = 1, turn = 1;
+    Epochs epochs, turns;         // of its launches
     int32_t n_wgs = 0;
     std::vector<int32_t> tile_off_h, tables_h;
     int32_t *tile_off = nullptr, *tables = nullptr;
@@ -613,8 +613,12 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     const int64_t room = c->partial_rows * (a.T > 64 ? 7 : 8) / (16 * (int64_t)a.T);
     a.limit = (int32_t)std::min<int64_t>(room, TL_ROWS);
     a.steps = steps;
-    a.epoch = c->tile_epoch;
-    c->tile_epoch += (uint64_t)steps + 2;
+    bool again;
+    a.epoch = c->epochs.take((uint64_t)steps + 2, again);
+    if (again) {
+        zero_words<<<1, WG, 0, s>>>((int64_t *)c->tile_word, 3 * TL_TILES, nullptr, 0);
+        LAUNCH_OK(c);
+    }
     a.word = c->tile_word; a.arrive = c->tile_arrive;
     // records in the energy's and the adjoint's scratch (8 and 12 doubles per particle), which
     // hold nothing between calls
@@ -832,7 +836,7 @@ nb_status nb_bind_scratch(nb_ctx *c, void *scratch, size_t bytes) {
     LAUNCH_OK(c);
     zero_words<<<1, WG, 0, c->stream>>>((int64_t *)c->tile_word, 3 * TL_TILES, nullptr, 0);
     LAUNCH_OK(c);
-    c->tile_epoch = 1;
+    c->epochs = Epochs{};
     reset_control<<<1, WG, 0, c->stream>>>(c->ctl);
     LAUNCH_OK(c);
     c->scratch_ok = true;
@@ -1684,7 +1688,7 @@ bool ens_plan_teams(nb_ens *e, const std::vector<EnsCluster> &cl, int64_t t_end)
     return true;
 }
 
-// nb_ens_run in one cooperative launch (per at most 2^20 block steps of a cluster).  done = false:
+// nb_ens_run in one cooperative launch (per at most TL_STEPS block steps of a cluster).  done = false:
 // not taken (the caller goes on with global steps).
 nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64_t max_steps, bool &done) {
     done = false;
@@ -1710,13 +1714,21 @@ nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64
         a.e = ens_view(e, t_end);
         a.s = ens_state(e);
         a.eta = eta;
-        a.steps = (int32_t)std::min<int64_t>(left, 1 << 20);
-        a.epoch = e->tile_epoch;
+        a.steps = (int32_t)std::min<int64_t>(left, TL_STEPS);
+        bool again, round;
+        a.epoch = e->epochs.take((uint64_t)a.steps + 3, again);
+        a.turn = e->turns.take((uint64_t)e->C + 2, round);
+        if (again) {
+            zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->word, 3 * e->tile_off_h[e->C], nullptr, 0);
+            ELAUNCH_OK(e);
+        }
+        if (round) {
+            zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->assign, ET_WGS, nullptr, 0);
+            ELAUNCH_OK(e);
+        }
         a.t = EnsTables(e->tables, e->C);
-        a.assign = e->assign; a.turn = e->turn; a.tile_off = e->tile_off;
+        a.assign = e->assign; a.tile_off = e->tile_off;
         a.word = e->word;
-        e->tile_epoch += (uint64_t)a.steps + 3;
-        e->turn += (uint64_t)e->C + 2;
         void *args[] = {&a};
         if (hipLaunchCooperativeKernel(ens_tiles_kernel(e->prec), dim3(e->n_wgs), dim3(WG), args, 0,
                                        e->stream) != hipSuccess) {
@@ -1897,7 +1909,7 @@ nb_status nb_ens_bind_scratch(nb_ens *e, void *scratch, size_t bytes) {
     zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->assign, ET_WGS, nullptr, 0);
     ELAUNCH_OK(e);
     EHIP_OK(e, hipStreamSynchronize(e->stream));
-    e->tile_epoch = 1; e->turn = 1;
+    e->epochs = e->turns = Epochs{};
     e->scratch_ok = true;
     e->initialised = false;
     return NB_OK;

@@ -7,6 +7,26 @@
 
 namespace nbody {
 
+constexpr int TL_SHIFT = 24;            // a published word: epoch << 24 | what it says
+constexpr int32_t TL_STEPS = 1 << 20;   // most block steps of one launch
+
+// The epochs (or turns) of launches whose workgroups meet through words that hold one above
+// TL_SHIFT bits: each launch takes as many as it may use, so they are used up in time (a launch
+// that ends early has taken them all the same).
+struct Epochs {
+    static constexpr uint64_t LAST = (1ull << (64 - TL_SHIFT)) - 1;
+    uint64_t next = 1;
+    // The first of n epochs for the next launch; again: they start over, and the words are to be
+    // zeroed before it.
+    uint64_t take(uint64_t n, bool &again) {
+        again = n > LAST - next;
+        if (again) next = 1;
+        const uint64_t first = next;
+        next += n;
+        return first;
+    }
+};
+
 struct RunLoop {
     enum Path {
         TILES,     // a cooperative launch of tile owners
@@ -30,7 +50,8 @@ struct RunLoop {
         if (max_steps > 0) k = (int32_t)std::min<int64_t>(k, max_steps - done_steps);
         if (k <= 0) return false;
         p = apart ? APART : tiles && chain_left == 0 ? TILES : resident ? RESIDENT : CHAIN;
-        if (p != TILES && chain_left > 0) k = std::min(k, chain_left);
+        if (p == TILES) k = std::min(k, TL_STEPS);
+        else if (chain_left > 0) k = std::min(k, chain_left);
         return true;
     }
 

@@ -47,6 +47,7 @@
 #include <type_traits>
 
 #include "ensemble.hpp"
+#include "run_loop.hpp"
 
 namespace nbody {
 
@@ -57,7 +58,6 @@ constexpr int TL_REPS = 16;          // most workgroups per tile
 constexpr int TL_ROWS = 8192;        // most block rows of a step (row map in LDS)
 constexpr int TL_WORDS = 8;          // doubles of a published record
 constexpr int TL_SUMS = 7;           // doubles of a row's partial sums
-constexpr int TL_SHIFT = 24;         // a published word: epoch << 24 | level << 16 | count
 constexpr uint32_t TL_POLLS = 1u << 24;  // about a quarter of a minute
 
 // How a launch ended (DevControl::tile_end).
@@ -72,7 +72,7 @@ struct TilesArgs {
     int32_t limit;       // most block rows (a larger block ends the launch)
     int32_t steps;       // most block steps
     uint64_t epoch;      // first epoch (above every epoch published before)
-    uint64_t *word;      // [2][T] published words, by epoch parity
+    uint64_t *word;      // [2][T] published words (epoch, level << 16 | count), by epoch parity
     uint64_t *arrive;    // [T * R] epoch whose partial sums a workgroup has stored
     double *rec[2];      // [T][TJ][TL_WORDS] published records, by epoch parity
     double *part;        // [2][T][limit][TL_SUMS] partial sums, by epoch parity

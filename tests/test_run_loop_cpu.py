@@ -46,13 +46,40 @@ int main(int argc, char **argv) {
 """
 
 
-@pytest.fixture(scope="module")
-def simulate(tmp_path_factory):
-    d = tmp_path_factory.mktemp("run_loop")
-    src, exe = str(d / "sim.cpp"), str(d / "sim")
-    open(src, "w").write(SIMULATION)
+EPOCHS = r"""
+#include "run_loop.hpp"
+#include <cstdio>
+using namespace nbody;
+int main() {
+    // launches of the most steps, ten times as many as use up all epochs
+    Epochs e;
+    const uint64_t n = TL_STEPS + 2;
+    uint64_t before = 0, over = 0;
+    for (uint64_t launch = 0; launch < 10 * (Epochs::LAST / n); ++launch) {
+        bool again;
+        const uint64_t first = e.take(n, again), last = first + n - 1;
+        if (first == 0 || last << TL_SHIFT >> TL_SHIFT != last) { printf("does not fit\n"); return 1; }
+        if (!again && first <= before) { printf("used before\n"); return 1; }
+        before = last;
+        over += again;
+    }
+    printf("%d\n", (int)over);
+}
+"""
+
+
+def _build(tmp_path_factory, name, text):
+    d = tmp_path_factory.mktemp(name)
+    src, exe = str(d / "a.cpp"), str(d / "a")
+    open(src, "w").write(text)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I",
                     os.path.join(ROOT, "paper_astro_ph_0702058_amd", "csrc"), "-o", exe, src], check=True)
+    return exe
+
+
+@pytest.fixture(scope="module")
+def simulate(tmp_path_factory):
+    exe = _build(tmp_path_factory, "run_loop", SIMULATION)
 
     def run(*args):
         r = subprocess.run([exe, *(str(int(a)) for a in args)], capture_output=True, text=True, timeout=60)
@@ -72,3 +99,11 @@ def test_every_run_ends(simulate, chunk, large, resident):
         assert at == total and done, (refuse, at, done)
         at, counted, done, looks = simulate(total, refuse, large, chunk, 37, 1, resident)
         assert at == counted == 37 and not done, (refuse, at, counted, done)
+
+
+def test_epochs_fit_their_words(tmp_path_factory):
+    """However many launches there were, an epoch fits above the words' low bits and is new, or the
+    words are zeroed for it."""
+    r = subprocess.run([_build(tmp_path_factory, "epochs", EPOCHS)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout
+    assert 9 <= int(r.stdout) <= 10
