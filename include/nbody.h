@@ -221,6 +221,14 @@ nb_status nb_run(nb_ctx *ctx, double eta, int64_t t_end, int64_t max_steps, int3
  * keeps every context on the chain. */
 nb_status nb_set_resident(nb_ctx *ctx, int32_t max_n);
 
+/* How nb_run's cooperative launches wait for the device.  Their workgroups meet in every step, so
+ * they start only together: where other work keeps some of them off the device, each looks for the
+ * others up to `polls` times (about 1 us a look; default 2^20, at most 2^24) and then all leave
+ * without a step, and the run goes on as if there were no such launches: by one resident workgroup
+ * (n <= max_n of nb_set_resident) or the launch chain.  polls = 0: no such launches at all.
+ * NB_EINVAL for polls outside [0, 2^24]. */
+nb_status nb_set_tiles(nb_ctx *ctx, int32_t polls);
+
 /* Sec. 4.2 energy diagnostic, synchronising: kinetic sum m v^2 / 2 and softened potential
  * energy -1/2 sum_i sum_{j != i} m_i m_j s^(-1/2), in double precision, of the state predicted
  * to the last completed block time (exact at times where all particles are synchronised).
@@ -391,6 +399,11 @@ nb_status nb_ens_set_lanes(nb_ens *ens, int32_t lanes, const int32_t *lane_of);
  * step whose clusters' blocks differ in size by orders of magnitude; the sums combine the
  * lanes' parts by wave shuffles in a fixed order.  NB_EINVAL otherwise.  Synchronising. */
 nb_status nb_ens_set_split(nb_ens *ens, int32_t smin);
+
+/* The same for an ensemble's cooperative launch (nb_set_tiles): up to `polls` looks until its
+ * workgroups run at the same time, else the run goes on by global steps.  polls = 0: global steps
+ * only, with the layout, split and lanes set above.  NB_EINVAL for polls outside [0, 2^24]. */
+nb_status nb_ens_set_teams(nb_ens *ens, int32_t polls);
 
 /* Sec. 2 start of run for every cluster: full force at time 0, initial steps from
  * Eq. initTimestep with this eta, times 0. */

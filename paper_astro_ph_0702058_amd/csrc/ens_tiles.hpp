@@ -4,8 +4,8 @@
 // A team of T resident workgroups takes one cluster of T tiles at a time and integrates it to the
 // end (tiles.hpp's block step, one workgroup per tile, the FP64 state of a particle in the
 // registers of its work-item), then takes the next cluster of that many tiles from their queue.
-// Teams of different sizes run side by side; nothing waits outside a team, the launch is
-// cooperative and every wait is bounded.
+// Teams of different sizes run side by side; nothing waits outside a team once all workgroups are
+// resident (roll_call), and every wait is bounded.
 //
 // What it replaces: global steps of two launches, in which every cluster shares the latency of
 // every step (about 50 us) and the number of steps is that of the cluster with the most.  512
@@ -58,6 +58,9 @@ struct EnsTilesArgs {
     uint64_t *assign;            // [teams] turn << TL_SHIFT | place: the team's current cluster
     uint64_t turn;               // first turn (above every turn published before)
     const int32_t *tile_off;     // tiles before each cluster
+    uint64_t *roll;              // as TilesArgs'
+    uint64_t present;
+    uint32_t polls;
     uint64_t *word;              // [total tiles][3]: words by epoch parity, then the arrival
 };
 
@@ -359,6 +362,10 @@ __global__ void __launch_bounds__(WG, WAVES) ens_tiles(EnsTilesArgs a) {
     __shared__ EnsTilesSmem<M> z;
     const int32_t tm = a.t.wg_team[blockIdx.x], tile = a.t.wg_tile[blockIdx.x];
     const EnsTeam team = a.t.team[tm];
+    if (threadIdx.x == 0)
+        z.late = !roll_call(a.roll, a.epoch, roll_count(a.roll, a.present), a.polls);
+    __syncthreads();
+    if (z.late) return;
     bool bad = false, clamp = false, behind = false, lost = false;
     int32_t place = team.first;
     for (uint64_t turn = a.turn; place < team.last;) {

@@ -44,7 +44,7 @@ struct DevControl {
     // word); zero between steps
     uint64_t sel;
     int32_t tile_steps;     // block steps the last tiled launch took
-    int32_t tile_end;       // why it ended (TL_RAN, TL_MOVED)
+    int32_t tile_end;       // why it ended (TL_RAN ...)
 };
 
 // ------------------------------------------------------------------------------------------

@@ -72,6 +72,12 @@ bool variant_compiled(int prec, const Variant &v) {
 
 }  // namespace
 
+// Looks at each other's start (about 1 us each) before the workgroups of a tiled or team launch
+// leave and the run goes on by another path: what other streams run is seldom longer than a second.
+constexpr int32_t TILE_POLLS = 1 << 20, TILE_POLLS_MAX = 1 << 24;
+
+constexpr int TILE_WORDS = 3 * TL_TILES + ROLL_WORDS;
+
 struct nb_ctx {
     int32_t n = 0;
     double eps = 0.0;
@@ -110,7 +116,9 @@ struct nb_ctx {
     // nb_run above that: one cooperative launch of tile owners (tiles.hpp)
     bool tiles_ok = true;                // cleared when the device refuses the launch
     Epochs epochs;                       // of its launches
-    uint64_t *tile_word = nullptr, *tile_arrive = nullptr;
+    uint64_t *tile_word = nullptr, *tile_arrive = nullptr, *tile_roll = nullptr;
+    uint64_t tile_present = 0;           // workgroups of all launches so far
+    int32_t tile_polls = TILE_POLLS;     // nb_set_tiles
     Variant var_full{2, 2, 4096, 256, 16};   // calls on (nearly) all particles
     Variant var_block{2, 2, 4096, 256, 16};  // block-step calls (device-resident count)
     int32_t max_target = 4096;           // partial planes are sized for targets up to this
@@ -161,10 +169,12 @@ struct nb_ens {
     // runs in one launch of teams (ens_tiles.hpp)
     bool teams_ok = true;         // cleared when the device refuses the launch
     Epochs epochs, turns;         // of its launches
+    uint64_t present = 0;         // workgroups of all launches so far
+    int32_t polls = TILE_POLLS;   // nb_ens_set_teams
     int32_t n_wgs = 0;
     std::vector<int32_t> tile_off_h, tables_h;
     int32_t *tile_off = nullptr, *tables = nullptr;
-    uint64_t *assign = nullptr, *word = nullptr;
+    uint64_t *assign = nullptr, *word = nullptr, *roll = nullptr;
     hipGraphExec_t gexec = nullptr;
     hipGraph_t graph = nullptr;
     double g_eta = -1.0;
@@ -595,7 +605,7 @@ nb_status enqueue_resident(nb_ctx *c, double eta, int32_t steps, hipStream_t s) 
 int32_t tiles_least(int prec) { return prec == NB_DS ? 257 : prec == NB_FP64 ? 401 : 513; }
 
 bool use_tiles(const nb_ctx *c) {
-    return c->tiles_ok && c->resident_max > 0 && !c->profile && c->eps > 0.0 &&
+    return c->tiles_ok && c->tile_polls > 0 && c->resident_max > 0 && !c->profile && c->eps > 0.0 &&
            c->n >= (c->n <= c->resident_max ? tiles_least(c->prec) : RES_MAX + 1) &&
            (c->n + TJ - 1) / TJ <= std::min<int32_t>(TL_TILES, c->num_cu) &&
            (c->prec == NB_FP32 || c->prec == NB_DS || c->prec == NB_FP64);
@@ -616,9 +626,13 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     bool again;
     a.epoch = c->epochs.take((uint64_t)steps + 2, again);
     if (again) {
-        zero_words<<<1, WG, 0, s>>>((int64_t *)c->tile_word, 3 * TL_TILES, nullptr, 0);
+        zero_words<<<1, WG, 0, s>>>((int64_t *)c->tile_word, TILE_WORDS, nullptr, 0);
         LAUNCH_OK(c);
+        c->tile_present = 0;
     }
+    a.roll = c->tile_roll;
+    a.present = c->tile_present + (uint64_t)(a.T * a.R);
+    a.polls = (uint32_t)c->tile_polls;
     a.word = c->tile_word; a.arrive = c->tile_arrive;
     // records in the energy's and the adjoint's scratch (8 and 12 doubles per particle), which
     // hold nothing between calls
@@ -637,7 +651,9 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
                   : c->prec == NB_DS ? (const void *)run_tiles<ModeDS, 1>
                                      : (const void *)run_tiles<ModeF64, 2>;
     launched = hipLaunchCooperativeKernel(f, dim3(a.T * a.R), dim3(TL_WG), args, 0, s) == hipSuccess;
-    if (!launched) {
+    if (launched) {
+        c->tile_present = a.present;
+    } else {
         (void)hipGetLastError();
         c->tiles_ok = false;
     }
@@ -766,8 +782,9 @@ size_t ctx_layout(nb_ctx *c, char *base) {
     c->adj_flag = k.take<int32_t>(4);
     c->t_zero = k.take<int64_t>(1);
     c->tune_n = k.take<int32_t>(1);
-    c->tile_word = k.take<uint64_t>(3 * TL_TILES);  // published words, then arrivals
+    c->tile_word = k.take<uint64_t>(TILE_WORDS);  // published words, arrivals, the roll call
     c->tile_arrive = base ? c->tile_word + 2 * TL_TILES : nullptr;
+    c->tile_roll = base ? c->tile_word + 3 * TL_TILES : nullptr;
     return k.off;
 }
 
@@ -834,9 +851,10 @@ nb_status nb_bind_scratch(nb_ctx *c, void *scratch, size_t bytes) {
     ctx_layout(c, (char *)scratch);
     zero_words<<<1, WG, 0, c->stream>>>(c->t_zero, 2, c->adj_flag, 4);
     LAUNCH_OK(c);
-    zero_words<<<1, WG, 0, c->stream>>>((int64_t *)c->tile_word, 3 * TL_TILES, nullptr, 0);
+    zero_words<<<1, WG, 0, c->stream>>>((int64_t *)c->tile_word, TILE_WORDS, nullptr, 0);
     LAUNCH_OK(c);
     c->epochs = Epochs{};
+    c->tile_present = 0;
     reset_control<<<1, WG, 0, c->stream>>>(c->ctl);
     LAUNCH_OK(c);
     c->scratch_ok = true;
@@ -1056,7 +1074,9 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
         if (h.flag_nonfinite) return fail(c, NB_ENONFINITE, "non-finite force or state on device");
         if (h.flag_wait) return fail(c, NB_EDEVICE, "the workgroups of a tiled run did not meet");
         if (h.done || (loop.retimed && h.flag_sched)) break;
-        if (path == RunLoop::TILES && h.tile_end == TL_MOVED) {
+        if (path == RunLoop::TILES && h.tile_end == TL_APART) {
+            loop.refused();
+        } else if (path == RunLoop::TILES && h.tile_end == TL_MOVED) {
             if (loop.moved()) {
                 tiles_time<<<1, WG, 0, c->stream>>>(state_rw(c), c->lmax, c->ctl);
                 LAUNCH_OK(c);
@@ -1402,6 +1422,14 @@ nb_status nb_set_resident(nb_ctx *c, int32_t max_n) {
     return NB_OK;
 }
 
+nb_status nb_set_tiles(nb_ctx *c, int32_t polls) {
+    if (!c) return NB_EINVAL;
+    if (polls < 0 || polls > TILE_POLLS_MAX)
+        return fail(c, NB_EINVAL, "nb_set_tiles: polls must lie in [0, %d]", TILE_POLLS_MAX);
+    c->tile_polls = polls;
+    return NB_OK;
+}
+
 nb_status nb_sync(nb_ctx *c) {
     if (!c) return NB_EINVAL;
     if (!c->scratch_ok) return fail(c, NB_ESTATE, "no workspace bound (call nb_bind_scratch)");
@@ -1601,6 +1629,7 @@ size_t ens_layout(nb_ens *e, char *base) {
     e->tables = k.take<int32_t>(EnsTables::words(e->C));
     e->assign = k.take<uint64_t>(ET_WGS);
     e->word = k.take<uint64_t>(3 * (size_t)e->tile_off_h[C]);
+    e->roll = k.take<uint64_t>(ROLL_WORDS);
     return k.off;
 }
 
@@ -1689,12 +1718,13 @@ bool ens_plan_teams(nb_ens *e, const std::vector<EnsCluster> &cl, int64_t t_end)
 }
 
 // nb_ens_run in one cooperative launch (per at most TL_STEPS block steps of a cluster).  done = false:
-// not taken (the caller goes on with global steps).
-nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64_t max_steps, bool &done) {
+// the run is not over, and the caller goes on with global steps, at most max_steps of them.
+nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64_t &max_steps, bool &done) {
     done = false;
     nb_status r = NB_OK;
     // global steps come in batches of spl
     int64_t left = max_steps > 0 ? (max_steps + spl - 1) / spl * spl : INT64_MAX;
+    uint64_t verdict = 0;
     std::vector<EnsCluster> h(e->C);
     auto records = [&]() -> nb_status {
         EHIP_OK(e, hipMemcpyAsync(h.data(), e->cl, e->C * sizeof(EnsCluster), hipMemcpyDeviceToHost, e->stream));
@@ -1721,7 +1751,13 @@ nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64
         if (again) {
             zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->word, 3 * e->tile_off_h[e->C], nullptr, 0);
             ELAUNCH_OK(e);
+            zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->roll, ROLL_WORDS, nullptr, 0);
+            ELAUNCH_OK(e);
+            e->present = 0;
         }
+        a.roll = e->roll;
+        a.present = e->present + (uint64_t)e->n_wgs;
+        a.polls = (uint32_t)e->polls;
         if (round) {
             zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->assign, ET_WGS, nullptr, 0);
             ELAUNCH_OK(e);
@@ -1736,9 +1772,12 @@ nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64
             e->teams_ok = false;
             return NB_OK;
         }
-        done = true;
+        e->present = a.present;
+        EHIP_OK(e, hipMemcpyAsync(&verdict, e->roll + ROLL_VERDICT, sizeof verdict, hipMemcpyDeviceToHost, e->stream));
         if ((r = records()) != NB_OK) return r;
+        if (!(verdict & 1)) return NB_OK;  // the workgroups did not start together
         left -= a.steps;
+        if (max_steps > 0) max_steps = left;
         bool all = true;
         int64_t total = 0;
         for (const auto &x : h) {
@@ -1750,6 +1789,7 @@ nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64
         if (total == prev) return fail(e, NB_ESTATE, "ensemble made no progress over %d block steps", a.steps);
         prev = total;
     }
+    done = true;
     return ens_flags(e);
 }
 
@@ -1909,7 +1949,11 @@ nb_status nb_ens_bind_scratch(nb_ens *e, void *scratch, size_t bytes) {
     zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->assign, ET_WGS, nullptr, 0);
     ELAUNCH_OK(e);
     EHIP_OK(e, hipStreamSynchronize(e->stream));
+    zero_words<<<1, WG, 0, e->stream>>>((int64_t *)e->roll, ROLL_WORDS, nullptr, 0);
+    ELAUNCH_OK(e);
+    EHIP_OK(e, hipStreamSynchronize(e->stream));
     e->epochs = e->turns = Epochs{};
+    e->present = 0;
     e->scratch_ok = true;
     e->initialised = false;
     return NB_OK;
@@ -1973,6 +2017,14 @@ nb_status nb_ens_set_split(nb_ens *e, int32_t smin) {
     e->smin = smin;
     ens_derive(e);
     ens_drop_graph(e);
+    return NB_OK;
+}
+
+nb_status nb_ens_set_teams(nb_ens *e, int32_t polls) {
+    if (!e) return NB_EINVAL;
+    if (polls < 0 || polls > TILE_POLLS_MAX)
+        return fail(e, NB_EINVAL, "nb_ens_set_teams: polls must lie in [0, %d]", TILE_POLLS_MAX);
+    e->polls = polls;
     return NB_OK;
 }
 
@@ -2055,7 +2107,7 @@ nb_status nb_ens_run(nb_ens *e, double eta, int64_t t_end, int32_t steps_per_lau
     EHIP_OK(e, hipSetDevice(e->device));
     if (use_graph) e->run_tend = t_end;
     // teams: graph runs (eager ones keep the launches apart) without local steps, at least 8 lanes a row
-    if (use_graph && e->teams_ok && e->local_limit == 0 && e->smin >= 8) {
+    if (use_graph && e->teams_ok && e->polls > 0 && e->local_limit == 0 && e->smin >= 8) {
         bool done = false;
         const nb_status r = ens_run_teams(e, eta, t_end, steps_per_launch, max_steps, done);
         if (r != NB_OK || done) return r;

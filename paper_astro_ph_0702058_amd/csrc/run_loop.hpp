@@ -55,7 +55,8 @@ struct RunLoop {
         return true;
     }
 
-    // The device refused a tiled launch: there is none any more.
+    // The device refused a tiled launch, or its workgroups did not start together: there is none
+    // any more in this run.
     void refused() { tiles = false; }
 
     // k steps of a path are enqueued.  False: no need to look at the record, since a tiled launch

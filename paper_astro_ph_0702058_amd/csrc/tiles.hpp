@@ -20,11 +20,11 @@
 // The workgroups meet twice a step, without fences: words, records and partial sums go through
 // relaxed agent-scope atomics, which the eight XCDs' L2 caches do not keep, each producer waits
 // for its stores to complete before it stores its word, and each consumer loads after it saw the
-// word.  (Measured on MI355X with 256 workgroups: 2.6 us per meeting; with agent-scope release
+// word.  They meet only once all are resident (roll_call): where other work keeps some of them off
+// the device, all leave before the first step and nb_run goes on by another path.  (Measured on MI355X with 256 workgroups: 2.6 us per meeting; with agent-scope release
 // and acquire fences, which write back and invalidate a whole L2, 19 us, and 62 us with 16 KB of
-// records read after it.)  The launch is cooperative, so all workgroups are resident, and every
-// wait gives up after TL_POLLS polls; the run then reports an error and leaves the state as it
-// was before the launch.
+// records read after it.)  Every wait gives up after TL_POLLS polls; the run then reports an error
+// and leaves the state as it was before the launch.
 //
 // The histogram gives the block time only while every particle's t_i is the last multiple of its
 // step not after the scheduler's time; then a block is never empty, somebody waits for all
@@ -63,6 +63,7 @@ constexpr uint32_t TL_POLLS = 1u << 24;  // about a quarter of a minute
 // How a launch ended (DevControl::tile_end).
 constexpr int32_t TL_RAN = 0;    // its steps, t_end, or a block of more rows than its limit
 constexpr int32_t TL_MOVED = 1;  // without a step: a particle's time does not fit the scheduler's
+constexpr int32_t TL_APART = 2;  // without a step: its workgroups did not start together
 
 struct TilesArgs {
     StateRW g;           // the state
@@ -73,6 +74,9 @@ struct TilesArgs {
     int32_t steps;       // most block steps
     uint64_t epoch;      // first epoch (above every epoch published before)
     uint64_t *word;      // [2][T] published words (epoch, level << 16 | count), by epoch parity
+    uint64_t *roll;      // workgroups that ever started; at ROLL_VERDICT the last launch's verdict
+    uint64_t present;    // workgroups that started once all of this launch did
+    uint32_t polls;      // looks before a workgroup gives up on the others' start
     uint64_t *arrive;    // [T * R] epoch whose partial sums a workgroup has stored
     double *rec[2];      // [T][TJ][TL_WORDS] published records, by epoch parity
     double *part;        // [2][T][limit][TL_SUMS] partial sums, by epoch parity
@@ -104,6 +108,27 @@ __device__ __forceinline__ bool wait_epoch(const uint64_t *p, uint64_t epoch, ui
         if ((v >> TL_SHIFT) >= epoch) return true;
     }
     return false;
+}
+
+// Whether all workgroups of a launch run at the same time.  Each counts itself in as it starts; the
+// one that completes the count says go, one that has looked `polls` times in vain says stop, and
+// the first word holds for all (an exchange on the verdict, tagged with the launch's epoch), also
+// for those that start when others have left.  By one work-item.
+constexpr int ROLL_VERDICT = 16, ROLL_WORDS = 32;
+__device__ __forceinline__ bool roll_count(uint64_t *roll, uint64_t present) {
+    return __hip_atomic_fetch_add(roll, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == present;
+}
+__device__ __forceinline__ bool roll_call(uint64_t *roll, uint64_t epoch, bool complete, uint32_t polls) {
+    uint64_t *verdict = roll + ROLL_VERDICT;
+    const uint64_t stop = epoch << 1, said = stop | (complete ? 1 : 0);
+    uint64_t v = agent_load(verdict);
+    if (!complete)
+        for (uint32_t k = 0; k < polls && v < stop; ++k) v = agent_load(verdict);
+    while (v < stop)  // nobody has spoken; on failure v is what somebody said
+        if (__hip_atomic_compare_exchange_strong(verdict, &v, said, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            v = said;
+    return v & 1;
 }
 
 // First multiple of the step of level l after t (the block time of particles on that level).
@@ -220,6 +245,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     DevControl *ctl = a.ctl;
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool complete = tid == 0 && roll_count(a.roll, a.present);
     if (ctl->done) {  // the same for every workgroup
         if (blockIdx.x == 0 && tid == 0) {
             ctl->tile_steps = 0;
@@ -268,9 +294,17 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     s.tick_len = a.g.tick_len;
     const auto eps2 = eps_as<M>(a.eps2);
     const int64_t t_end = ctl->t_end;
+    if (tid == 0 && !roll_call(a.roll, a.epoch, complete, a.polls)) late = 1;
     int32_t stepped = 0, n_last = 0, last_base = 0, last_cnt = 0, last_par = 0;
     bool done = false, bad = false, clamp = false, behind = false, lost = false, moved = false;
     __syncthreads();
+    if (late) {
+        if (blockIdx.x == 0 && tid == 0) {
+            ctl->tile_steps = 0;
+            ctl->tile_end = TL_APART;
+        }
+        return;
+    }
     while (stepped < a.steps) {
         const uint64_t epoch = a.epoch + (uint64_t)stepped;
         const int32_t par = (int32_t)(epoch & 1);

@@ -58,7 +58,8 @@ EXPORTS = ["nb_create", "nb_destroy", "nb_set_stream", "nb_bind", "nb_init",
            "nb_ens_last_error", "nb_shared_step", "nb_force_vjp", "nb_step_vjp",
            "nb_scratch_bytes", "nb_bind_scratch", "nb_ens_scratch_bytes", "nb_ens_bind_scratch",
            "nb_ens_set_local", "nb_fma_rate", "nb_force_noalloc",
-           "nb_set_resident", "nb_ens_set_split", "nb_ens_set_lanes"]
+           "nb_set_resident", "nb_ens_set_split", "nb_ens_set_lanes",
+           "nb_set_tiles", "nb_ens_set_teams"]
 
 _lib = None
 
@@ -117,6 +118,8 @@ def load_library(path: str = LIB_PATH):
         "nb_fma_rate": [P, ctypes.POINTER(D)],
         "nb_force_noalloc": [P, P, P, I32, P, P, P],
         "nb_set_resident": [P, I32],
+        "nb_set_tiles": [P, I32],
+        "nb_ens_set_teams": [P, I32],
     }
     for name, args in sig.items():
         f = getattr(lib, name)
@@ -378,8 +381,15 @@ class Context:
                                     int(bool(use_graph))))
 
     def nb_set_resident(self, max_n):
-        """nb_run on contexts of at most max_n particles uses one resident workgroup (0: never)."""
+        """nb_run on contexts of at most max_n particles keeps the state in LDS, in one resident
+        workgroup or in tiles (0: the chain of launches per step at every size)."""
         self._check(self.lib.nb_set_resident(self.h, int(max_n)))
+
+    def nb_set_tiles(self, polls):
+        """Looks (about 1 us each) until the workgroups of a tiled nb_run launch, which meet in
+        every step, run at the same time; else one resident workgroup or the chain of launches
+        takes the run.  0: no tiled launches."""
+        self._check(self.lib.nb_set_tiles(self.h, int(polls)))
 
     def nb_energy(self):
         ek, ep = ctypes.c_double(), ctypes.c_double()
@@ -557,6 +567,11 @@ class Ensemble:
     def nb_ens_set_split(self, smin):
         """Every block particle of a force item shared by at least smin lanes (power of 2)."""
         self._check(self.lib.nb_ens_set_split(self.h, int(smin)))
+
+    def nb_ens_set_teams(self, polls):
+        """Looks (about 1 us each) until all workgroups of a run by teams run at the same time; else
+        global steps take the run.  0: global steps only."""
+        self._check(self.lib.nb_ens_set_teams(self.h, int(polls)))
 
     def nb_ens_set_lanes(self, lane_of=None):
         """Independent lanes: lane_of[c] in [0, lanes) for every cluster (None: one lane)."""

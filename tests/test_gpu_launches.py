@@ -1,0 +1,93 @@
+"""Cooperative launches of nb_run and nb_ens_run: their workgroups start together or leave to another
+path, and their epochs last.  (The order of the launches is simulated in test_run_loop_cpu.py.)"""
+import numpy as np
+import pytest
+import torch
+
+from paper_astro_ph_0702058_amd import nbody
+from paper_astro_ph_0702058_amd.plummer import plummer
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(n, prec, calls, polls=None, resident=1024, lmin=3, seed=17, chunk=64, pending=False):
+    """(block steps, particle steps), state after nb_run calls of (t_end, max_steps)."""
+    st = nbody.DeviceState(*plummer(n, seed))
+    with nbody.Context(n, 1 / 256, lmin=lmin, precision=prec) as ctx:
+        ctx.nb_set_resident(resident)
+        if polls is not None:
+            ctx.nb_set_tiles(polls)
+        ctx.nb_bind(st)
+        ctx.nb_init(0.01)
+        if pending:  # a block corrected by the separate calls, its new levels to come
+            acc = torch.zeros((3, n), dtype=torch.float64, device="cuda")
+            jerk, pot = torch.zeros_like(acc), torch.zeros(n, dtype=torch.float64, device="cuda")
+            idx, cnt = ctx.nb_active()
+            ctx.nb_predict()
+            ctx.nb_force(acc, jerk, pot, i_idx=idx, n_i=cnt, n_i_max=n)
+            ctx.nb_correct(acc, jerk, pot)
+        for t_end, max_steps in calls:
+            ctx.nb_run(0.01, t_end, max_steps=max_steps, chunk=chunk)
+        c = ctx.nb_read_control()
+    return (c.n_steps, c.n_active_sum, c.t_cur), st.numpy()
+
+
+def _same(a, b):
+    assert a[0] == b[0] and a[0][0] > 10
+    for key in a[1]:
+        assert np.array_equal(a[1][key], b[1][key]), key
+
+
+def test_many_runs_of_the_largest_chunk():
+    """Runs of one launch each (the largest chunk) do not use up the launches' epochs: 600 short ones
+    end where a single run does, bitwise."""
+    t = 600 * 2.0 ** -15
+    cuts = [(t * (k + 1) / 600, 0) for k in range(600)]
+    _same(_run(1100, "fp32", cuts, lmin=6, chunk=2 ** 31 - 1), _run(1100, "fp32", [(t, 0)], lmin=6))
+
+
+@pytest.mark.parametrize("prec,n", [("fp32", 3000), ("fp64", 16384), ("ds", 2000), ("fp64", 700),
+                                    ("ds", 300), ("fp32", 1024)])
+def test_workgroups_that_do_not_start_together(prec, n):
+    """Workgroups that look for each other once only leave before the first step; the launch chain,
+    or the resident workgroup of a set that it holds, takes the run, bitwise as without tiles."""
+    calls = [(1 / 128, 0), (1 / 32, 21)]
+    _same(_run(n, prec, calls, polls=1), _run(n, prec, calls, polls=0))
+    if n > 1024:
+        _same(_run(n, prec, calls, polls=1), _run(n, prec, calls, resident=0))
+
+
+def _ensemble(sizes, prec, calls, polls=None):
+    parts = [plummer(int(k), 300 + c) for c, k in enumerate(sizes)]
+    st = nbody.DeviceState(*(np.concatenate([p[k] for p in parts]) for k in range(3)))
+    with nbody.Ensemble(sizes, [1.0 / max(k, 16) for k in sizes], lmin=3, precision=prec) as ens:
+        if polls is not None:
+            ens.nb_ens_set_teams(polls)
+        ens.nb_ens_bind(st)
+        ens.nb_ens_init(0.02)
+        for t_end, max_steps, graph in calls:
+            ens.nb_ens_run(0.02, t_end, steps_per_launch=8, max_steps=max_steps, use_graph=graph)
+        ctl = ens.nb_ens_control()
+    return [(c.n_steps, c.n_active_sum, c.t_cur, c.n_act) for c in ctl], st.numpy()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("max_steps", [0, 20])
+def test_teams_that_do_not_start_together(prec, max_steps):
+    """Global steps take the run, bitwise as without teams, with or without a step limit."""
+    sizes = [8192, 4097, 2000, 1024, 257, 64, 2, 1]
+    calls = [(1 / 32, max_steps, True)] + [(1 / 32, 0, True)] * (max_steps > 0)
+    a, b = (_ensemble(sizes, prec, calls, polls) for polls in (1, 0))
+    assert a[0] == b[0]
+    for key in a[1]:
+        assert np.array_equal(a[1][key], b[1][key]), key
+    if prec == "fp64":
+        assert a[0] == _ensemble(sizes, prec, calls)[0]
+
+
+def test_polls_are_checked():
+    with nbody.Context(64, 1 / 256) as ctx, nbody.Ensemble([64], 1 / 64) as ens:
+        for bad in (-1, (1 << 24) + 1):
+            for call in (ctx.nb_set_tiles, ens.nb_ens_set_teams):
+                with pytest.raises(nbody.NBodyError, match="polls"):
+                    call(bad)

@@ -66,26 +66,6 @@ def test_blocks_too_large_for_the_tiled_path(n, lmin):
     _same(a, _run(n, "fp32", 0, lmin, calls))
 
 
-def test_many_runs_of_the_largest_chunk():
-    """Runs of one launch each (the largest chunk) do not use up the launches' epochs: 600 short ones
-    end where a single run does, bitwise."""
-    n, t = 1100, 2.0 ** -15
-    x, v, m = plummer(n, 9)
-    out = []
-    for cuts in (600, 1):
-        st = nbody.DeviceState(x, v, m)
-        with nbody.Context(n, 1 / 256, lmin=6, precision="fp32") as ctx:
-            ctx.nb_bind(st)
-            ctx.nb_init(0.01)
-            for k in range(cuts):
-                ctx.nb_run(0.01, 600 * t * (k + 1) / cuts, chunk=2 ** 31 - 1)
-            out.append((ctx.nb_read_control().n_steps, st.numpy()))
-    (sa, a), (sb, b) = out
-    assert sa == sb > 10
-    for key in a:
-        assert np.array_equal(a[key], b[key]), key
-
-
 @pytest.mark.parametrize("n", [1300, 9000])
 def test_pending_levels_before_a_tiled_run(n):
     """A block corrected by the separate calls has its new levels before the first tiled step."""
