@@ -1293,16 +1293,13 @@ __global__ void __launch_bounds__(WG) reset_control(DevControl *ctl) {
     }
 }
 
-__global__ void __launch_bounds__(WG) set_t_end(DevControl *ctl, int64_t t_end) {
+// levelled: the block corrected last got its new levels from a launch of sched_newlevel before.
+__global__ void __launch_bounds__(WG) set_t_end(DevControl *ctl, int64_t t_end, bool levelled) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         ctl->t_end = t_end;
         ctl->done = 0;
+        if (levelled) ctl->n_pending = 0;
     }
-}
-
-// The block corrected last has its new levels (sched_newlevel's launch is over).
-__global__ void __launch_bounds__(WG) levels_done(DevControl *ctl) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->n_pending = 0;
 }
 
 struct StateRW {

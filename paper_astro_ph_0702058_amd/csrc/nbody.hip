@@ -1036,8 +1036,6 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
     if ((r = need(c)) != NB_OK) return r;
     if (chunk < 1) return fail(c, NB_EINVAL, "chunk must be >= 1");
     if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, NB_EINVAL, "eta must be > 0");
-    set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, t_end);
-    LAUNCH_OK(c);
     RunLoop loop{chunk, max_steps, use_tiles(c) && (use_graph || c->n <= RES_MAX),
                  use_resident(c) && !c->profile};
     if (loop.resident || loop.tiles) {  // new levels of a block corrected by a separate nb_correct
@@ -1045,6 +1043,8 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
                                                                     eta, c->lmin, c->lmax, c->ctl);
         LAUNCH_OK(c);
     }
+    set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, t_end, loop.resident || loop.tiles);
+    LAUNCH_OK(c);
     RunLoop::Path path;
     for (int32_t k; loop.next(path, k);) {
         switch (path) {
@@ -1089,11 +1089,9 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
         sched_newlevel<<<grid_for(c->n, 2048), WG, 0, c->stream>>>(state_rw(c), c->active, c->crit, eta,
                                                                     c->lmin, c->lmax, c->ctl);
         LAUNCH_OK(c);
-        levels_done<<<1, WG, 0, c->stream>>>(c->ctl);
-        LAUNCH_OK(c);
     }
     // leave the scheduler open-ended again
-    set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, INT64_MAX);
+    set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, INT64_MAX, loop.apart);
     LAUNCH_OK(c);
     return latched(c);
 }

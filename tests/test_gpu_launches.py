@@ -10,7 +10,7 @@ from paper_astro_ph_0702058_amd.plummer import plummer
 pytestmark = pytest.mark.gpu
 
 
-def _run(n, prec, calls, polls=None, resident=1024, lmin=3, seed=17, chunk=64, pending=False):
+def _run(n, prec, calls, polls=None, resident=1024, lmin=3, seed=17, chunk=64, pending=0):
     """(block steps, particle steps), state after nb_run calls of (t_end, max_steps)."""
     st = nbody.DeviceState(*plummer(n, seed))
     with nbody.Context(n, 1 / 256, lmin=lmin, precision=prec) as ctx:
@@ -18,14 +18,16 @@ def _run(n, prec, calls, polls=None, resident=1024, lmin=3, seed=17, chunk=64, p
         if polls is not None:
             ctx.nb_set_tiles(polls)
         ctx.nb_bind(st)
-        ctx.nb_init(0.01)
-        if pending:  # a block corrected by the separate calls, its new levels to come
+        ctx.nb_init(2.5e-5 if pending else 0.01)
+        if pending:  # steps by the separate calls, the last one's new levels to come
             acc = torch.zeros((3, n), dtype=torch.float64, device="cuda")
             jerk, pot = torch.zeros_like(acc), torch.zeros(n, dtype=torch.float64, device="cuda")
-            idx, cnt = ctx.nb_active()
-            ctx.nb_predict()
-            ctx.nb_force(acc, jerk, pot, i_idx=idx, n_i=cnt, n_i_max=n)
-            ctx.nb_correct(acc, jerk, pot)
+            for _ in range(pending):
+                ctx.nb_schedule_block(2.5e-5)
+                idx, cnt = ctx.nb_active()
+                ctx.nb_predict()
+                ctx.nb_force(acc, jerk, pot, i_idx=idx, n_i=cnt, n_i_max=n)
+                ctx.nb_correct(acc, jerk, pot)
         for t_end, max_steps in calls:
             ctx.nb_run(0.01, t_end, max_steps=max_steps, chunk=chunk)
         c = ctx.nb_read_control()
@@ -55,6 +57,17 @@ def test_workgroups_that_do_not_start_together(prec, n):
     _same(_run(n, prec, calls, polls=1), _run(n, prec, calls, polls=0))
     if n > 1024:
         _same(_run(n, prec, calls, polls=1), _run(n, prec, calls, resident=0))
+
+
+@pytest.mark.parametrize("n", [1300, 9000])
+@pytest.mark.parametrize("pending", [1, 4, 16])
+def test_pending_levels_before_the_chain_takes_over(n, pending):
+    """A block corrected by the separate calls gets its new levels once, also where the tiled launch
+    after that leaves to the chain: the run's eta allows steps 20 times those of the blocks before it,
+    and a particle at a multiple of four steps would be doubled twice."""
+    calls = [(1 / 64, 0)]
+    _same(_run(n, "fp64", calls, polls=1, pending=pending),
+          _run(n, "fp64", calls, resident=0, pending=pending))
 
 
 def _ensemble(sizes, prec, calls, polls=None):
