@@ -45,6 +45,7 @@ struct DevControl {
     uint64_t sel;
     int32_t tile_steps;     // block steps the last tiled launch took
     int32_t tile_end;       // why it ended (TL_RAN ...)
+    int32_t moved;          // a particle's time does not fit t_cur (run_start)
 };
 
 // ------------------------------------------------------------------------------------------
@@ -1289,7 +1290,7 @@ __global__ void __launch_bounds__(WG) reset_control(DevControl *ctl) {
         ctl->n_active_sum = 0; ctl->n_act = 0; ctl->flags = 0; ctl->t_cand = 0;
         ctl->n_pending = 0; ctl->done = 0; ctl->flag_nonfinite = 0; ctl->flag_dtmin = 0;
         ctl->flag_sched = 0; ctl->flag_wait = 0; ctl->sel = 0; ctl->tile_steps = 0;
-        ctl->tile_end = 0;
+        ctl->tile_end = 0; ctl->moved = 0;
     }
 }
 
@@ -1432,6 +1433,7 @@ __global__ void __launch_bounds__(WG) sched_newlevel(StateRW s, const int32_t *a
                                                      int32_t lmin, int32_t lmax,
                                                      DevControl *ctl) {
     const int32_t np = ctl->n_pending;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->moved = 0;
     for (int32_t q = blockIdx.x * WG + threadIdx.x; q < np; q += gridDim.x * WG) {
         const int32_t i = active[q];
         const double num = crit[2 * (int64_t)i], den = crit[2 * (int64_t)i + 1];

@@ -1043,7 +1043,11 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
                                                                     eta, c->lmin, c->lmax, c->ctl);
         LAUNCH_OK(c);
     }
-    set_t_end<<<1, WG, 0, c->stream>>>(c->ctl, t_end, loop.resident || loop.tiles);
+    const auto start = [&] {
+        run_start<<<loop.tiles ? grid_for(c->n, 256) : 1, WG, 0, c->stream>>>(
+            state_rw(c), c->lmax, t_end, loop.resident || loop.tiles, loop.tiles, c->ctl);
+    };
+    start();
     LAUNCH_OK(c);
     RunLoop::Path path;
     for (int32_t k; loop.next(path, k);) {
@@ -1079,6 +1083,8 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
         } else if (path == RunLoop::TILES && h.tile_end == TL_MOVED) {
             if (loop.moved()) {
                 tiles_time<<<1, WG, 0, c->stream>>>(state_rw(c), c->lmax, c->ctl);
+                LAUNCH_OK(c);
+                start();
                 LAUNCH_OK(c);
             }
         } else if (path == RunLoop::TILES) {

@@ -29,9 +29,10 @@
 // The histogram gives the block time only while every particle's t_i is the last multiple of its
 // step not after the scheduler's time; then a block is never empty, somebody waits for all
 // arrivals in every step, and no workgroup can be two epochs ahead of another (what the reuse of
-// words, records and sums every second epoch needs).  The correctors keep it so; a launch checks it
-// of the state it is given, which calls other than the block steps may have moved, and ends without
-// a step if it does not hold (tile_end TL_MOVED).
+// words, records and sums every second epoch needs).  The correctors keep it so; of the state that a
+// run is given, which calls other than the block steps may have moved, run_start checks it, and the
+// launch ends without a step if it does not hold (tile_end TL_MOVED).  (Checked by the owners, as a
+// level finer than all in the first words, it cost every step 0.3 us: registers.)
 //
 // What bounds a step (MI355X, N = 16384 FP32, mean block 230, cycles at 2.15 GHz): the rows' tile
 // sums 11000 (one wave's serial chain over 256 j), the two meetings 8000, record and partial-sum
@@ -203,6 +204,26 @@ __device__ __forceinline__ TilesArgs tiles_args() {
     return a;
 }
 
+// The start of a run to t_end.  levelled: as set_t_end.  check: whether every particle's time fits
+// the scheduler's, that is whether its next time is the first multiple of its step after it
+// (`moved` was cleared by the launch of sched_newlevel before).
+__global__ void __launch_bounds__(WG) run_start(StateRW s, int32_t lmax, int64_t t_end, bool levelled,
+                                                bool check, DevControl *ctl) {
+    if (check) {
+        const int64_t t = ctl->t_cur;
+        for (int32_t i = blockIdx.x * WG + threadIdx.x; i < s.n; i += gridDim.x * WG) {
+            const int32_t l = s.level[i];
+            if (l < 0 || l > lmax || s.tick[i] + ((int64_t)1 << (lmax - l)) != level_time(t, l, lmax))
+                ctl->moved = 1;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl->t_end = t_end;
+        ctl->done = 0;
+        if (levelled) ctl->n_pending = 0;
+    }
+}
+
 // The scheduler's time moved on to the state's (its latest particle time), for a launch that ended
 // with TL_MOVED.  A particle whose next time lies before the first multiple of the finest step
 // after the scheduler's time is behind it, as the launch chain reports.  One workgroup.
@@ -222,6 +243,7 @@ __global__ void __launch_bounds__(WG) tiles_time(StateRW s, int32_t lmax, DevCon
     if (threadIdx.x == 0) {
         if (next < level_time(ctl->t_cur, (int32_t)-fine, lmax)) ctl->flag_sched = 1;
         else ctl->t_cur = -late;
+        ctl->moved = 0;  // run_start looks again
     }
 }
 
@@ -246,16 +268,15 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool complete = tid == 0 && roll_count(a.roll, a.present);
-    if (ctl->done) {  // the same for every workgroup
+    if (ctl->done || ctl->moved) {  // the same for every workgroup
         if (blockIdx.x == 0 && tid == 0) {
             ctl->tile_steps = 0;
-            ctl->tile_end = TL_RAN;
+            ctl->tile_end = ctl->done ? TL_RAN : TL_MOVED;
         }
         return;
     }
     const int32_t T = a.T, R = a.R, G = T * R, lmax = a.lmax;
     const int32_t tile = (int32_t)blockIdx.x % T, rep = (int32_t)blockIdx.x / T;
-    int64_t t_cur = ctl->t_cur, act_sum = 0;
     int32_t p0, n_t;
     if (tid < NLEV) hist[tid] = 0;
     if (tid < TL_TILES) owner[tid] = 0;
@@ -274,18 +295,13 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
         }
         if (tid < TJ) {
             const bool in = tid < n_t;
-            const int32_t lg = in ? g.level[p0 + tid] : 0;
-            const bool held = lg >= 0 && lg <= lmax;
-            const int32_t l = held ? lg : 0;
+            const int32_t l = in ? g.level[p0 + tid] & (NLEV - 1) : 0;
             lm[tid] = in ? g.m[p0 + tid] : 0.0;
             lpot[tid] = in ? g.pot[p0 + tid] : 0.0;
             ltick[tid] = in ? g.tick[p0 + tid] : 0;
             lnext[tid] = in ? ltick[tid] + ((int64_t)1 << (lmax - l)) : INT64_MAX;  // never a member
             llevel[tid] = l;
-            // a particle out of step with the scheduler counts on a level that there is not, finer
-            // than all
-            const bool fits = held && lnext[tid] == level_time(t_cur, l, lmax);
-            if (in) atomicAdd(&hist[fits ? l : NLEV - 1], 1);
+            if (in) atomicAdd(&hist[l], 1);
         }
     }
     StateRW s;
@@ -293,10 +309,11 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     s.n = TJ;
     s.tick_len = a.g.tick_len;
     const auto eps2 = eps_as<M>(a.eps2);
+    int64_t t_cur = ctl->t_cur, act_sum = 0;
     const int64_t t_end = ctl->t_end;
     if (tid == 0 && !roll_call(a.roll, a.epoch, complete, a.polls)) late = 1;
     int32_t stepped = 0, n_last = 0, last_base = 0, last_cnt = 0, last_par = 0;
-    bool done = false, bad = false, clamp = false, behind = false, lost = false, moved = false;
+    bool done = false, bad = false, clamp = false, behind = false, lost = false;
     __syncthreads();
     if (late) {
         if (blockIdx.x == 0 && tid == 0) {
@@ -312,7 +329,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
         // select: the tile's own next block time and its members (the waves that hold them)
         if (wave < TJ / 64) {
             const int32_t lf = 63 - __builtin_clzll(__ballot(hist[lane] > 0) | 1ull);
-            const int64_t t_own = lf > lmax ? INT64_MIN : level_time(t_cur, lf, lmax);
+            const int64_t t_own = level_time(t_cur, lf, lmax);
             int32_t n_own = 0, below = 0;
             bool member = false;
             uint64_t mask = 0;
@@ -367,16 +384,15 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) fine = o4[k] >> 16 > fine ? o4[k] >> 16 : fine;
             fine = wave_max(fine);
-            const bool odd = fine > lmax;  // first step only: no time, and more rows than any limit
-            const int64_t tn = odd ? INT64_MIN : level_time(t_cur, fine, lmax);
+            const int64_t tn = level_time(t_cur, fine, lmax);
             int32_t c4[4], sum = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                c4[k] = !odd && level_time(t_cur, o4[k] >> 16, lmax) == tn ? o4[k] & 0xffff : 0;
+                c4[k] = level_time(t_cur, o4[k] >> 16, lmax) == tn ? o4[k] & 0xffff : 0;
                 sum += c4[k];
             }
             const int32_t inc = wave_scan_add(sum);
-            const int32_t rows = odd ? INT32_MAX : __builtin_amdgcn_readlane(inc, 63);
+            const int32_t rows = __builtin_amdgcn_readlane(inc, 63);
             const bool taken = tn <= t_end && rows <= a.limit;
             if (wave >= 12) {  // the row map, one owner of each lane per wave
                 if (tid == 12 * 64) {
@@ -407,10 +423,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
             break;
         }
         const int32_t n_act = __builtin_amdgcn_readfirstlane(plan_rows);
-        if (n_act > a.limit) {
-            moved = t_next == INT64_MIN;
-            break;
-        }
+        if (n_act > a.limit) break;
         // force: i-blocks of WG / L rows against the tile, TL_SUB at a time
         int32_t S, H;
         row_lanes(n_act, a.sp, S, H);
@@ -555,7 +568,7 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
     if (blockIdx.x == 0 && tid == 0) {
         ctl->n_pending = 0;  // levels are current
         ctl->tile_steps = stepped;
-        ctl->tile_end = moved ? TL_MOVED : TL_RAN;
+        ctl->tile_end = TL_RAN;
         if (stepped > 0) {
             ctl->t_cur = t_cur;
             ctl->t_next = t_cur;
