@@ -15,11 +15,9 @@
 #include <stdint.h>
 
 #include "ds_arith.hpp"
+#include "plan.hpp"
 
 namespace nbody {
-
-constexpr int WG = 256;      // work-items per workgroup
-constexpr int TJ = 256;      // j-particles per tile (LDS tile of the lane split; fold interval)
 
 // Device-side scheduler record.  The first 48 bytes mirror nb_control of the C ABI.
 struct DevControl {
@@ -47,100 +45,6 @@ struct DevControl {
     int32_t tile_end;       // why it ended (TL_RAN ...)
     int32_t moved;          // a particle's time does not fit t_cur (run_start)
 };
-
-// ------------------------------------------------------------------------------------------
-// Work decomposition of one force call, computed identically on host and device from the
-// number of i-particles: i-blocks of WG*IPL particles times K contiguous j-ranges (whole
-// tiles).  K > 1 only when the i-blocks alone cannot fill `target` work items.
-// ------------------------------------------------------------------------------------------
-struct ForcePlan {
-    int32_t n_i, n_iblk, ntiles, tps, K, items;
-    int32_t S;   // slices of a tile's j-slots an i-particle's lanes take (1: every lane all)
-    int32_t H;   // helper lanes per slice (quad_tile); S * H lanes share one i-particle
-    int32_t ib;  // i-particles per i-block
-    int64_t P;   // padded i rows of one partial plane
-};
-
-// Lanes per i-particle for a list of n_i with one i per work-item: a workgroup of wg lanes is
-// spread over the list, up to smax lanes (at most one wave) per i.
-__host__ __device__ inline int32_t lane_split(int32_t n_i, int32_t smax = 64, int32_t wg = WG) {
-    if (n_i >= wg) return 1;
-    // wg over the least power of two not below n_i
-    const int32_t S = n_i > 1 ? wg >> (32 - __builtin_clz((uint32_t)n_i - 1)) : wg;
-    return S > smax ? smax : S;
-}
-
-// How an arithmetic's lists may be spread over more lanes than lane_split gives, on launches too
-// small to fill the chip.  A lane's 256-j tile sum is a serial chain on a wave that issues one
-// instruction every four cycles however idle its SIMD is (measured: 185-200 cycles per j, 21 us
-// per tile, the same with one wave per SIMD as with four).  Predict + force of all rows, without
-// and with the spread: N = 1024 FP32 49 and 19 us, FP64 36 and 15 us; 300 rows at N = 10000 FP32
-// 33 and 19 us, double-single 164 and 32 us.
-struct Spread {
-    int32_t smax;     // most slices
-    int32_t hmax;     // 4: helper lanes keep the order of the sums (FP32); 1: none
-    int32_t fill;     // lanes per tile that fill the chip (0: lane_split alone)
-    int32_t wg = WG;  // lanes that lane_split spreads over a list
-    int32_t pack = 0; // lists longer than a workgroup take slices that leave less padding
-};
-
-// Slices of a list longer than a workgroup that takes S: more, up to 4, where the i-blocks of
-// fewer rows that they give leave at least 1/16 less padding (a padded row costs as much as a
-// true one; below 1/16 the tile staging shared by fewer rows takes the gain).  FP64 and
-// double-single only: FP32's tile sums fix the slices, and fixed point would leave its scalar
-// j-loads (881 rows at N = 65536 105 and 111 us).  Without and with it: 520 rows at N = 65536
-// FP64 106 and 92 us, double-single 335 and 246; 881 rows 127 and 118, 400 and 356; 257 rows at
-// N = 524288 390 and 292, 1340 and 937 (calls one after the other, launches included).
-__host__ __device__ inline int32_t pack_lanes(int32_t n_i, int32_t S) {
-    const auto padded = [n_i](int32_t ib) { return (n_i + ib - 1) & -ib; };  // ib a power of two
-    const int32_t r1 = padded(WG), r2 = padded(WG / 2), r4 = padded(WG / 4);
-    int32_t rows = S == 1 ? r1 : S == 2 ? r2 : r4;
-    const int32_t least = rows >> 4;
-    if (S < 2 && rows - r2 >= least) { rows = r2; S = 2; }
-    if (S < 4 && rows - r4 >= least) S = 4;
-    return S;
-}
-
-// Slices S and helper lanes H of each of n_i rows.
-__host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, int32_t &H) {
-    S = lane_split(n_i, sp.smax, sp.wg);
-    H = 1;
-    if (n_i <= sp.fill) {  // also keeps the products below in range
-        if (sp.hmax > 1) {
-            if (S * 4 <= 64 && n_i * S * 4 <= sp.fill) H = 4;
-        } else {
-            while (S < sp.smax && n_i * S * 2 <= sp.fill) S *= 2;
-        }
-    }
-    if (sp.pack && n_i > WG) S = pack_lanes(n_i, S);
-}
-
-// ib_max: WG * (i-particles per work-item).  Lists shorter than a workgroup take the lane
-// split whatever the variant (one i per group of lanes), so that a short block costs work in
-// proportion to its length.  Where the rows' lanes, on every tile, leave the chip unfilled (no
-// more than sp.fill per tile), rows take more lanes: more slices where the order of the sums is
-// free, helper lanes where the float tile sums fix it.
-__host__ __device__ inline ForcePlan make_plan(int32_t n_i, int32_t n, int32_t ib_max,
-                                               int32_t target, int32_t kmax,
-                                               Spread sp = Spread{64, 1, 0}) {
-    ForcePlan p;
-    p.n_i = n_i;
-    p.ntiles = (n + TJ - 1) / TJ;
-    row_lanes(n_i, sp, p.S, p.H);
-    const int32_t L = p.S * p.H;
-    const int32_t ib = L > 1 ? WG / L : ib_max;
-    p.ib = ib;
-    p.n_iblk = (n_i + ib - 1) / ib;
-    int32_t K = p.n_iblk > 0 ? target / p.n_iblk : 1;
-    if (K > kmax) K = kmax;
-    if (K > p.ntiles) K = p.ntiles;
-    if (K < 1) K = 1;
-    p.tps = (p.ntiles + K - 1) / K;
-    p.K = (p.ntiles + p.tps - 1) / p.tps;
-    p.items = p.n_iblk * p.K;
-    p.P = (int64_t)p.n_iblk * ib;
-    return p;
-}
 
 struct ForceCommon {
     int32_t n;               // number of j-particles

@@ -115,6 +115,7 @@ struct nb_ctx {
     int32_t resident_max = 1024;         // nb_run: one resident workgroup up to this n
     // nb_run above that: one cooperative launch of tile owners (tiles.hpp)
     bool tiles_ok = true;                // cleared when the device refuses the launch
+    BlockRows tiles_rows{0, 0, -1};      // of the present variant (most < 0: to be found)
     Epochs epochs;                       // of its launches
     uint64_t *tile_word = nullptr, *tile_arrive = nullptr, *tile_roll = nullptr;
     uint64_t tile_present = 0;           // workgroups of all launches so far
@@ -604,11 +605,36 @@ nb_status enqueue_resident(nb_ctx *c, double eta, int32_t steps, hipStream_t s) 
 // and 14.5; double-single N = 256 22.6 and 24.8, N = 300 26.3 and 16.3.
 int32_t tiles_least(int prec) { return prec == NB_DS ? 257 : prec == NB_FP64 ? 401 : 513; }
 
-bool use_tiles(const nb_ctx *c) {
+Spread tiles_spread(const nb_ctx *c) {
+    Spread sp = spread_of(c, Variant{1, 2, 0, 0, 0});
+    if (c->n <= RES_MAX) {  // the slices of the resident workgroup
+        sp.wg = WGL;
+        sp.pack = 0;
+    }
+    return sp;
+}
+
+// Rows of the blocks that tiles take; others go to the chain.  At most what the row map in LDS and
+// the partial planes, held twice, hold (past 64 tiles 7/8 of that: larger blocks are the chain's,
+// which uses every compute unit); and beyond the sets that a resident workgroup could hold, only
+// blocks that the chain sums in the same order, so that a run's result does not depend on where its
+// launches are cut: at the default targets the chain joins tiles past 4096 rows at 256 tiles, 5120 at
+// 196, and from 2049 to 3840 rows in FP64 and double-single at 130.  Found once per variant (0.4 ms).
+BlockRows tiles_rows(nb_ctx *c) {
+    if (c->tiles_rows.most >= 0) return c->tiles_rows;
+    const int64_t T = (c->n + TJ - 1) / TJ;
+    const int32_t most = (int32_t)std::min<int64_t>(c->partial_rows * (T > 64 ? 7 : 8) / (16 * T), TL_ROWS);
+    const Variant &v = c->var_block;
+    c->tiles_rows = c->n <= RES_MAX ? BlockRows{most, most, most}
+                  : rows_by_tiles(c->n, WG * v.ipl, v.target, v.kmax, spread_of(c, v), tiles_spread(c), most);
+    return c->tiles_rows;
+}
+
+bool use_tiles(nb_ctx *c) {
     return c->tiles_ok && c->tile_polls > 0 && c->resident_max > 0 && !c->profile && c->eps > 0.0 &&
            c->n >= (c->n <= c->resident_max ? tiles_least(c->prec) : RES_MAX + 1) &&
            (c->n + TJ - 1) / TJ <= std::min<int32_t>(TL_TILES, c->num_cu) &&
-           (c->prec == NB_FP32 || c->prec == NB_DS || c->prec == NB_FP64);
+           (c->prec == NB_FP32 || c->prec == NB_DS || c->prec == NB_FP64) && tiles_rows(c).most > 0;
 }
 
 // Up to `steps` block steps in one cooperative launch.  false in `launched`: the device refused
@@ -617,11 +643,8 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     TilesArgs a;
     a.T = (c->n + TJ - 1) / TJ;
     a.R = std::max(1, std::min(c->num_cu / a.T, TL_REPS));
-    // blocks of more rows (in LDS: the row map; in the partial planes, held twice) go to the chain
-    // (past 64 tiles the chain's items join tiles for blocks that large: 7/8 of the room keeps the
-    // sums of both in one order)
-    const int64_t room = c->partial_rows * (a.T > 64 ? 7 : 8) / (16 * (int64_t)a.T);
-    a.limit = (int32_t)std::min<int64_t>(room, TL_ROWS);
+    a.rows = tiles_rows(c);
+    a.limit = a.rows.most;
     a.steps = steps;
     bool again;
     a.epoch = c->epochs.take((uint64_t)steps + 2, again);
@@ -640,11 +663,7 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     a.part = c->partial;
     a.active = c->active; a.js = c->js; a.ctl = c->ctl;
     a.eps2 = c->eps * c->eps; a.eta = eta; a.lmin = c->lmin; a.lmax = c->lmax;
-    a.sp = spread_of(c, Variant{1, 2, 0, 0, 0});
-    if (c->n <= RES_MAX) {  // the slices of the resident workgroup
-        a.sp.wg = WGL;
-        a.sp.pack = 0;
-    }
+    a.sp = tiles_spread(c);
     a.g = state_rw(c);
     void *args[] = {&a};
     const void *f = c->prec == NB_FP32 ? (const void *)run_tiles<ModeF32, 4>
@@ -1276,6 +1295,7 @@ nb_status nb_set_variant(nb_ctx *c, int32_t which, const nb_variant *vin) {
                     "variant ipl=%d unroll=%d target=%d kmax=%d scalar_tiles=%d not available",
                     v->ipl, v->unroll, v->target, v->kmax, v->scalar_tiles);
     cur = *v;
+    c->tiles_rows.most = -1;
     drop_graph(c);
     return NB_OK;
 }
@@ -1353,6 +1373,7 @@ nb_status nb_tune(nb_ctx *c, int32_t which, int32_t n_i, int32_t reps, nb_varian
     (void)hipEventDestroy(e1);
     c->profile = was_profiling;
     (which == 0 ? c->var_full : c->var_block) = bestv;
+    c->tiles_rows.most = -1;
     drop_graph(c);
     if (best) *best = bestv;
     if (best_ms) *best_ms = bms;

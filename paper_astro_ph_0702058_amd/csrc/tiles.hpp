@@ -71,7 +71,8 @@ struct TilesArgs {
     JStreamView js;      // the j-particle stream, written at the end
     int32_t *active;
     int32_t T, R;        // tiles, workgroups per tile (grid T * R: tile = block % T)
-    int32_t limit;       // most block rows (a larger block ends the launch)
+    int32_t limit;       // most block rows
+    BlockRows rows;      // the lengths taken (a block of another ends the launch)
     int32_t steps;       // most block steps
     uint64_t epoch;      // first epoch (above every epoch published before)
     uint64_t *word;      // [2][T] published words (epoch, level << 16 | count), by epoch parity
@@ -392,7 +393,8 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
                 sum += c4[k];
             }
             const int32_t inc = wave_scan_add(sum);
-            const int32_t rows = __builtin_amdgcn_readlane(inc, 63);
+            int32_t rows = __builtin_amdgcn_readlane(inc, 63);
+            if (!a.rows.has(rows)) rows = INT32_MAX;
             const bool taken = tn <= t_end && rows <= a.limit;
             if (wave >= 12) {  // the row map, one owner of each lane per wave
                 if (tid == 12 * 64) {

@@ -10,13 +10,16 @@ from paper_astro_ph_0702058_amd.plummer import plummer
 pytestmark = pytest.mark.gpu
 
 
-def _run(n, prec, calls, polls=None, resident=1024, lmin=3, seed=17, chunk=64, pending=0):
+def _run(n, prec, calls, polls=None, resident=1024, lmin=3, seed=17, chunk=64, pending=0,
+         variant=None):
     """(block steps, particle steps), state after nb_run calls of (t_end, max_steps)."""
     st = nbody.DeviceState(*plummer(n, seed))
     with nbody.Context(n, 1 / 256, lmin=lmin, precision=prec) as ctx:
         ctx.nb_set_resident(resident)
         if polls is not None:
             ctx.nb_set_tiles(polls)
+        if variant is not None:
+            ctx.nb_set_variant(1, variant)
         ctx.nb_bind(st)
         ctx.nb_init(2.5e-5 if pending else 0.01)
         if pending:  # steps by the separate calls, the last one's new levels to come
@@ -68,6 +71,35 @@ def test_pending_levels_before_the_chain_takes_over(n, pending):
     calls = [(1 / 64, 0)]
     _same(_run(n, "fp64", calls, polls=1, pending=pending),
           _run(n, "fp64", calls, resident=0, pending=pending))
+
+
+@pytest.mark.parametrize("prec,n,lo,hi", [("fp64", 33023, 2049, 7168), ("fp32", 58000, 4609, 7168)])
+def test_large_blocks_are_summed_in_one_order(prec, n, lo, hi):
+    """Blocks of lo to hi rows, whose tiles the chain joins: whichever launch takes them, and wherever
+    the launches are cut, the run's bits are the chain's."""
+    st = nbody.DeviceState(*plummer(n, 17))
+    with nbody.Context(n, 1 / 256, lmin=3, precision=prec) as ctx:
+        ctx.nb_bind(st)
+        ctx.nb_init(0.01)
+        blocks = []
+        for _ in range(24):
+            ctx.nb_step(0.01, 1)
+            blocks.append(ctx.nb_read_control().n_act)
+    assert any(lo <= b <= hi for b in blocks), blocks
+    calls = [(1.0, 24)]
+    ref = _run(n, prec, calls, resident=0)
+    for chunk in (64, 5, 1):
+        _same(_run(n, prec, calls, chunk=chunk), ref)
+
+
+@pytest.mark.parametrize("variant", [dict(ipl=2, unroll=2, target=2048, kmax=1 << 16),
+                                     dict(ipl=1, unroll=1, target=1024, kmax=1 << 16),
+                                     dict(ipl=1, unroll=2, target=4096, kmax=8)])
+def test_block_variant_keeps_its_order(variant):
+    """A caller's block-step variant decides the order of the sums on every path."""
+    calls = [(1 / 128, 0)]
+    a, b = (_run(5000, "fp32", calls, resident=r, variant=variant) for r in (1024, 0))
+    _same(a, b)
 
 
 def _ensemble(sizes, prec, calls, polls=None):
