@@ -221,11 +221,15 @@ nb_status nb_run(nb_ctx *ctx, double eta, int64_t t_end, int64_t max_steps, int3
  * keeps every context on the chain. */
 nb_status nb_set_resident(nb_ctx *ctx, int32_t max_n);
 
-/* How nb_run's cooperative launches wait for the device.  Their workgroups meet in every step, so
- * they start only together: where other work keeps some of them off the device, each looks for the
- * others up to `polls` times (about 1 us a look; default 2^20, at most 2^24) and then all leave
- * without a step, and the run goes on as if there were no such launches: by one resident workgroup
- * (n <= max_n of nb_set_resident) or the launch chain.  polls = 0: no such launches at all.
+/* How nb_run's launches of several workgroups wait for the device.  Their workgroups meet in every
+ * step, so they start only together: where other work keeps some of them off the device, each looks
+ * for the others up to `polls` times (about 1 us a look; default 2^20, at most 2^24) and then all
+ * leave without a step, and the run goes on as if there were no such launches: by one resident
+ * workgroup (n <= max_n of nb_set_resident) or the launch chain.  polls = 0: no such launches at all.
+ * Runs of several contexts on streams of their own: those of at most 1024 particles go on side by
+ * side (8 of N = 1024 FP32 to t = 1/8 in 21 ms on MI355X, one in 7; in one resident workgroup each
+ * 42 and 14); larger ones are cooperative launches of up to `chunk` steps, which follow each other
+ * (4 of N = 16384 FP32 to t = 1/64 in 23 ms, one in 5.7; by the launch chain, polls = 0, 23 and 9.4).
  * NB_EINVAL for polls outside [0, 2^24]. */
 nb_status nb_set_tiles(nb_ctx *ctx, int32_t polls);
 

@@ -637,9 +637,10 @@ bool use_tiles(nb_ctx *c) {
            (c->prec == NB_FP32 || c->prec == NB_DS || c->prec == NB_FP64) && tiles_rows(c).most > 0;
 }
 
-// Up to `steps` block steps in one cooperative launch.  false in `launched`: the device refused
-// it (the caller goes on with the launch chain).
-nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, bool &launched) {
+// Up to `steps` block steps in one launch, cooperative or plain.  false in `launched`: the device
+// refused it (the caller goes on with the launch chain).  A plain launch waits for its workgroups
+// for 4 ms at most: others like it may hold the compute units that it lacks, and lack those it holds.
+nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, bool plain, bool &launched) {
     TilesArgs a;
     a.T = (c->n + TJ - 1) / TJ;
     a.R = std::max(1, std::min(c->num_cu / a.T, TL_REPS));
@@ -655,7 +656,7 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     }
     a.roll = c->tile_roll;
     a.present = c->tile_present + (uint64_t)(a.T * a.R);
-    a.polls = (uint32_t)c->tile_polls;
+    a.polls = (uint32_t)(plain ? std::min(c->tile_polls, 1 << 12) : c->tile_polls);
     a.word = c->tile_word; a.arrive = c->tile_arrive;
     // records in the energy's and the adjoint's scratch (8 and 12 doubles per particle), which
     // hold nothing between calls
@@ -669,7 +670,9 @@ nb_status enqueue_tiles(nb_ctx *c, double eta, int32_t steps, hipStream_t s, boo
     const void *f = c->prec == NB_FP32 ? (const void *)run_tiles<ModeF32, 4>
                   : c->prec == NB_DS ? (const void *)run_tiles<ModeDS, 1>
                                      : (const void *)run_tiles<ModeF64, 2>;
-    launched = hipLaunchCooperativeKernel(f, dim3(a.T * a.R), dim3(TL_WG), args, 0, s) == hipSuccess;
+    const dim3 grid(a.T * a.R), wg(TL_WG);
+    launched = (plain ? hipLaunchKernel(f, grid, wg, args, 0, s)
+                      : hipLaunchCooperativeKernel(f, grid, wg, args, 0, s)) == hipSuccess;
     if (launched) {
         c->tile_present = a.present;
     } else {
@@ -1056,7 +1059,7 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
     if (chunk < 1) return fail(c, NB_EINVAL, "chunk must be >= 1");
     if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, NB_EINVAL, "eta must be > 0");
     RunLoop loop{chunk, max_steps, use_tiles(c) && (use_graph || c->n <= RES_MAX),
-                 use_resident(c) && !c->profile};
+                 use_resident(c) && !c->profile, c->n <= RES_MAX};
     if (loop.resident || loop.tiles) {  // new levels of a block corrected by a separate nb_correct
         sched_newlevel<<<grid_for(c->n, 2048), WG, 0, c->stream>>>(state_rw(c), c->active, c->crit,
                                                                     eta, c->lmin, c->lmax, c->ctl);
@@ -1073,7 +1076,7 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
         switch (path) {
             case RunLoop::TILES: {
                 bool launched = false;
-                if ((r = enqueue_tiles(c, eta, k, c->stream, launched)) != NB_OK) return r;
+                if ((r = enqueue_tiles(c, eta, k, c->stream, loop.plain, launched)) != NB_OK) return r;
                 if (!launched) {
                     loop.refused();
                     continue;
@@ -1098,7 +1101,7 @@ nb_status nb_run(nb_ctx *c, double eta, int64_t t_end, int64_t max_steps, int32_
         if (h.flag_wait) return fail(c, NB_EDEVICE, "the workgroups of a tiled run did not meet");
         if (h.done || (loop.retimed && h.flag_sched)) break;
         if (path == RunLoop::TILES && h.tile_end == TL_APART) {
-            loop.refused();
+            loop.missed();
         } else if (path == RunLoop::TILES && h.tile_end == TL_MOVED) {
             if (loop.moved()) {
                 tiles_time<<<1, WG, 0, c->stream>>>(state_rw(c), c->lmax, c->ctl);

@@ -29,7 +29,7 @@ struct Epochs {
 
 struct RunLoop {
     enum Path {
-        TILES,     // a cooperative launch of tile owners
+        TILES,     // a launch of tile owners, cooperative or (`plain`) not
         RESIDENT,  // one resident workgroup
         CHAIN,     // launches per block step
         APART,     // the separate launches of a step, for particle times that fit no scheduler's
@@ -38,6 +38,11 @@ struct RunLoop {
     int64_t max_steps;    // <= 0: no limit
     bool tiles;           // tiled launches are taken
     bool resident;        // what tiles do not take goes to the resident workgroup, else the chain
+    // Cooperative launches follow each other whatever their streams, so a small set, which needs a
+    // few compute units, starts plainly: launches of several contexts run side by side.  Where they
+    // keep each other's workgroups from starting together they leave, and this run's next launches
+    // are cooperative.
+    bool plain = false;
     int64_t done_steps = 0;
     // a block too large for the tiled path ends its launch and takes the launch chain: for one
     // step, or for ever longer stretches while such blocks come within a few steps of each other
@@ -55,9 +60,14 @@ struct RunLoop {
         return true;
     }
 
-    // The device refused a tiled launch, or its workgroups did not start together: there is none
-    // any more in this run.
+    // The device refused a tiled launch: there is none any more in this run.
     void refused() { tiles = false; }
+
+    // The workgroups of a tiled launch did not start together.
+    void missed() {
+        tiles = plain;
+        plain = false;
+    }
 
     // k steps of a path are enqueued.  False: no need to look at the record, since a tiled launch
     // follows and sees for itself that the run is over.

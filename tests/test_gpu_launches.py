@@ -136,3 +136,34 @@ def test_polls_are_checked():
             for call in (ctx.nb_set_tiles, ens.nb_ens_set_teams):
                 with pytest.raises(nbody.NBodyError, match="polls"):
                     call(bad)
+
+
+def test_small_runs_from_many_threads():
+    """Twelve contexts of small sets on streams of their own, more workgroups than the device holds:
+    their launches run side by side or make room for each other, and each run ends as it does alone."""
+    import threading
+    n, count = 1024, 12
+
+    def run(seed, stream):
+        with torch.cuda.stream(stream):
+            st = nbody.DeviceState(*plummer(n, seed))
+            with nbody.Context(n, 1 / 256, lmin=6, precision="fp32", stream=stream) as ctx:
+                ctx.nb_bind(st)
+                for _ in range(3):
+                    ctx.nb_init(0.01)
+                    ctx.nb_run(0.01, 1 / 64, chunk=16)
+                ctx.nb_sync()
+                return st.numpy()
+
+    alone = [run(k, torch.cuda.current_stream()) for k in range(count)]
+    streams, got = [torch.cuda.Stream() for _ in range(count)], [None] * count
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=lambda k=k: got.__setitem__(k, run(k, streams[k]))) for k in range(count)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    for a, g in zip(alone, got):
+        assert g is not None
+        for key in a:
+            assert np.array_equal(a[key], g[key]), key

@@ -7,25 +7,25 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-# A device with `total` block steps to t_end, whose block `i` is too large for tiles where
-# i % 7 < large, and which refuses tiled launches from the refuse-th on.  Prints steps taken,
-# steps the loop counted, whether it stopped for `done`, and the looks at the record.
+# A device with 500 block steps to t_end, whose block `i` is too large for tiles where i % 7 < large,
+# which refuses tiled launches from the refuse-th on and whose every miss-th does not start together
+# (0: none): a run to the end and one of 37 steps for every refuse and miss.
 SIMULATION = r"""
 #include "run_loop.hpp"
 #include <cstdio>
 #include <cstdlib>
 using namespace nbody;
-int main(int argc, char **argv) {
-    const long total = atol(argv[1]), refuse = atol(argv[2]), large = atol(argv[3]);
-    RunLoop l{(int32_t)atol(argv[4]), atol(argv[5]), argv[6][0] == '1', argv[7][0] == '1'};
-    long at = 0, launches = 0, looks = 0, turns = 0;
+static bool run(long large, RunLoop l, long refuse, long miss) {
+    const long total = 500;
+    long at = 0, launches = 0, turns = 0;
     bool done = false;
     RunLoop::Path p;
     for (int32_t k; l.next(p, k);) {
-        if (++turns > 20 * total + 1000) { printf("endless\n"); return 1; }
+        if (++turns > 20 * total + 1000) return printf("endless\n"), false;
         int32_t steps = 0;
         if (p == RunLoop::TILES) {
             if (launches++ >= refuse) { l.refused(); continue; }
+            if (miss && launches % miss == 0) { l.missed(); continue; }
             while (!done && steps < k && !(at < total && at % 7 < large)) {
                 if (at == total) done = true;
                 else ++at, ++steps;
@@ -37,14 +37,25 @@ int main(int argc, char **argv) {
             }
         }
         if (!l.enqueued(p, k)) continue;
-        ++looks;
         if (done) break;
         if (p == RunLoop::TILES) l.tiled(k, steps);
     }
-    printf("%ld %lld %d %ld\n", at, (long long)l.done_steps, (int)done, looks);
+    const bool right = l.max_steps > 0 ? at == l.max_steps && l.done_steps == at && !done
+                                       : at == total && done;
+    if (!right) printf("refuse %ld miss %ld: %ld steps, %ld counted\n", refuse, miss, at, (long)l.done_steps);
+    return right;
+}
+int main(int, char **argv) {
+    const long large = atol(argv[1]);
+    const bool resident = argv[3][0] == '1';
+    bool ok = true;
+    for (long refuse : {0l, 1l, 3l, 1000000000l})
+        for (long miss = 0; miss < 4; ++miss)
+            for (long max_steps : {0l, 37l})
+                ok = run(large, RunLoop{(int32_t)atol(argv[2]), max_steps, true, resident, resident}, refuse, miss) && ok;
+    return !ok;
 }
 """
-
 
 EPOCHS = r"""
 #include "run_loop.hpp"
@@ -78,27 +89,17 @@ def _build(tmp_path_factory, name, text):
 
 
 @pytest.fixture(scope="module")
-def simulate(tmp_path_factory):
-    exe = _build(tmp_path_factory, "run_loop", SIMULATION)
-
-    def run(*args):
-        r = subprocess.run([exe, *(str(int(a)) for a in args)], capture_output=True, text=True, timeout=60)
-        assert r.returncode == 0, (args, r.stdout)
-        return [int(w) for w in r.stdout.split()]
-
-    return run
+def simulation(tmp_path_factory):
+    return _build(tmp_path_factory, "run_loop", SIMULATION)
 
 
 @pytest.mark.parametrize("chunk", [1, 2, 64, 2 ** 31 - 1])
 @pytest.mark.parametrize("large", [0, 1, 7])
 @pytest.mark.parametrize("resident", [0, 1])
-def test_every_run_ends(simulate, chunk, large, resident):
-    total = 500
-    for refuse in (0, 1, 3, 10 ** 9):
-        at, counted, done, looks = simulate(total, refuse, large, chunk, 0, 1, resident)
-        assert at == total and done, (refuse, at, done)
-        at, counted, done, looks = simulate(total, refuse, large, chunk, 37, 1, resident)
-        assert at == counted == 37 and not done, (refuse, at, counted, done)
+def test_every_run_ends(simulation, chunk, large, resident):
+    r = subprocess.run([simulation, str(large), str(chunk), str(resident)], capture_output=True, text=True,
+                       timeout=60)
+    assert r.returncode == 0, r.stdout
 
 
 def test_epochs_fit_their_words(tmp_path_factory):
