@@ -31,7 +31,7 @@ static bool run(long large, RunLoop l, long refuse, long miss) {
                 else ++at, ++steps;
             }
         } else {
-            for (int32_t i = 0; i < k; ++i) {
+            for (int32_t i = 0; i < k && !done; ++i) {
                 if (at == total) done = true;
                 else ++at;
             }
