@@ -59,7 +59,12 @@ struct ForceCommon {
     DevControl *ctl;         // latched flags (may be NULL)
     Spread sp;               // how the arithmetic mode's lists spread over lanes
     int32_t scalar_min;      // fewest j-tiles per item read with scalar loads (float modes)
+    ForcePlan pl{};          // of a host count (a device count's is formed in the kernels: 1 us)
 };
+
+__device__ __forceinline__ ForcePlan plan_of(const ForceCommon &fc, int32_t n_i, int32_t ib) {
+    return fc.n_i_dev ? make_plan(n_i, fc.n, ib, fc.target, fc.kmax, fc.sp) : fc.pl;
+}
 
 // Sum record written per i-particle: acc (3), jerk (3), accumulated m/r (1).
 struct Out7 {
@@ -799,11 +804,11 @@ template <class M, int UNR, bool SOFT, bool HELP>
 __device__ void force_items_split(const typename M::Args &pa, const ForceCommon &fc,
                                   const ForcePlan &pl, typename M::Smem &sm, int32_t n_i,
                                   typename EpsOf<M>::T eps2) {
-    const int32_t Sl = pl.S, H = pl.H, L = Sl * H;
-    const int32_t slice = (int32_t)threadIdx.x % L / H;
+    const int32_t Sl = pl.S, H = pl.H, L = Sl * H, ls = log2i(L);  // powers of two
+    const int32_t slice = ((int32_t)threadIdx.x & (L - 1)) >> log2i(H);
     for (int32_t w = blockIdx.x; w < pl.items; w += gridDim.x) {
         const int32_t iblk = w / pl.K, ks = w - (w / pl.K) * pl.K;
-        const int32_t q = iblk * pl.ib + (int32_t)threadIdx.x / L;
+        const int32_t q = iblk * pl.ib + ((int32_t)threadIdx.x >> ls);
         const int32_t g = q < n_i ? (fc.ilist ? fc.ilist[q] : q) : 0;
         const int32_t own = q < n_i ? g : -1;  // the i-particle's own j-slot (none on padding)
         const typename M::I ii = M::load_i(pa, g);
@@ -818,7 +823,7 @@ __device__ void force_items_split(const typename M::Args &pa, const ForceCommon 
             tile_sums<M, UNR, SOFT, HELP>(ii, sm, slice, Sl, H, rel, eps2, S);
         }
         lanes_add<M>(S, L, H);
-        if ((int32_t)threadIdx.x % L == 0 && q < n_i) store_result<M>(fc, pl, ks, q, S);
+        if (((int32_t)threadIdx.x & (L - 1)) == 0 && q < n_i) store_result<M>(fc, pl, ks, q, S);
     }
 }
 
@@ -949,7 +954,7 @@ __device__ __forceinline__ void force_items(const typename M::Args &pa, const Fo
         n_i = d < n_i ? d : n_i;
     }
     if (n_i <= 0) return;
-    const ForcePlan pl = make_plan(n_i, fc.n, WG * IPL, fc.target, fc.kmax, fc.sp);
+    const ForcePlan pl = plan_of(fc, n_i, WG * IPL);
     const auto eps2 = pa.eps2;
     if (pl.S * pl.H > 1) {
         force_items_split<M, UNR, SOFT, HELP>(pa, fc, pl, sm, n_i, eps2);
@@ -1006,7 +1011,7 @@ __global__ void __launch_bounds__(WG) force_kernel(typename M::Args pa, ForceCom
 // instead of 71) cost the whole-block path two of its seven waves per SIMD (1.4 % of a gradient
 // at N = 16384), so only launches whose plans may take helpers use it.
 template <class M, bool SOFT>
-__global__ void __launch_bounds__(WG) force_kernel_helped(typename M::Args pa, ForceCommon fc) {
+__global__ void __launch_bounds__(WG, 7) force_kernel_helped(typename M::Args pa, ForceCommon fc) {
     __shared__ typename M::Smem sm;
     force_items<M, 1, 2, SOFT, true>(pa, fc, sm);
 }
@@ -1048,7 +1053,7 @@ __global__ void __launch_bounds__(WG_REDUCE) force_reduce(ForceCommon fc, int32_
         n_i = d < n_i ? d : n_i;
     }
     if (n_i <= 0) return;
-    const ForcePlan pl = make_plan(n_i, fc.n, ib, fc.target, fc.kmax, fc.sp);
+    const ForcePlan pl = plan_of(fc, n_i, ib);
     if (pl.K == 1) return;
     const int32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int32_t units = ((n_i + 63) >> 6) * 7;

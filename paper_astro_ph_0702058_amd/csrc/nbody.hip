@@ -383,11 +383,24 @@ int32_t smax_of(int prec) { return prec == NB_FP32_FIXED ? TJ / ModeTraits<ModeF
 // default shape of the kernel), the paper's all-single sums have no helpers, and the other
 // arithmetics take more slices.
 Spread spread_of(const nb_ctx *c, const Variant &v) {
-    const int32_t fill = c->num_cu * 1024 / ((c->n + TJ - 1) / TJ);
-    if (c->prec == NB_FP32) return Spread{64, v.ipl == 1 && v.unroll == 2 ? 4 : 1, v.ipl == 1 && v.unroll == 2 ? fill : 0};
+    const int32_t T = (c->n + TJ - 1) / TJ, fill = c->num_cu * 1024 / T;
+    if (c->prec == NB_FP32) {
+        if (v.ipl != 1 || v.unroll != 2) return Spread{64, 1, 0};
+        Spread sp{64, 4, fill};
+        sp.hfill = fill / 2;
+        return sp;
+    }
     if (c->prec == NB_FP32_ALL) return Spread{64, 1, 0};
-    const bool pack = v.ipl == 1 && (c->prec == NB_FP64 || c->prec == NB_DS);
-    return Spread{smax_of(c->prec), 1, fill, WG, pack};
+    const bool fixed = c->prec == NB_FP32_FIXED;
+    Spread sp{smax_of(c->prec), 1, fill, WG, v.ipl == 1 && !fixed};
+    sp.most = sp.smax;
+    // sets that tiles may hold keep the most slices, a block's in tiled runs too
+    if (fixed || T > TL_TILES) {
+        sp.most = std::min(sp.smax, c->prec == NB_FP64 ? 8 : 32);
+        sp.tq = (int32_t)(((int64_t)T * 4096 + c->num_cu - 1) / c->num_cu);
+        sp.scalar = fixed;
+    }
+    return sp;
 }
 
 // Largest K * P over every i-count up to n_i_max against n j-particles, for one variant (the
@@ -419,18 +432,17 @@ nb_status enqueue_force(nb_ctx *c, const Variant &v, int cls, const int32_t *ili
     const Spread sp = spread_of(c, v);
     ForceCommon fc{c->n, ilist, n_i_dev, n_i_max, v.target, v.kmax, acc, jerk, pot, ld,
                    partial ? partial : c->partial, c->ctl, sp, v.scalar_tiles};
+    fc.pl = make_plan(n_i_max, c->n, ib, v.target, v.kmax, sp);
     int32_t grid;
     bool helped;  // the plan takes helper lanes, or for a device count may take them
     if (n_i_dev) {
-        // the count is known only on the device: enough workgroups for any count up to n_i_max
-        // (fewer than 64 rows that may have helpers are not worth their kernel)
-        helped = sp.hmax > 1 && sp.fill >= 256;
-        const ForcePlan full = make_plan(n_i_max, c->n, ib, v.target, v.kmax, sp);
-        grid = std::max(std::max(1, v.target), std::min(full.items, 65535));
+        // the count is known only on the device: enough workgroups for any count up to n_i_max;
+        // 129 rows in one slice, 65 in two ... are the fewest lanes that a list with helpers has
+        helped = sp.hmax > 1 && sp.hfill > 4 * WG / 2;
+        grid = std::max(std::max(1, v.target), std::min(fc.pl.items, 65535));
     } else {
-        const ForcePlan p = make_plan(n_i_max, c->n, ib, v.target, v.kmax, sp);
-        helped = p.H > 1;
-        grid = std::min(p.items, 1 << 20);
+        helped = fc.pl.H > 1;
+        grid = std::min(fc.pl.items, 1 << 20);
     }
     grid = (grid + 7) & ~7;  // a multiple of 8: the force kernel's XCD-aware item order
     const bool soft = c->eps > 0.0;
@@ -607,6 +619,8 @@ int32_t tiles_least(int prec) { return prec == NB_DS ? 257 : prec == NB_FP64 ? 4
 
 Spread tiles_spread(const nb_ctx *c) {
     Spread sp = spread_of(c, Variant{1, 2, 0, 0, 0});
+    sp.hslices = 16;  // helpers wherever they fit: the tile is staged once
+    sp.hfill = sp.fill;
     if (c->n <= RES_MAX) {  // the slices of the resident workgroup
         sp.wg = WGL;
         sp.pack = 0;

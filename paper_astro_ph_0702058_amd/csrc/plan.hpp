@@ -23,6 +23,8 @@ struct ForcePlan {
     int64_t P;   // padded i rows of one partial plane
 };
 
+__host__ __device__ inline int32_t log2i(int32_t v) { return 31 - __builtin_clz((uint32_t)v); }
+
 // Lanes per i-particle for a list of n_i with one i per work-item: a workgroup of wg lanes is
 // spread over the list, up to smax lanes (at most one wave) per i.
 __host__ __device__ inline int32_t lane_split(int32_t n_i, int32_t smax = 64, int32_t wg = WG) {
@@ -44,7 +46,32 @@ struct Spread {
     int32_t fill;     // lanes per tile that fill the chip (0: lane_split alone)
     int32_t wg = WG;  // lanes that lane_split spreads over a list
     int32_t pack = 0; // lists longer than a workgroup take slices that leave less padding
+    // Helpers double the instructions of a pair: a list takes them where they fill half the chip at
+    // most and a slice has 32 j-slots or more.  At the whole chip 600 rows of 20000 took 35 us for
+    // 31, 10 rows of 100000, 16 slices of one row each, 22 for 16.
+    int32_t hslices = 8, hfill = 0;
+    // More slices for a list: `most` of them, and (tq) only where they spread the work: an item
+    // has half the pairs of one before, so twice the items on the busiest compute unit are no gain
+    // once they keep its SIMDs busy.  DS 10 rows of 100000 (391 items, then 782) 27 us for 22 with a
+    // second doubling of its lanes, 250 of 20000 (316, then 632) 52 for 59.  `scalar`: arithmetics
+    // that leave their scalar j-loads with the first doubling; a second one pays only while no
+    // compute unit has two items (fixed point, 400 rows: of 8000 17 us for 22, of 20000 31 for 27).
+    int32_t most = 64;
+    int32_t tq = 0;      // tiles per compute unit in 1/4096 (0: not looked at)
+    int32_t scalar = 0;
 };
+
+// Items of n_i rows in S slices that the busiest compute unit gets.
+__host__ __device__ inline int32_t items_per_cu(int32_t n_i, int32_t S, int32_t tq) {
+    const int32_t ls = log2i(S), ib = WG >> ls;
+    return (((n_i + ib - 1) >> (log2i(WG) - ls)) * tq + 4095) >> 12;
+}
+__host__ __device__ inline bool more_slices(int32_t n_i, int32_t S, const Spread &sp) {
+    if (S >= sp.most || n_i * S * 2 > sp.fill) return false;
+    if (sp.tq == 0) return true;
+    const int32_t now = items_per_cu(n_i, S, sp.tq), then = items_per_cu(n_i, 2 * S, sp.tq);
+    return sp.scalar && S > 1 ? then <= 1 : then < 2 * (now > 2 ? now : 2);
+}
 
 // Slices of a list longer than a workgroup that takes S: more, up to 4, where the i-blocks of
 // fewer rows that they give leave at least 1/16 less padding (a padded row costs as much as a
@@ -69,9 +96,9 @@ __host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, in
     H = 1;
     if (n_i <= sp.fill) {  // also keeps the products below in range
         if (sp.hmax > 1) {
-            if (S * 4 <= 64 && n_i * S * 4 <= sp.fill) H = 4;
+            if (S <= sp.hslices && n_i * S * 4 <= sp.hfill) H = 4;
         } else {
-            while (S < sp.smax && n_i * S * 2 <= sp.fill) S *= 2;
+            while (more_slices(n_i, S, sp)) S *= 2;
         }
     }
     if (sp.pack && n_i > WG) S = pack_lanes(n_i, S);
@@ -90,9 +117,9 @@ __host__ __device__ inline ForcePlan make_plan(int32_t n_i, int32_t n, int32_t i
     p.ntiles = (n + TJ - 1) / TJ;
     row_lanes(n_i, sp, p.S, p.H);
     const int32_t L = p.S * p.H;
-    const int32_t ib = L > 1 ? WG / L : ib_max;
+    const int32_t ib = L > 1 ? WG >> log2i(L) : ib_max;  // powers of two: shifts, not divisions
     p.ib = ib;
-    p.n_iblk = (n_i + ib - 1) / ib;
+    p.n_iblk = (n_i + ib - 1) >> log2i(ib);
     int32_t K = p.n_iblk > 0 ? target / p.n_iblk : 1;
     if (K > kmax) K = kmax;
     if (K > p.ntiles) K = p.ntiles;

@@ -17,7 +17,8 @@ using namespace nbody;
 int main(int argc, char **argv) {
     int32_t v[9];
     for (int i = 1; i < 9; ++i) v[i] = atoi(argv[i]);
-    const Spread sp{v[5], v[6], v[7], WG, v[8]};
+    Spread sp{v[5], v[6], v[7], WG, v[8]};
+    sp.hfill = v[6] > 1 ? v[7] / 2 : 0;
     const int32_t T = (v[1] + TJ - 1) / TJ, most = 8192;
     const BlockRows rows = rows_by_tiles(v[1], v[4], v[2], v[3], sp, sp, most);
     printf("%d %d %d", rows.lo, rows.hi, rows.most);
@@ -69,3 +70,54 @@ def test_limit_follows_the_variant(limits, target, kmax, ib):
         lo, hi, most = limits(n, target, kmax, ib, 64, 1, 0, 0)
         if kmax < (n + 255) // 256:
             assert most == 0
+
+
+# argv: n, target, kmax.  For every spread a context may have: lists whose plan needs more partial rows
+# than the one without a spread, that the workspace is sized for, or whose lanes do not fit a wave.
+ROWS = r"""
+#include "plan.hpp"
+#include <cstdio>
+#include <cstdlib>
+using namespace nbody;
+int main(int, char **argv) {
+    const int32_t n = atoi(argv[1]), target = atoi(argv[2]), kmax = atoi(argv[3]);
+    const int32_t T = (n + TJ - 1) / TJ, fill = 256 * 1024 / T, tq = (int32_t)(((int64_t)T * 4096 + 255) / 256);
+    Spread all[5] = {Spread{64, 4, fill}, Spread{64, 1, fill, WG, 1}, Spread{64, 1, fill, WG, 1},
+                     Spread{64, 1, fill, WG, 1}, Spread{4, 1, fill}};
+    all[0].hfill = fill / 2;
+    all[2].most = 8; all[2].tq = tq;
+    all[3].most = 32; all[3].tq = tq;
+    all[4].most = 4; all[4].tq = tq; all[4].scalar = 1;
+    int bad = 0;
+    for (int k = 0; k < 5; ++k)
+        for (int32_t m = 1; m <= n; m += m < 20000 ? 1 : 977) {
+            const ForcePlan p = make_plan(m, n, WG, target, kmax, all[k]);
+            const ForcePlan q = make_plan(m, n, WG, target, kmax, Spread{all[k].smax, 1, 0});
+            const int64_t need = p.K > 1 ? p.K * p.P : 0, held = q.K > 1 ? q.K * q.P : 0;
+            const bool whole = (int64_t)p.K * p.tps >= p.ntiles && (int64_t)p.n_iblk * p.ib >= m &&
+                               p.items == p.n_iblk * p.K && p.ib * p.S * p.H == WG;
+            if (need > held || !whole || p.S * p.H > 64 || p.S < q.S)
+                bad += printf("spread %d rows %d: %lld of %lld\n", k, m, (long long)need, (long long)held) > 0;
+        }
+    return bad != 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rows_check(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rows")
+    src, exe = str(d / "a.cpp"), str(d / "a")
+    open(src, "w").write(ROWS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_astro_ph_0702058_amd", "csrc"), "-o", exe, src], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("n", [1, 100, 257, 1000, 5000, 20000, 65536, 100003, 1 << 20, 1 << 24])
+@pytest.mark.parametrize("target,kmax", [(4096, 1 << 16), (65536, 64), (1024, 1 << 16)])
+def test_spread_lists_fit_the_planes(rows_check, n, target, kmax):
+    """Every list length: more lanes per row cover every tile and row, at most 64 a row, and need no
+    more partial sums than the plan that the workspace is sized for."""
+    r = subprocess.run([rows_check, str(n), str(target), str(kmax)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout[:400]
