@@ -334,8 +334,9 @@ nb_status nb_sync(nb_ctx *ctx);
  * loaded), then one workgroup per cluster for the corrector, the new levels and the next
  * block.  A run replays a HIP
  * graph of steps_per_launch global steps until every cluster is done; or, where every cluster
- * has at most 8192 particles, one cooperative launch in which teams of resident workgroups, one
- * workgroup per 256 particles of a cluster, integrate a cluster each and then take the next.
+ * has at most 8192 particles and the blocks to be expected are small enough, one cooperative launch
+ * in which teams of resident workgroups, one workgroup per 256 particles of a cluster, integrate a
+ * cluster each and then take the next.
  * The state is one nb_state over all particles, clusters stored contiguously.
  * ------------------------------------------------------------------------------------------ */
 typedef struct nb_ens nb_ens;
@@ -404,9 +405,10 @@ nb_status nb_ens_set_lanes(nb_ens *ens, int32_t lanes, const int32_t *lane_of);
  * lanes' parts by wave shuffles in a fixed order.  NB_EINVAL otherwise.  Synchronising. */
 nb_status nb_ens_set_split(nb_ens *ens, int32_t smin);
 
-/* The same for an ensemble's cooperative launch (nb_set_tiles): up to `polls` looks until its
- * workgroups run at the same time, else the run goes on by global steps.  polls = 0: global steps
- * only, with the layout, split and lanes set above.  NB_EINVAL for polls outside [0, 2^24]. */
+/* The same for an ensemble's cooperative launch (nb_set_tiles): up to `polls` looks (default 2^20)
+ * until its workgroups run at the same time, else the run goes on by global steps.  After this call
+ * teams take every run that they can, whatever the blocks; polls = 0: none, global steps only, with
+ * the layout, split and lanes set above.  NB_EINVAL for polls outside [0, 2^24]. */
 nb_status nb_ens_set_teams(nb_ens *ens, int32_t polls);
 
 /* Sec. 2 start of run for every cluster: full force at time 0, initial steps from
@@ -421,8 +423,10 @@ nb_status nb_ens_init(nb_ens *ens, double eta);
  * that block, the next block, and the cluster's local block steps.  Graph runs without local
  * steps, with at least 8 lanes per block particle (nb_ens_set_split) and clusters of at most
  * 8192 particles need no global steps: teams of workgroups advance every cluster by itself (the
- * same block steps and limits; lanes and tiles per item change nothing then).  Returns NB_OK or
- * a latched device error. */
+ * same block steps and limits; lanes and tiles per item change nothing then).  Teams take a run
+ * unless the levels that nb_ens_init gave promise blocks so large that few clusters' workgroups
+ * would take longer over them than the whole device (nb_ens_set_teams decides otherwise).
+ * Returns NB_OK or a latched device error. */
 nb_status nb_ens_run(nb_ens *ens, double eta, int64_t t_end, int32_t steps_per_launch,
                      int64_t max_steps, int32_t use_graph);
 

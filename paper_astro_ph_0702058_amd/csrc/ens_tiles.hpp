@@ -362,8 +362,10 @@ __global__ void __launch_bounds__(WG, WAVES) ens_tiles(EnsTilesArgs a) {
     __shared__ EnsTilesSmem<M> z;
     const int32_t tm = a.t.wg_team[blockIdx.x], tile = a.t.wg_tile[blockIdx.x];
     const EnsTeam team = a.t.team[tm];
-    if (threadIdx.x == 0)
-        z.late = !roll_call(a.roll, a.epoch, roll_count(a.roll, a.present), a.polls);
+    if (threadIdx.x == 0) {
+        const EnsTilesArgs r = ens_tiles_args();
+        z.late = !roll_call(r.roll, r.epoch, roll_count(r.roll, r.present), r.polls);
+    }
     __syncthreads();
     if (z.late) return;
     bool bad = false, clamp = false, behind = false, lost = false;

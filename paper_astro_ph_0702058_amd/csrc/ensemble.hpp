@@ -22,7 +22,8 @@ namespace nbody {
 
 struct EnsCluster {  // device-resident per-cluster record
     int64_t t_cur, t_next, n_steps, n_active_sum;
-    int32_t n_act, n_pending, done, pad;
+    int32_t n_act, n_pending, done;
+    uint32_t outlook;  // ens_outlook: expected finest level << 24 | mean block of the run to come
 };
 
 struct EnsView {
@@ -50,6 +51,7 @@ struct EnsView {
     int32_t local_steps;
     int64_t local_work;
     int32_t smin;               // fewest lanes per block particle in a force item (power of 2)
+    int32_t coarser;            // ens_outlook
 };
 
 // Lanes per block particle of a cluster's force items: the lane split of its block, at least
@@ -320,6 +322,32 @@ __device__ void ens_block_step_local(const EnsView &e, const StateRW &s, int32_t
     __syncthreads();  // the corrected times and levels precede the next selection
 }
 
+// What the initial levels say of the run to come: the first steps are nu |a|/|k|, later ones
+// sqrt(nu) of such a ratio and so `coarser` levels coarser, but not below lmin.  With every particle
+// that much coarser, a block at each multiple of the finest step holds sum_i 2^(l_i - finest) rows on
+// average; a third more than that fits Plummer spheres of 300 to 8192 within a factor of 1.7 over
+// largest steps of 2^-3 to 2^-11.  By the cluster's workgroup; valid in work-item 0.
+__device__ uint32_t ens_outlook(const int32_t *level, int32_t lo, int32_t hi, int32_t lmin,
+                                int32_t coarser, int64_t *red) {
+    int32_t fine = lmin;
+    double sum = 0.0;  // of 2^l
+    for (int32_t i = lo + threadIdx.x; i < hi; i += WGL) {
+        const int32_t l = level[i] - coarser > lmin ? level[i] - coarser : lmin;
+        fine = l > fine ? l : fine;
+        sum += __builtin_ldexp(1.0, l);
+    }
+    fine = (int32_t)-block_min_i64<WGL>(-(int64_t)fine, red);
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) ((double *)red)[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    sum = 0.0;
+    for (int w = 0; w < WGL / 64; ++w) sum += ((const double *)red)[w];
+    __syncthreads();
+    sum = __builtin_ceil(__builtin_ldexp(sum, -fine) * (4.0 / 3.0));
+    return (uint32_t)fine << 24 | (uint32_t)(sum < 16777215.0 ? sum : 16777215.0);
+}
+
 // One workgroup of WGL per cluster.
 //   phase 0: start of run -- block = every particle, times 0, block time 0
 //   phase 1: after the start-of-run force -- store a, k, pot and the initial levels
@@ -381,6 +409,10 @@ __global__ void __launch_bounds__(WGL) ens_local(EnsView e, StateRW s, double et
             }
         }
         __syncthreads();
+        if (phase == 1) {
+            const uint32_t outlook = ens_outlook(s.level, lo, hi, e.lmin, e.coarser, red);
+            if (threadIdx.x == 0) cl->outlook = outlook;
+        }
         if (phase == 2 && threadIdx.x == 0 && n_act > 0) {
             cl->t_cur = t_next;
             cl->n_steps += 1;

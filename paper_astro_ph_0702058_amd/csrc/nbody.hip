@@ -172,6 +172,8 @@ struct nb_ens {
     Epochs epochs, turns;         // of its launches
     uint64_t present = 0;         // workgroups of all launches so far
     int32_t polls = TILE_POLLS;   // nb_ens_set_teams
+    bool chosen = false;          // by the caller: teams wherever they can run
+    int32_t pays = -1;            // whether teams suit this start of a run (-1: to be found)
     int32_t n_wgs = 0;
     std::vector<int32_t> tile_off_h, tables_h;
     int32_t *tile_off = nullptr, *tables = nullptr;
@@ -1499,7 +1501,7 @@ EnsView ens_view(const nb_ens *e, int64_t t_end, int lane = -1) {
     v.partial = e->partial; v.crit = e->crit; v.flags = e->flags;
     v.lmin = e->lmin; v.lmax = e->lmax; v.tick_len = std::ldexp(1.0, -e->lmax); v.t_end = t_end;
     v.local_limit = e->local_limit; v.local_steps = e->local_steps; v.local_work = e->local_work;
-    v.smin = e->smin;
+    v.smin = e->smin; v.coarser = 0;
     return v;
 }
 
@@ -1549,6 +1551,7 @@ nb_status ens_enqueue_local(nb_ens *e, double eta, int32_t phase, int64_t t_end,
                             bool local = true, int lane = -1) {
     EnsView v = ens_view(e, t_end, lane);
     if (!local) v.local_limit = 0;
+    v.coarser = std::max(0, (int32_t)std::lround(0.5 * std::log2(1.0 / eta)) - 1);
     switch (e->prec) {
         case NB_FP32: ens_local<ModeF32><<<v.C, WGL, 0, s>>>(v, ens_state(e), eta, phase); break;
         case NB_DS: ens_local<ModeDS><<<v.C, WGL, 0, s>>>(v, ens_state(e), eta, phase); break;
@@ -1660,6 +1663,7 @@ size_t ens_layout(nb_ens *e, char *base) {
     e->part_off = k.take<int64_t>(C + 1);
     e->eps2 = k.take<double>(C);
     e->cl = k.take<EnsCluster>(C);
+    e->roll = k.take<uint64_t>(ROLL_WORDS);  // behind the records: one copy to the host brings both
     e->active = k.take<int32_t>(N);
     e->flags = k.take<int32_t>(4);
     e->partial = k.take<double>((size_t)e->part_off_h[C]);
@@ -1671,7 +1675,6 @@ size_t ens_layout(nb_ens *e, char *base) {
     e->tables = k.take<int32_t>(EnsTables::words(e->C));
     e->assign = k.take<uint64_t>(ET_WGS);
     e->word = k.take<uint64_t>(3 * (size_t)e->tile_off_h[C]);
-    e->roll = k.take<uint64_t>(ROLL_WORDS);
     return k.off;
 }
 
@@ -1691,6 +1694,34 @@ nb_status ens_flags(nb_ens *e) {
 const void *ens_tiles_kernel(int prec) {
     return prec == NB_FP32 ? (const void *)ens_tiles<ModeF32, 4>
          : prec == NB_DS ? (const void *)ens_tiles<ModeDS, 3> : (const void *)ens_tiles<ModeF64, 3>;
+}
+
+// Whether teams take a run in less time than global steps, from each cluster's outlook: a team's
+// step costs its latency and its share of the block's pairs on a compute unit to itself, a global step
+// its own latency, longer the more tiles an item has, and all blocks' pairs on the whole device.  Found
+// once per nb_ens_init, so that a run's sums do not depend on where its calls are cut.  One cluster of
+// 8192, FP32, by teams and by global steps: 32 and 39 us a step with blocks of 160, 187 and 50 with
+// blocks of 1289 (steps of at most 2^-11); DS, one of 4096: 111 and 66, 1083 and 98.
+bool ens_teams_pay(const nb_ens *e, const std::vector<EnsCluster> &cl, const std::vector<int32_t> &teams) {
+    struct Costs { double team, row, step, tile, pairs; };  // us; pairs a us on the device
+    const Costs k = e->prec == NB_DS ? Costs{14, 0.80, 15, 10.5, 0.27e6}
+                  : e->prec == NB_FP64 ? Costs{10, 0.14, 12, 3.0, 0.8e6} : Costs{10, 0.14, 12, 2.8, 1.1e6};
+    uint32_t fine = 0;
+    for (const auto &x : cl) fine = std::max(fine, x.outlook >> 24);
+    const double shared = std::max(1.0, 0.5 * e->n_wgs / e->num_cu);  // two waves of four fill a SIMD
+    std::vector<double> load(ET_TILES + 1, 0.0);
+    double pairs = 0.0;
+    int32_t tpi = 1;
+    for (int32_t c = 0; c < e->C; ++c) {
+        const int32_t n = e->off_h[c + 1] - e->off_h[c], T = (n + TJ - 1) / TJ;
+        const double steps = std::ldexp(1.0, (int)(cl[c].outlook >> 24) - (int)fine);  // relative
+        const double rows = std::min<double>(cl[c].outlook & 0xffffff, n);
+        load[T] += steps * (k.team + k.row * shared * rows) / teams[T];
+        pairs += steps * rows * n;
+        tpi = std::max(tpi, e->tpi_h[c]);
+    }
+    const double global = (k.step + k.tile * tpi) * (1.0 + 0.1 * std::log2((double)e->C)) + pairs / k.pairs;
+    return *std::max_element(load.begin(), load.end()) < (e->prec == NB_DS ? 0.9 : 1.2) * global;
 }
 
 // Teams and queues of a run from the clusters' records: a cluster's work is about the number of
@@ -1741,6 +1772,8 @@ bool ens_plan_teams(nb_ens *e, const std::vector<EnsCluster> &cl, int64_t t_end)
         used += best;
     }
     e->n_wgs = used;
+    if (!e->chosen && e->pays < 0) e->pays = ens_teams_pay(e, cl, teams);
+    if (!e->chosen && !e->pays) return false;
     e->tables_h.assign(EnsTables::words(e->C), 0);
     const EnsTables t(e->tables_h.data(), e->C);
     int32_t place = 0, wg = 0, team = 0;
@@ -1768,16 +1801,20 @@ nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64
     int64_t left = max_steps > 0 ? (max_steps + spl - 1) / spl * spl : INT64_MAX;
     uint64_t verdict = 0;
     std::vector<EnsCluster> h(e->C);
+    const size_t to_verdict = (const char *)(e->roll + ROLL_VERDICT) - (const char *)e->cl;
+    std::vector<char> copy(to_verdict + sizeof verdict);
     auto records = [&]() -> nb_status {
-        EHIP_OK(e, hipMemcpyAsync(h.data(), e->cl, e->C * sizeof(EnsCluster), hipMemcpyDeviceToHost, e->stream));
+        EHIP_OK(e, hipMemcpyAsync(copy.data(), e->cl, copy.size(), hipMemcpyDeviceToHost, e->stream));
         EHIP_OK(e, hipStreamSynchronize(e->stream));
+        std::memcpy(h.data(), copy.data(), e->C * sizeof(EnsCluster));
+        std::memcpy(&verdict, copy.data() + to_verdict, sizeof verdict);
         return NB_OK;
     };
     if ((r = records()) != NB_OK) return r;
     int64_t prev = -1;
     while (left > 0) {
         if (!ens_plan_teams(e, h, t_end)) {
-            e->teams_ok = false;
+            if (e->pays != 0) e->teams_ok = false;
             return NB_OK;
         }
         EHIP_OK(e, hipMemcpyAsync(e->tables, e->tables_h.data(), e->tables_h.size() * sizeof(int32_t),
@@ -1815,7 +1852,6 @@ nb_status ens_run_teams(nb_ens *e, double eta, int64_t t_end, int32_t spl, int64
             return NB_OK;
         }
         e->present = a.present;
-        EHIP_OK(e, hipMemcpyAsync(&verdict, e->roll + ROLL_VERDICT, sizeof verdict, hipMemcpyDeviceToHost, e->stream));
         if ((r = records()) != NB_OK) return r;
         if (!(verdict & 1)) return NB_OK;  // the workgroups did not start together
         left -= a.steps;
@@ -2067,6 +2103,7 @@ nb_status nb_ens_set_teams(nb_ens *e, int32_t polls) {
     if (polls < 0 || polls > TILE_POLLS_MAX)
         return fail(e, NB_EINVAL, "nb_ens_set_teams: polls must lie in [0, %d]", TILE_POLLS_MAX);
     e->polls = polls;
+    e->chosen = polls > 0;
     return NB_OK;
 }
 
@@ -2137,6 +2174,7 @@ nb_status nb_ens_init(nb_ens *e, double eta) {
     if ((r = ens_enqueue_local(e, eta, 0, INT64_MAX, e->stream, false)) != NB_OK) return r;
     if ((r = ens_enqueue_force(e, INT64_MAX, e->stream, false)) != NB_OK) return r;
     if ((r = ens_enqueue_local(e, eta, 1, INT64_MAX, e->stream, false)) != NB_OK) return r;
+    e->pays = -1;
     e->initialised = true;
     return NB_OK;
 }
@@ -2149,7 +2187,7 @@ nb_status nb_ens_run(nb_ens *e, double eta, int64_t t_end, int32_t steps_per_lau
     EHIP_OK(e, hipSetDevice(e->device));
     if (use_graph) e->run_tend = t_end;
     // teams: graph runs (eager ones keep the launches apart) without local steps, at least 8 lanes a row
-    if (use_graph && e->teams_ok && e->polls > 0 && e->local_limit == 0 && e->smin >= 8) {
+    if (use_graph && e->teams_ok && e->polls > 0 && (e->chosen || e->pays != 0) && e->local_limit == 0 && e->smin >= 8) {
         bool done = false;
         const nb_status r = ens_run_teams(e, eta, t_end, steps_per_launch, max_steps, done);
         if (r != NB_OK || done) return r;

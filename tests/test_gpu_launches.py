@@ -167,3 +167,32 @@ def test_small_runs_from_many_threads():
         assert g is not None
         for key in a:
             assert np.array_equal(a[key], g[key]), key
+
+
+def _blocks(sizes, prec, lmin, polls, max_steps=0):
+    parts = [plummer(int(k), 300 + c) for c, k in enumerate(sizes)]
+    st = nbody.DeviceState(*(np.concatenate([p[k] for p in parts]) for k in range(3)))
+    with nbody.Ensemble(sizes, [1.0 / k for k in sizes], lmin=lmin, precision=prec) as ens:
+        if polls is not None:
+            ens.nb_ens_set_teams(polls)
+        ens.nb_ens_bind(st)
+        ens.nb_ens_init(0.02)
+        while not all(c.flags for c in ens.nb_ens_control()):  # max_steps steps a call
+            ens.nb_ens_run(0.02, 1 / 64, steps_per_launch=8, max_steps=max_steps)
+    return st.numpy()
+
+
+@pytest.mark.parametrize("sizes,lmin,teams", [([4096], 11, False), ([2048, 1500], 11, False),
+                                              ([2048], 3, True), ([2000] * 12, 3, True)])
+def test_large_blocks_of_few_clusters_take_the_whole_device(sizes, lmin, teams):
+    """Where nearly every block is a whole cluster, a few workgroups would take five times as long
+    over a block step as global steps: those take the run (their FP64 sums are in another order
+    than teams', so the bits tell).  The choice is the start's: wherever the run is cut, its bits are
+    the same."""
+    ref = _blocks(sizes, "fp64", lmin, (1 << 20) if teams else 0)
+    other = _blocks(sizes, "fp64", lmin, 0 if teams else 1 << 20)
+    assert not np.array_equal(ref["x"], other["x"])
+    for max_steps in (0, 8):
+        got = _blocks(sizes, "fp64", lmin, None, max_steps)
+        for key in ref:
+            assert np.array_equal(got[key], ref[key]), (key, max_steps)
