@@ -282,6 +282,12 @@ Variant default_variant(int32_t n, int prec, int num_cu, bool block) {
     v.ipl = 1;
     v.unroll = 2;
     v.target = num_cu * (block ? BLOCK_ITEMS_PER_CU : FULL_ITEMS_PER_CU);
+    // of the largest sets that tiles hold, so many items that the blocks which tiled runs take
+    // (tiles_rows) have every tile in a plane of its own: the chain sums them in the tiles' order
+    // (lists of N = 40000 - 65536 at 16 items per CU and so: within 1 % up to 20000 rows, 3.5 % faster
+    // to 4 % slower past that; the N = 65536 run's blocks of 4097 - 7168 rows stay in its tiles)
+    const int32_t T = (n + TJ - 1) / TJ;
+    if (block && T <= TL_TILES) v.target = std::max(v.target, T * (TL_LONG / WG));
     v.kmax = block ? 1 << 16 : FULL_KMAX;  // K is also bounded by the tile count
     // scalar j-loads from 1 tile per item in full-force calls and from 4 in block steps
     // (interleaved runs on one MI355X against 16 tiles: the shared-step gradient at N = 16384,
@@ -631,15 +637,16 @@ Spread tiles_spread(const nb_ctx *c) {
 }
 
 // Rows of the blocks that tiles take; others go to the chain.  At most what the row map in LDS and
-// the partial planes, held twice, hold (past 64 tiles 7/8 of that: larger blocks are the chain's,
+// the partial planes, held twice, hold (past 64 tiles TL_LONG rows: larger blocks are the chain's,
 // which uses every compute unit); and beyond the sets that a resident workgroup could hold, only
 // blocks that the chain sums in the same order, so that a run's result does not depend on where its
-// launches are cut: at the default targets the chain joins tiles past 4096 rows at 256 tiles, 5120 at
-// 196, and from 2049 to 3840 rows in FP64 and double-single at 130.  Found once per variant (0.4 ms).
+// launches are cut: at the default targets the chain joins tiles past 7168 rows at 256 tiles, and
+// from 2049 to 3840 rows in FP64 and double-single at 130.  Found once per variant (0.4 ms).
 BlockRows tiles_rows(nb_ctx *c) {
     if (c->tiles_rows.most >= 0) return c->tiles_rows;
     const int64_t T = (c->n + TJ - 1) / TJ;
-    const int32_t most = (int32_t)std::min<int64_t>(c->partial_rows * (T > 64 ? 7 : 8) / (16 * T), TL_ROWS);
+    const int32_t most = (int32_t)std::min<int64_t>(c->partial_rows * (T > 64 ? 7 : 8) / (16 * T),
+                                                    T > 64 ? TL_LONG : TL_ROWS);
     const Variant &v = c->var_block;
     c->tiles_rows = c->n <= RES_MAX ? BlockRows{most, most, most}
                   : rows_by_tiles(c->n, WG * v.ipl, v.target, v.kmax, spread_of(c, v), tiles_spread(c), most);
@@ -749,7 +756,8 @@ void ctx_plan(nb_ctx *c) {
         // scalar-load threshold does not change the plan
         rows = std::max(rows, partial_rows_for(n, Variant{ipl, 1, c->num_cu * FULL_ITEMS_PER_CU / ipl,
                                                           FULL_KMAX, 1}, smax_of(precision)));
-        rows = std::max(rows, partial_rows_for(n, Variant{ipl, 1, c->num_cu * BLOCK_ITEMS_PER_CU,
+        rows = std::max(rows, partial_rows_for(n, Variant{ipl, 1, ipl == 1 ? c->var_block.target
+                                                                            : c->num_cu * BLOCK_ITEMS_PER_CU,
                                                           1 << 16, 1}, smax_of(precision)));
     }
     // the force VJP writes K * P rows of its plan even when K = 1

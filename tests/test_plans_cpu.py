@@ -56,8 +56,9 @@ def test_tiled_blocks_join_no_tiles(limits, n, prec):
     all up to a limit, but for the lengths of several i-blocks that take more slices."""
     fill = 256 * 1024 // ((n + 255) // 256)
     spread = (64, 4, fill, 0) if prec == "fp32" else (64, 1, fill, 1)
-    lo, hi, most = limits(n, 4096, 1 << 16, 256, *spread)
-    assert most == {33023: 31 * 256, 50000: 5120, 65536: 4096}.get(n, 8192)
+    tiles = (n + 255) // 256
+    lo, hi, most = limits(n, max(4096, 28 * tiles), 1 << 16, 256, *spread)
+    assert most == {33023: 31 * 256, 50000: 7168, 65536: 7168}.get(n, 8192)
     if prec == "fp32":
         assert lo == most
     else:
