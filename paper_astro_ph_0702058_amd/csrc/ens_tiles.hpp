@@ -362,14 +362,14 @@ __global__ void __launch_bounds__(WG, WAVES) ens_tiles(EnsTilesArgs a) {
     __shared__ EnsTilesSmem<M> z;
     const int32_t tm = a.t.wg_team[blockIdx.x], tile = a.t.wg_tile[blockIdx.x];
     const EnsTeam team = a.t.team[tm];
+    bool bad = false, clamp = false, behind = false, lost = false;
+    int32_t place = team.first;
     if (threadIdx.x == 0) {
         const EnsTilesArgs r = ens_tiles_args();
         z.late = !roll_call(r.roll, r.epoch, roll_count(r.roll, r.present), r.polls);
     }
     __syncthreads();
-    if (z.late) return;
-    bool bad = false, clamp = false, behind = false, lost = false;
-    int32_t place = team.first;
+    if (z.late) place = team.last;  // no cluster (a return here cost the loop 2 %: registers)
     for (uint64_t turn = a.turn; place < team.last;) {
         if (!ens_tiles_cluster<M>(a, z, a.t.queue[place], tile, team.tiles, bad, clamp, behind)) {
             lost = true;
