@@ -1807,6 +1807,10 @@ __host__ __device__ inline EnergyPlan energy_plan(int32_t n, int32_t num_cu) {
     return p;
 }
 
+__device__ __forceinline__ bool no_position(double x, double y, double z) {
+    return __builtin_isunordered(x, y) || __builtin_isunordered(z, z);
+}
+
 // One staged tile: the terms m_j s^-1/2 of rows i with j > i (each pair once).  MASK: the tile may
 // hold j <= i (or padding j, whose mass is zero).
 template <int IPL, bool SOFT, bool MASK>
@@ -1831,7 +1835,8 @@ __device__ __forceinline__ void energy_tile(const double4 *sm, int32_t j0, int32
 // Per item, the compensated sum of m_i m_j s^-1/2 over its pairs i < j.  FP64 VALU bound: 13
 // instructions a pair and the quarter-rate reciprocal square root, 70 cycles a wave at N = 65536
 // (1.08 ms with both ends of the call; rows against every j, one workgroup per 256 rows over all
-// tiles: 3.69 ms, and at N = 1024 81 against 32 us).
+// tiles: 3.69 ms, and at N = 1024 81 against 32 us).  A particle whose position is not a number is
+// in no pair: staged without mass, its own row dropped, so that a softened pair needs no test.
 template <int IPL, bool SOFT>
 __global__ void __launch_bounds__(WG) energy_pairs(const double *xp, const double *m, int32_t n,
                                                    double eps2, EnergyPlan pl, Sum2 *out) {
@@ -1862,8 +1867,12 @@ __global__ void __launch_bounds__(WG) energy_pairs(const double *xp, const doubl
         for (int32_t t = t0; t < t1; ++t) {
             __syncthreads();
             const int32_t j = t * TJ + (int32_t)threadIdx.x;
-            sm[threadIdx.x] = j < n ? double4{xp[j], xp[(int64_t)n + j], xp[2 * (int64_t)n + j], m[j]}
-                                    : double4{0.0, 0.0, 0.0, 0.0};
+            double4 q{0.0, 0.0, 0.0, 0.0};
+            if (j < n) {
+                const double4 r{xp[j], xp[(int64_t)n + j], xp[2 * (int64_t)n + j], m[j]};
+                if (!no_position(r.x, r.y, r.z)) q = r;
+            }
+            sm[threadIdx.x] = q;
             __syncthreads();
             double ts[IPL] = {};
             if (t * TJ <= last) energy_tile<IPL, SOFT, true>(sm, t * TJ, slice, S, xi, i, eps2, ts);
@@ -1873,7 +1882,8 @@ __global__ void __launch_bounds__(WG) energy_pairs(const double *xp, const doubl
         }
 #pragma unroll
         for (int p = 0; p < IPL; ++p)
-            if (i[p] < n) sum.add(m[i[p]] * (w[p].s + w[p].c));
+            if (i[p] < n)
+                sum.add(m[i[p]] * (no_position(xi[p][0], xi[p][1], xi[p][2]) ? 0.0 : w[p].s + w[p].c));
     }
     sum = wg_sum2<WG>(sum, red);
     if (threadIdx.x == 0) out[blockIdx.x] = sum;
