@@ -97,7 +97,10 @@ def bench_ensemble(args, emit=True):
         layout = ensemble_autotune(ens, st, x0, v0, eta)
         log(f"[bench] ensemble layout {layout}")
     lanes = None
-    if args.ens_lanes == "probe":
+    ens.nb_ens_init(eta)
+    ens.nb_ens_run(eta, args.t_end, steps_per_launch=args.ens_spl, max_steps=1)
+    st.x.copy_(x0); st.v.copy_(v0)
+    if args.ens_lanes == "probe" and not ens.nb_ens_took_teams():  # teams have no lanes
         # untimed, like the tuner: a run to t = 1/4 picks the 4 clusters with the most block
         # steps for a lane of their own
         from paper_astro_ph_0702058_amd.tuning import ensemble_lanes
@@ -122,6 +125,7 @@ def bench_ensemble(args, emit=True):
         step()
     torch.cuda.synchronize()
     t1 = time.perf_counter()
+    path = "teams" if ens.nb_ens_took_teams() else "global steps"
     ctl = ens.nb_ens_control()
     ek, ep = ens.nb_ens_energy()
     st.x.copy_(x0); st.v.copy_(v0)
@@ -141,7 +145,7 @@ def bench_ensemble(args, emit=True):
                                f"(total {int(sizes.sum())}), eps=1/N_c, eta=0.02, t -> {args.t_end}",
                    "clusters": args.clusters, "particles": int(sizes.sum()),
                    "local_blocks": args.ens_local or "default",
-                   "interactions_per_run": inter, "layout": layout, "lanes": lanes,
+                   "interactions_per_run": inter, "layout": layout, "path": path, "lanes": lanes,
                    "max_block_steps": max(c.n_steps for c in ctl),
                    "mean_block_steps": float(np.mean([c.n_steps for c in ctl])),
                    "dE_over_E_max": float(de.max()), "dE_over_E_median": float(np.median(de))},
@@ -657,8 +661,8 @@ def main():
                     help="adjoint: recompute the next checkpoint segment on a second stream "
                          "while the current segment's step VJPs run (default on)")
     ap.add_argument("--ens-lanes", default="probe", choices=["probe", "one"],
-                    help="ensemble: two independent lanes chosen by an untimed probe run "
-                         "(default), or one lane")
+                    help="ensemble, where it runs by global steps: two independent lanes chosen by "
+                         "an untimed probe run (default), or one lane")
     ap.add_argument("--ens-spl", type=int, default=128,
                     help="ensemble: global steps per graph replay (one host check per replay)")
     ap.add_argument("--ens-local", default="",
@@ -952,6 +956,7 @@ def other_configs(args):
                            "frac_fp32_peak": r["roofline"]["frac"],
                            "max_block_steps": r["config"]["max_block_steps"],
                            "dE_over_E_median": r["config"]["dE_over_E_median"],
+                           "path": r["config"]["path"],
                            "lanes": (r["config"]["lanes"] or {}).get("lanes", 1)}
     r = bench_adjoint(sub, emit=False)
     out["adjoint_n16384"] = {"ms_per_gradient": r["ms_per_step"], "interactions_per_s": r["value"]}

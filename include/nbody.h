@@ -411,6 +411,10 @@ nb_status nb_ens_set_split(nb_ens *ens, int32_t smin);
  * the layout, split and lanes set above.  NB_EINVAL for polls outside [0, 2^24]. */
 nb_status nb_ens_set_teams(nb_ens *ens, int32_t polls);
 
+/* *took (HOST): 1 if teams took the last nb_ens_run to its end, 0 if global steps did, whose layout,
+ * split and lanes then count. */
+nb_status nb_ens_took_teams(nb_ens *ens, int32_t *took);
+
 /* Sec. 2 start of run for every cluster: full force at time 0, initial steps from
  * Eq. initTimestep with this eta, times 0. */
 nb_status nb_ens_init(nb_ens *ens, double eta);

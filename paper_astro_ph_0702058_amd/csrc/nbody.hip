@@ -173,6 +173,7 @@ struct nb_ens {
     uint64_t present = 0;         // workgroups of all launches so far
     int32_t polls = TILE_POLLS;   // nb_ens_set_teams
     bool chosen = false;          // by the caller: teams wherever they can run
+    bool by_teams = false;        // the last nb_ens_run
     int32_t pays = -1;            // whether teams suit this start of a run (-1: to be found)
     int32_t n_wgs = 0;
     std::vector<int32_t> tile_off_h, tables_h;
@@ -2115,6 +2116,13 @@ nb_status nb_ens_set_teams(nb_ens *e, int32_t polls) {
     return NB_OK;
 }
 
+nb_status nb_ens_took_teams(nb_ens *e, int32_t *took) {
+    if (!e) return NB_EINVAL;
+    if (!took) return fail(e, NB_EINVAL, "nb_ens_took_teams: host output required");
+    *took = e->by_teams;
+    return NB_OK;
+}
+
 nb_status nb_ens_set_lanes(nb_ens *e, int32_t lanes, const int32_t *lane_of) {
     if (!e) return NB_EINVAL;
     if (lanes < 1 || lanes > ENS_MAX_LANES)
@@ -2193,11 +2201,13 @@ nb_status nb_ens_run(nb_ens *e, double eta, int64_t t_end, int32_t steps_per_lau
     if (!e->initialised) return fail(e, NB_ESTATE, "nb_ens_run before nb_ens_init");
     if (!(eta > 0.0) || steps_per_launch < 1) return fail(e, NB_EINVAL, "bad arguments");
     EHIP_OK(e, hipSetDevice(e->device));
+    e->by_teams = false;
     if (use_graph) e->run_tend = t_end;
     // teams: graph runs (eager ones keep the launches apart) without local steps, at least 8 lanes a row
     if (use_graph && e->teams_ok && e->polls > 0 && (e->chosen || e->pays != 0) && e->local_limit == 0 && e->smin >= 8) {
         bool done = false;
         const nb_status r = ens_run_teams(e, eta, t_end, steps_per_launch, max_steps, done);
+        e->by_teams = done;
         if (r != NB_OK || done) return r;
     }
     if (e->lanes > 1) return ens_run_lanes(e, eta, t_end, steps_per_launch, max_steps, use_graph);

@@ -59,7 +59,7 @@ EXPORTS = ["nb_create", "nb_destroy", "nb_set_stream", "nb_bind", "nb_init",
            "nb_scratch_bytes", "nb_bind_scratch", "nb_ens_scratch_bytes", "nb_ens_bind_scratch",
            "nb_ens_set_local", "nb_fma_rate", "nb_force_noalloc",
            "nb_set_resident", "nb_ens_set_split", "nb_ens_set_lanes",
-           "nb_set_tiles", "nb_ens_set_teams"]
+           "nb_set_tiles", "nb_ens_set_teams", "nb_ens_took_teams"]
 
 _lib = None
 
@@ -120,6 +120,7 @@ def load_library(path: str = LIB_PATH):
         "nb_set_resident": [P, I32],
         "nb_set_tiles": [P, I32],
         "nb_ens_set_teams": [P, I32],
+        "nb_ens_took_teams": [P, P],
     }
     for name, args in sig.items():
         f = getattr(lib, name)
@@ -504,6 +505,7 @@ class Ensemble:
         self.offsets[1:] = np.cumsum(sizes)
         self.eps = np.ascontiguousarray(np.broadcast_to(np.asarray(eps, np.float64), (self.C,)))
         self.lmin, self.lmax, self.precision = int(lmin), int(lmax), precision
+        self.polls = None  # of nb_ens_set_teams, if it was called
         h = ctypes.c_void_p()
         st = self.lib.nb_ens_create(ctypes.byref(h), self.C,
                                     self.offsets.ctypes.data_as(ctypes.c_void_p),
@@ -572,6 +574,13 @@ class Ensemble:
         """Looks (about 1 us each) until all workgroups of a run by teams run at the same time; else
         global steps take the run.  0: global steps only."""
         self._check(self.lib.nb_ens_set_teams(self.h, int(polls)))
+        self.polls = int(polls)
+
+    def nb_ens_took_teams(self):
+        """Whether teams took the last nb_ens_run to its end (else global steps did)."""
+        took = ctypes.c_int32()
+        self._check(self.lib.nb_ens_took_teams(self.h, ctypes.byref(took)))
+        return bool(took.value)
 
     def nb_ens_set_lanes(self, lane_of=None):
         """Independent lanes: lane_of[c] in [0, lanes) for every cluster (None: one lane)."""

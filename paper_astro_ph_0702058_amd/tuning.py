@@ -11,6 +11,8 @@ from __future__ import annotations
 import json
 import os
 
+TEAM_POLLS = 1 << 20  # nb_ens_set_teams: the library's default
+
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "libnbody_tune.json")
 
 
@@ -55,16 +57,19 @@ def autotune(ctx, cache_path: str | None = DEFAULT_CACHE, reps: int = 2, retune:
 
 
 def ensemble_autotune(ens, state, x0, v0, eta, t_probe=0.25, steps_per_launch=128):
-    """Choose the ensemble's force work layout by timing runs from the initial state to
-    t_probe (default 1/4: the phase in which nearly every cluster is active and which takes
-    most of a run's time): first the fewest lanes per block particle of a force item (smin,
+    """Choose how an ensemble runs by timing runs from the initial state to t_probe (default 1/4:
+    the phase in which nearly every cluster is active and which takes most of a run's time).
+    Layouts are searched among global steps, the only runs that they change
+    (nb_ens_set_teams(0)): first the fewest lanes per block particle of a force item (smin,
     which bounds an item's size), then the j-loop unroll, then, for each size class of clusters
     (N < 512, 512 <= N < 2048, N >= 2048), the whole j-tiles per work item halved or doubled
     from the default's.  The winner is timed again against the library's default layout (at
-    most 4 j-ranges per cluster, smin 8, unroll 2) on the same probe and kept only if it is
-    faster; the state is
-    restored from (x0, v0) before every trial and after tuning.  Returns the layout in effect
-    with both probe times and whether the search beat the default."""
+    most 4 j-ranges per cluster, smin 8, unroll 2) and against a run by teams in that layout
+    (unless the caller has switched teams off) on the same probe, and the fastest of the three
+    stays set: teams with nb_ens_set_teams on, a layout with them off.  The state is
+    restored from (x0, v0) before every trial and after tuning.  Returns the layout in effect,
+    whether teams are, the probe times (None: no run by teams) and whether the search beat both
+    the default layout and the teams."""
     import time
     import numpy as np
     import torch
@@ -82,9 +87,17 @@ def ensemble_autotune(ens, state, x0, v0, eta, t_probe=0.25, steps_per_launch=12
         ens.nb_ens_run(eta, t_probe, steps_per_launch=steps_per_launch)
         return time.perf_counter() - t
 
+    def by_teams():
+        ens.nb_ens_set_teams(polls or TEAM_POLLS)
+        t = trial(*default)
+        return t if ens.nb_ens_took_teams() else None
+
     # the library's default: at most 4 j-ranges per cluster, 8 lanes per block particle
     ntiles = (sizes + 255) // 256
     default = (np.maximum(1, (ntiles + 3) // 4).astype(np.int32), 8, 1, 2)
+    polls = ens.polls
+    t_teams = None if polls == 0 else by_teams()  # warm
+    ens.nb_ens_set_teams(0)
     trial(*default)  # warm: graphs and caches of the default layout
     tpi = default[0].copy()
     timed = {sm: trial(tpi, sm, 1, 2) for sm in (2, 4, 8, 16)}
@@ -107,27 +120,35 @@ def ensemble_autotune(ens, state, x0, v0, eta, t_probe=0.25, steps_per_launch=12
     # the search's winner against the default, each timed once more, in that order
     t_best = trial(tpi, smin, 1, unroll)
     t_default = trial(*default)
-    beats = t_best < t_default
+    if t_teams is not None:
+        t_teams = by_teams()
+    teams = t_teams is not None and t_teams < min(t_best, t_default)
+    beats = t_best < t_default and not teams
     if not beats:
         tpi, smin, _, unroll = default
+    ens.nb_ens_set_teams((polls or TEAM_POLLS) if teams else 0)
     ens.nb_ens_set_layout(tpi, 1, unroll)
     ens.nb_ens_set_split(smin)
     state.x.copy_(x0); state.v.copy_(v0)
     return {"smin": int(smin), "ipl": 1, "unroll": int(unroll),
             "tiles_per_item_by_class": [sorted(set(int(t) for t in tpi[m])) if m.any() else None
                                         for m in classes],
-            "probe_t_end": t_probe, "probe_seconds_chosen": t_best,
-            "probe_seconds_default": t_default, "beats_default": bool(beats)}
+            "teams": bool(teams), "probe_t_end": t_probe,
+            "probe_seconds_chosen": min(t for t in (t_best, t_default, t_teams) if t is not None),
+            "probe_seconds_default": t_default, "probe_seconds_teams": t_teams,
+            "beats_default": bool(beats)}
 
 
 def ensemble_lanes(ens, state, x0, v0, eta, t_probe=0.25, top=4, steps_per_launch=128):
-    """Two independent lanes for an ensemble (nb_ens_set_lanes): a probe run to t_probe from the
-    initial state (x0, v0) counts every cluster's block steps, and the `top` clusters with the
-    most steps get a lane of their own, so the global step count of the rest no longer follows
-    the cluster with the tightest encounters.  On MI355X, 512 Plummer clusters of 64-4096
-    particles to t = 1 (alternated on one machine): 0.657-0.658 s against 0.757-0.758 s in one
-    lane; 2 / 8 / 16 / 32 / 64 clusters apart 0.661 / 0.683 / 0.709 / 0.710 / 0.710 s; three
-    lanes (8 / 56 / the rest) 0.85-0.88 s; 8 apart by size 1.01 s.
+    """Two independent lanes for an ensemble's global steps (nb_ens_set_lanes): a probe run to
+    t_probe from the initial state (x0, v0) counts every cluster's block steps, and the `top`
+    clusters with the most steps get a lane of their own, so the global step count of the rest no
+    longer follows the cluster with the tightest encounters.  Runs by teams have no global steps
+    and no lanes (nb_ens_took_teams tells; nb_ens_set_teams(0) is global steps).  On MI355X, 512
+    Plummer clusters of 64-4096 particles to t = 1 by global steps (alternated on one machine):
+    0.657-0.658 s against 0.757-0.758 s in one lane; 2 / 8 / 16 / 32 / 64 clusters apart 0.661 /
+    0.683 / 0.709 / 0.710 / 0.710 s; three lanes (8 / 56 / the rest) 0.85-0.88 s; 8 apart by size
+    1.01 s.  By teams the run takes 0.47 s.
     The probe leaves the ensemble re-initialised at (x0, v0).  Returns the lane of each cluster
     (numpy int32) after setting it."""
     import numpy as np

@@ -61,6 +61,7 @@ def _ensemble(sizes, prec, t_end, graph=True, lanes=None, layout=None, split=Non
             ens.nb_ens_set_lanes(lanes)
         ens.nb_ens_init(0.02)
         ens.nb_ens_run(0.02, t_end, steps_per_launch=8, max_steps=max_steps, use_graph=graph)
+        assert ens.nb_ens_took_teams() == (polls > 0 and graph)
         ctl = ens.nb_ens_control()
         e = ens.nb_ens_energy()
     return [(c.n_steps, c.n_active_sum, c.t_cur) for c in ctl], st.numpy(), e, parts
