@@ -464,8 +464,10 @@ nb_status enqueue_force(nb_ctx *c, const Variant &v, int cls, const int32_t *ili
     switch (c->prec) {
         case NB_FP32: {
             ModeF32::Args pa{c->js.px, c->js.py, c->js.pz, c->js.vm, (float)(c->eps * c->eps)};
-            if (helped && soft) force_kernel_helped<ModeF32, true><<<grid, WG, 0, s>>>(pa, fc);
-            else if (helped) force_kernel_helped<ModeF32, false><<<grid, WG, 0, s>>>(pa, fc);
+            if (helped && n_i_dev && soft) force_kernel_helped<ModeF32, true, 7><<<grid, WG, 0, s>>>(pa, fc);
+            else if (helped && n_i_dev) force_kernel_helped<ModeF32, false, 7><<<grid, WG, 0, s>>>(pa, fc);
+            else if (helped && soft) force_kernel_helped<ModeF32, true, 5><<<grid, WG, 0, s>>>(pa, fc);
+            else if (helped) force_kernel_helped<ModeF32, false, 5><<<grid, WG, 0, s>>>(pa, fc);
             else launch_f32(pa, fc, v, soft, cls, grid, s);
             break;
         }
