@@ -66,9 +66,11 @@ __host__ __device__ inline int32_t items_per_cu(int32_t n_i, int32_t S, int32_t 
     const int32_t ls = log2i(S), ib = WG >> ls;
     return (((n_i + ib - 1) >> (log2i(WG) - ls)) * tq + 4095) >> 12;
 }
+// ITEMS false: sp.tq is known to be 0.
+template <bool ITEMS>
 __host__ __device__ inline bool more_slices(int32_t n_i, int32_t S, const Spread &sp) {
     if (S >= sp.most || n_i * S * 2 > sp.fill) return false;
-    if (sp.tq == 0) return true;
+    if (!ITEMS || sp.tq == 0) return true;
     const int32_t now = items_per_cu(n_i, S, sp.tq), then = items_per_cu(n_i, 2 * S, sp.tq);
     return sp.scalar && S > 1 ? then <= 1 : then < 2 * (now > 2 ? now : 2);
 }
@@ -91,6 +93,7 @@ __host__ __device__ inline int32_t pack_lanes(int32_t n_i, int32_t S) {
 }
 
 // Slices S and helper lanes H of each of n_i rows.
+template <bool ITEMS = true>
 __host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, int32_t &H) {
     S = lane_split(n_i, sp.smax, sp.wg);
     H = 1;
@@ -98,7 +101,7 @@ __host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, in
         if (sp.hmax > 1) {
             if (S <= sp.hslices && n_i * S * 4 <= sp.hfill) H = 4;
         } else {
-            while (more_slices(n_i, S, sp)) S *= 2;
+            while (more_slices<ITEMS>(n_i, S, sp)) S *= 2;
         }
     }
     if (sp.pack && n_i > WG) S = pack_lanes(n_i, S);

@@ -21,10 +21,11 @@
 // relaxed agent-scope atomics, which the eight XCDs' L2 caches do not keep, each producer waits
 // for its stores to complete before it stores its word, and each consumer loads after it saw the
 // word.  They meet only once all are resident (roll_call): where other work keeps some of them off
-// the device, all leave before the first step and nb_run goes on by another path.  (Measured on MI355X with 256 workgroups: 2.6 us per meeting; with agent-scope release
-// and acquire fences, which write back and invalidate a whole L2, 19 us, and 62 us with 16 KB of
-// records read after it.)  Every wait gives up after TL_POLLS polls; the run then reports an error
-// and leaves the state as it was before the launch.
+// the device, all leave before the first step and nb_run goes on by another path.  (Measured on
+// MI355X with 256 workgroups: 2.6 us per meeting; with agent-scope release and acquire fences,
+// which write back and invalidate a whole L2, 19 us, and 62 us with 16 KB of records read after
+// it.)  Every wait gives up after TL_POLLS polls; the run then reports an error and leaves the
+// state as it was before the launch.
 //
 // The histogram gives the block time only while every particle's t_i is the last multiple of its
 // step not after the scheduler's time; then a block is never empty, somebody waits for all
@@ -394,13 +395,12 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
                 sum += c4[k];
             }
             const int32_t inc = wave_scan_add(sum);
-            int32_t rows = __builtin_amdgcn_readlane(inc, 63);
-            if (!a.rows.has(rows)) rows = INT32_MAX;
-            const bool taken = tn <= t_end && rows <= a.limit;
+            const int32_t rows = __builtin_amdgcn_readlane(inc, 63);
+            const bool fits = a.rows.has(rows), taken = tn <= t_end && fits;
             if (wave >= 12) {  // the row map, one owner of each lane per wave
                 if (tid == 12 * 64) {
                     plan_t = tn;
-                    plan_rows = rows;
+                    plan_rows = fits ? rows : 0;
                 }
                 int32_t b4[4];
                 b4[0] = inc - sum;
@@ -426,10 +426,10 @@ __global__ void __launch_bounds__(TL_WG) run_tiles(TilesArgs a) {
             break;
         }
         const int32_t n_act = __builtin_amdgcn_readfirstlane(plan_rows);
-        if (n_act > a.limit) break;
+        if (n_act == 0) break;  // not for this path
         // force: i-blocks of WG / L rows against the tile, TL_SUB at a time
         int32_t S, H;
-        row_lanes(n_act, a.sp, S, H);
+        row_lanes<false>(n_act, a.sp, S, H);
         const int32_t L = S * H, ls = 31 - __builtin_clz(L);      // L = 1 << ls
         const int32_t ib = WG >> ls, n_iblk = (n_act + ib - 1) >> (8 - ls);
         const int32_t sub = wave >> 2, tt = tid & (WG - 1);
