@@ -36,7 +36,7 @@ def log(*a):
 def kernel_source_hash():
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hpp", "ds_arith.hpp"):
+    for f in ("kernels.hpp", "plan.hpp", "ds_arith.hpp"):
         with open(os.path.join(ROOT, "paper_astro_ph_0702058_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -154,7 +154,7 @@ def bench_ensemble(args, emit=True):
                      "frac": round(60 * inter / elapsed / 1e12 / PEAK_FP32_TFLOPS, 4),
                      "traffic": None,
                      "basis": "60 flop per interaction over the whole run's wall clock (all "
-                              "kernels; the run is bound by the latency of its global steps)"},
+                              "kernels; the run is bound by the latency of its block steps)"},
     }
     if not args.no_cpu_baseline:
         # the oracle on the same clusters in index order, each for at most 2 s of its own block

@@ -211,14 +211,16 @@ nb_status nb_run(nb_ctx *ctx, double eta, int64_t t_end, int64_t max_steps, int3
  * Sec. 2, the force of Eq. Force on it with every particle predicted as it is staged, the
  * corrector and the new levels of Eq. timestep) up to `chunk` times per launch, instead of a
  * chain of launches per step; the state is written back at the end of each launch.  One
- * workgroup holds up to 512 particles (FP32; 400 in FP64, 256 in double-single), a cooperative
- * launch of one or more per 256 particles the rest.  The same steps up to the summation order;
+ * workgroup holds up to 512 particles (FP32; 400 in FP64, 256 in double-single), a launch of one
+ * or more per 256 particles the rest (nb_set_tiles).  The same steps up to the summation order;
  * call nb_predict before a later nb_force (nb_run need not write the j-particle stream then).
  * NB_EINVAL for max_n outside [0, 1024].
- * Larger contexts, to 65536 particles, take the cooperative launch under the same conditions
- * (max_n > 0, eps > 0, those arithmetics) with use_graph != 0: the same sums as the launch
- * chain's, the j-particle stream written.  A block too large for it takes the chain.  max_n = 0
- * keeps every context on the chain. */
+ * Larger contexts, to 65536 particles, take such a launch, a cooperative one, under the same
+ * conditions (max_n > 0, eps > 0, those arithmetics) with use_graph != 0: the same sums as the
+ * launch chain's, the j-particle stream written.  A block too large for it, or one that the chain
+ * would sum in another order (the block-step variant decides), takes the chain.  Where particles'
+ * times do not fit the scheduler's (calls other than the block steps have moved them), the run goes
+ * on by launches.  max_n = 0 keeps every context on the chain. */
 nb_status nb_set_resident(nb_ctx *ctx, int32_t max_n);
 
 /* How nb_run's launches of several workgroups wait for the device.  Their workgroups meet in every
@@ -235,13 +237,14 @@ nb_status nb_set_tiles(nb_ctx *ctx, int32_t polls);
 
 /* Sec. 4.2 energy diagnostic, synchronising: kinetic sum m v^2 / 2 and softened potential
  * energy -1/2 sum_i sum_{j != i} m_i m_j s^(-1/2), in double precision, of the state predicted
- * to the last completed block time (exact at times where all particles are synchronised).
- * ekin, epot are HOST pointers. */
+ * to the last completed block time (exact at times where all particles are synchronised).  A
+ * particle whose position is not a number is in no pair.  ekin, epot are HOST pointers. */
 nb_status nb_energy(nb_ctx *ctx, double *ekin, double *epot);
 
 /* Copy the device scheduler record to the HOST struct *out (synchronising), and return the
  * latched device error, if any: NB_ENONFINITE, NB_ESTATE from the block selection or
- * NB_EDTMIN, with *out filled in those cases too (its flags say which).  NB_ESTATE without a
+ * NB_EDTMIN, with *out filled in those cases too (its flags say which), or NB_EDEVICE (a tiled
+ * run's workgroups did not meet; no flag), with *out filled.  NB_ESTATE without a
  * bound workspace leaves *out untouched. */
 nb_status nb_read_control(nb_ctx *ctx, nb_control *out);
 

@@ -382,8 +382,9 @@ class Context:
                                     int(bool(use_graph))))
 
     def nb_set_resident(self, max_n):
-        """nb_run on contexts of at most max_n particles keeps the state in LDS, in one resident
-        workgroup or in tiles (0: the chain of launches per step at every size)."""
+        """nb_run on contexts of at most max_n particles keeps the state in LDS: up to 512 (FP32; 400
+        in FP64, 256 in double-single) in one resident workgroup, above in tiles (nb_set_tiles).
+        0: the chain of launches per step at every size."""
         self._check(self.lib.nb_set_resident(self.h, int(max_n)))
 
     def nb_set_tiles(self, polls):
@@ -572,7 +573,8 @@ class Ensemble:
 
     def nb_ens_set_teams(self, polls):
         """Looks (about 1 us each) until all workgroups of a run by teams run at the same time; else
-        global steps take the run.  0: global steps only."""
+        global steps take the run.  From then on teams take every run that they can; 0: none, global
+        steps only."""
         self._check(self.lib.nb_ens_set_teams(self.h, int(polls)))
         self.polls = int(polls)
 

@@ -24,7 +24,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("kernels.hpp", "ds_arith.hpp"):
+    for f in ("kernels.hpp", "plan.hpp", "ds_arith.hpp"):
         with open(os.path.join(ROOT, "paper_astro_ph_0702058_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
