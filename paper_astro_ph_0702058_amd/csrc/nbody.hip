@@ -113,7 +113,7 @@ struct nb_ctx {
     int32_t sched_groups = 1, sched_chunk = 1;
     int32_t fused_groups = 1, fused_chunk = 1;  // chunks of the fused step's count + predict
     int32_t resident_max = 1024;         // nb_run: one resident workgroup up to this n
-    // nb_run above that: one cooperative launch of tile owners (tiles.hpp)
+    // nb_run above that: one launch of tile owners (tiles.hpp)
     bool tiles_ok = true;                // cleared when the device refuses the launch
     BlockRows tiles_rows{0, 0, -1};      // of the present variant (most < 0: to be found)
     Epochs epochs;                       // of its launches
