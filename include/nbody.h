@@ -167,7 +167,7 @@ nb_status nb_force(nb_ctx *ctx, const int32_t *i_idx, const int32_t *n_i, int32_
 /* For callers that cannot allocate device memory or take it from the caller's workspace (code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation): nb_force with
  * the same arguments and bitwise the same results, whose j-split partial sums go to a static
- * device array of 64 MiB per GPU (held from the first nb_create on that GPU until the process
+ * device array of 98 MiB per GPU (held from the first nb_create on that GPU until the process
  * ends) instead of the context's workspace.  Allocates nothing.  NB_EINVAL, before anything is
  * enqueued, if the call's j-split needs more than the array holds (7 doubles per partial row;
  * with a device count the largest count up to n_i_max is assumed): all block-step lists fit at

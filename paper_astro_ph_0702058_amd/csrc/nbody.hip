@@ -32,7 +32,9 @@ using namespace nbody;
 // the device (the array's name is a host-side stand-in there).
 // ------------------------------------------------------------------------------------------
 namespace {
-constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)64 << 20;
+// the most partial sums of a block-step list in the sets that tiles hold: 28 i-blocks on 256 planes
+constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)98 << 20;
+static_assert((size_t)TL_TILES * TL_LONG * 7 * sizeof(double) <= NOALLOC_SCRATCH_BYTES, "block-step lists");
 constexpr int NOALLOC_MAX_DEVICES = 64;
 static __device__ __align__(256) char scratch[NOALLOC_SCRATCH_BYTES];
 std::mutex noalloc_mu;
