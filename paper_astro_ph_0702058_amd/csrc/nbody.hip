@@ -285,12 +285,6 @@ Variant default_variant(int32_t n, int prec, int num_cu, bool block) {
     v.ipl = 1;
     v.unroll = 2;
     v.target = num_cu * (block ? BLOCK_ITEMS_PER_CU : FULL_ITEMS_PER_CU);
-    // of the largest sets that tiles hold, so many items that the blocks which tiled runs take
-    // (tiles_rows) have every tile in a plane of its own: the chain sums them in the tiles' order
-    // (lists of N = 40000 - 65536 at 16 items per CU and so: within 1 % up to 20000 rows, 3.5 % faster
-    // to 4 % slower past that; the N = 65536 run's blocks of 4097 - 7168 rows stay in its tiles)
-    const int32_t T = (n + TJ - 1) / TJ;
-    if (block && T <= TL_TILES) v.target = std::max(v.target, T * (TL_LONG / WG));
     v.kmax = block ? 1 << 16 : FULL_KMAX;  // K is also bounded by the tile count
     // scalar j-loads from 1 tile per item in full-force calls and from 4 in block steps
     // (interleaved runs on one MI355X against 16 tiles: the shared-step gradient at N = 16384,
@@ -389,11 +383,22 @@ void launch_fixed(const ModeF32Fixed::Args &pa, const ForceCommon &fc, const Var
 // Largest lane split of a precision's force kernel (fixed-point sums: whole 64-j sub-blocks).
 int32_t smax_of(int prec) { return prec == NB_FP32_FIXED ? TJ / ModeTraits<ModeF32Fixed>::FOLD : 64; }
 
+// Rows up to which a launch has a plane per tile (Spread::whole): with the block-step default, in the
+// sets and arithmetics that tiled runs take.  At its target alone the chain would join tiles of 4097
+// to 7168 rows at 256 tiles, and in FP64 and double-single of 2049 to 3840 rows from 69 on, and tiled
+// runs leave such blocks to it: N = 65536 FP32 to t = 1/64 43.1 and 42.1 ms, FP64 40000 to 1/128 13.5
+// and 12.4 ms.
+int32_t whole_rows(int32_t n, int prec, int32_t num_cu, const Variant &v) {
+    const int32_t T = (n + TJ - 1) / TJ;
+    return T <= TL_TILES && (prec == NB_FP32 || prec == NB_DS || prec == NB_FP64) && v.ipl == 1 &&
+           v.target == num_cu * BLOCK_ITEMS_PER_CU && v.kmax >= T ? LONG_LIST : 0;
+}
+
 // How the lists of a precision and variant spread over lanes on small launches: four waves per
 // SIMD fill the chip.  The float tile sums of FP32 keep their order (helper lanes, with the
 // default shape of the kernel), the paper's all-single sums have no helpers, and the other
 // arithmetics take more slices.
-Spread spread_of(const nb_ctx *c, const Variant &v) {
+Spread lanes_of(const nb_ctx *c, const Variant &v) {
     const int32_t T = (c->n + TJ - 1) / TJ, fill = c->num_cu * 1024 / T;
     if (c->prec == NB_FP32) {
         if (v.ipl != 1 || v.unroll != 2) return Spread{64, 1, 0};
@@ -414,15 +419,23 @@ Spread spread_of(const nb_ctx *c, const Variant &v) {
     return sp;
 }
 
+Spread spread_of(const nb_ctx *c, const Variant &v) {
+    Spread sp = lanes_of(c, v);
+    sp.whole = whole_rows(c->n, c->prec, c->num_cu, v);
+    return sp;
+}
+
 // Largest K * P over every i-count up to n_i_max against n j-particles, for one variant (the
 // plan depends on the count only through its number of i-blocks, and lists shorter than a
 // workgroup have the one i-block's K with fewer rows).
-int64_t partial_rows_upto(int32_t n_i_max, int32_t n, const Variant &v, int32_t smax) {
+int64_t partial_rows_upto(int32_t n_i_max, int32_t n, const Variant &v, int32_t smax, int32_t whole = 0) {
     const int32_t ib = WG * v.ipl;
+    Spread sp{smax, 1, 0};
+    sp.whole = whole;
     int64_t rows = 0;
     for (int32_t nb = 1; nb <= (n_i_max + ib - 1) / ib; ++nb) {
         const ForcePlan pl = make_plan((int32_t)std::min<int64_t>((int64_t)nb * ib, n_i_max), n,
-                                       ib, v.target, v.kmax, Spread{smax, 1, 0});
+                                       ib, v.target, v.kmax, sp);
         if (pl.K > 1) rows = std::max<int64_t>(rows, (int64_t)pl.K * pl.P);
         if (pl.K == 1) break;  // K only falls as the number of i-blocks grows
     }
@@ -649,8 +662,7 @@ Spread tiles_spread(const nb_ctx *c) {
 // the partial planes, held twice, hold (past 64 tiles TL_LONG rows: larger blocks are the chain's,
 // which uses every compute unit); and beyond the sets that a resident workgroup could hold, only
 // blocks that the chain sums in the same order, so that a run's result does not depend on where its
-// launches are cut: at the default targets the chain joins tiles past 7168 rows at 256 tiles, and
-// from 2049 to 3840 rows in FP64 and double-single at 130.  Found once per variant (0.4 ms).
+// launches are cut (the default's are all, whole_rows).  Found once per variant (0.4 ms).
 BlockRows tiles_rows(nb_ctx *c) {
     if (c->tiles_rows.most >= 0) return c->tiles_rows;
     const int64_t T = (c->n + TJ - 1) / TJ;
@@ -765,9 +777,8 @@ void ctx_plan(nb_ctx *c) {
         // scalar-load threshold does not change the plan
         rows = std::max(rows, partial_rows_for(n, Variant{ipl, 1, c->num_cu * FULL_ITEMS_PER_CU / ipl,
                                                           FULL_KMAX, 1}, smax_of(precision)));
-        rows = std::max(rows, partial_rows_for(n, Variant{ipl, 1, ipl == 1 ? c->var_block.target
-                                                                            : c->num_cu * BLOCK_ITEMS_PER_CU,
-                                                          1 << 16, 1}, smax_of(precision)));
+        const Variant v{ipl, 1, c->num_cu * BLOCK_ITEMS_PER_CU, 1 << 16, 1};
+        rows = std::max(rows, partial_rows_upto(n, n, v, smax_of(precision), whole_rows(n, precision, c->num_cu, v)));
     }
     // the force VJP writes K * P rows of its plan even when K = 1
     {
@@ -1027,9 +1038,11 @@ nb_status nb_force_noalloc(nb_ctx *c, const int32_t *i_idx, const int32_t *n_i,
     // partial-sum rows of this call's plan (for a device count: of the largest count it allows)
     int64_t rows = 0;
     if (n_i) {
-        rows = partial_rows_upto(n_i_max, c->n, v, smax);
+        rows = partial_rows_upto(n_i_max, c->n, v, smax, whole_rows(c->n, c->prec, c->num_cu, v));
     } else {
-        const ForcePlan pl = make_plan(n_i_max, c->n, WG * v.ipl, v.target, v.kmax, Spread{smax, 1, 0});
+        Spread sp{smax, 1, 0};
+        sp.whole = whole_rows(c->n, c->prec, c->num_cu, v);
+        const ForcePlan pl = make_plan(n_i_max, c->n, WG * v.ipl, v.target, v.kmax, sp);
         rows = pl.K > 1 ? (int64_t)pl.K * pl.P : 0;
     }
     const size_t bytes = (size_t)rows * 7 * sizeof(double);

@@ -9,6 +9,7 @@ namespace nbody {
 
 constexpr int WG = 256;      // work-items per workgroup
 constexpr int TJ = 256;      // j-particles per tile (LDS tile of the lane split; fold interval)
+constexpr int LONG_LIST = 7168;  // most rows of a block in tiled runs past 64 tiles
 
 // ------------------------------------------------------------------------------------------
 // Work decomposition of one force call, computed identically on host and device from the
@@ -59,6 +60,9 @@ struct Spread {
     int32_t most = 64;
     int32_t tq = 0;      // tiles per compute unit in 1/4096 (0: not looked at)
     int32_t scalar = 0;
+    // Lists of up to so many rows sum every tile in a plane of its own, whatever the target: the blocks
+    // that tiled runs take, whose order of sums that is.
+    int32_t whole = 0;
 };
 
 // Items of n_i rows in S slices that the busiest compute unit gets.
@@ -124,6 +128,7 @@ __host__ __device__ inline ForcePlan make_plan(int32_t n_i, int32_t n, int32_t i
     p.ib = ib;
     p.n_iblk = (n_i + ib - 1) >> log2i(ib);
     int32_t K = p.n_iblk > 0 ? target / p.n_iblk : 1;
+    if (n_i <= sp.whole) K = p.ntiles;
     if (K > kmax) K = kmax;
     if (K > p.ntiles) K = p.ntiles;
     if (K < 1) K = 1;

@@ -7,7 +7,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-# argv: n, target, kmax, ib_max, smax, hmax, fill, pack.  Prints the lengths of blocks that tiles
+# argv: n, target, kmax, ib_max, smax, hmax, fill, pack [, whole].  Prints the lengths of blocks that tiles
 # take, and those up to 8192 that are taken although the chain's plan joins tiles (none).
 SOURCE = r"""
 #include "plan.hpp"
@@ -20,6 +20,7 @@ int main(int argc, char **argv) {
     Spread sp{v[5], v[6], v[7], WG, v[8]};
     sp.hfill = v[6] > 1 ? v[7] / 2 : 0;
     const int32_t T = (v[1] + TJ - 1) / TJ, most = 8192;
+    if (argc > 9) sp.whole = atoi(argv[9]);
     const BlockRows rows = rows_by_tiles(v[1], v[4], v[2], v[3], sp, sp, most);
     printf("%d %d %d", rows.lo, rows.hi, rows.most);
     for (int32_t m = 1; m <= most; ++m) {
@@ -52,17 +53,15 @@ def limits(tmp_path_factory):
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 @pytest.mark.parametrize("n", [1025, 5000, 16384, 16385, 33023, 50000, 65536])
 def test_tiled_blocks_join_no_tiles(limits, n, prec):
-    """At 256 compute units and the default targets, where no block that tiles take has joined ones:
-    all up to a limit, but for the lengths of several i-blocks that take more slices."""
-    fill = 256 * 1024 // ((n + 255) // 256)
-    spread = (64, 4, fill, 0) if prec == "fp32" else (64, 1, fill, 1)
+    """At 256 compute units the default gives every block that tiles take a plane per tile; its target
+    alone joins tiles of some lengths."""
     tiles = (n + 255) // 256
-    lo, hi, most = limits(n, max(4096, 28 * tiles), 1 << 16, 256, *spread)
-    assert most == {33023: 31 * 256, 50000: 7168, 65536: 7168}.get(n, 8192)
-    if prec == "fp32":
-        assert lo == most
-    else:
-        assert lo == most or 1024 <= lo < hi < 4096
+    fill = 256 * 1024 // tiles
+    spread = (64, 4, fill, 0) if prec == "fp32" else (64, 1, fill, 1)
+    lo, hi, most = limits(n, 4096, 1 << 16, 256, *spread, 7168)
+    assert lo == most == {33023: 31 * 256, 50000: 7168, 65536: 7168}.get(n, 8192)
+    lo, hi, most = limits(n, 4096, 1 << 16, 256, *spread)
+    assert lo == most or (prec == "fp64" and 1024 <= lo < hi < 4096)
 
 
 @pytest.mark.parametrize("target,kmax,ib", [(1024, 1 << 16, 256), (4096, 8, 256), (4096, 1 << 16, 512), (64, 64, 1024)])
@@ -92,8 +91,10 @@ int main(int, char **argv) {
     int bad = 0;
     for (int k = 0; k < 5; ++k)
         for (int32_t m = 1; m <= n; m += m < 20000 ? 1 : 977) {
+            Spread held_by{all[k].smax, 1, 0};
+            held_by.whole = all[k].whole = T <= 256 && target == 4096 && kmax >= T && k != 4 ? LONG_LIST : 0;
             const ForcePlan p = make_plan(m, n, WG, target, kmax, all[k]);
-            const ForcePlan q = make_plan(m, n, WG, target, kmax, Spread{all[k].smax, 1, 0});
+            const ForcePlan q = make_plan(m, n, WG, target, kmax, held_by);
             const int64_t need = p.K > 1 ? p.K * p.P : 0, held = q.K > 1 ? q.K * q.P : 0;
             const bool whole = (int64_t)p.K * p.tps >= p.ntiles && (int64_t)p.n_iblk * p.ib >= m &&
                                p.items == p.n_iblk * p.K && p.ib * p.S * p.H == WG;
