@@ -1009,12 +1009,11 @@ __global__ void __launch_bounds__(WG) force_kernel(typename M::Args pa, ForceCom
 
 // The same with helper lanes for short lists.  A kernel of its own: the helpers' registers (87
 // instead of 71) cost the whole-block path two of its seven waves per SIMD (1.4 % of a gradient
-// at N = 16384), so only launches whose plans may take helpers use it: with five waves per SIMD where
-// the plan takes them (half the chip at most), with seven where the count is the device's and may be
-// that of a long list (prediction and force of all rows, with five and with seven: N = 300 18.1 and
-// 18.9 us, 1024 18.9 and 19.3, 2000 19.2 and 20.7).
-template <class M, bool SOFT, int WAVES>
-__global__ void __launch_bounds__(WG, WAVES) force_kernel_helped(typename M::Args pa, ForceCommon fc) {
+// at N = 16384), so only launches whose plans may take helpers use it.  (At seven waves per SIMD nine
+// of them spill: all rows of N = 2000 20.7 us for 19.2, 200 of 20000 26.7 for 25.0, and 1253 of 65536
+// 77.5 for 77.2.)
+template <class M, bool SOFT>
+__global__ void __launch_bounds__(WG) force_kernel_helped(typename M::Args pa, ForceCommon fc) {
     __shared__ typename M::Smem sm;
     force_items<M, 1, 2, SOFT, true>(pa, fc, sm);
 }

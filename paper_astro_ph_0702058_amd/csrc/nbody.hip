@@ -400,10 +400,13 @@ int32_t whole_rows(int32_t n, int prec, int32_t num_cu, const Variant &v) {
 // arithmetics take more slices.
 Spread lanes_of(const nb_ctx *c, const Variant &v) {
     const int32_t T = (c->n + TJ - 1) / TJ, fill = c->num_cu * 1024 / T;
+    const int32_t tq = (int32_t)(((int64_t)T * 4096 + c->num_cu - 1) / c->num_cu);
     if (c->prec == NB_FP32) {
-        if (v.ipl != 1 || v.unroll != 2) return Spread{64, 1, 0};
+        // (a list with helpers has three i-blocks at least, too many items for any to gain past that)
+        if (v.ipl != 1 || v.unroll != 2 || 3 * T > 4 * c->num_cu) return Spread{64, 1, 0};
         Spread sp{64, 4, fill};
-        sp.hfill = fill / 2;
+        sp.hfill = fill;
+        sp.tq = tq;
         return sp;
     }
     if (c->prec == NB_FP32_ALL) return Spread{64, 1, 0};
@@ -413,7 +416,7 @@ Spread lanes_of(const nb_ctx *c, const Variant &v) {
     // sets that tiles may hold keep the most slices, a block's in tiled runs too
     if (fixed || T > TL_TILES) {
         sp.most = std::min(sp.smax, c->prec == NB_FP64 ? 8 : 32);
-        sp.tq = (int32_t)(((int64_t)T * 4096 + c->num_cu - 1) / c->num_cu);
+        sp.tq = tq;
         sp.scalar = fixed;
     }
     return sp;
@@ -460,9 +463,8 @@ nb_status enqueue_force(nb_ctx *c, const Variant &v, int cls, const int32_t *ili
     int32_t grid;
     bool helped;  // the plan takes helper lanes, or for a device count may take them
     if (n_i_dev) {
-        // the count is known only on the device: enough workgroups for any count up to n_i_max;
-        // 129 rows in one slice, 65 in two ... are the fewest lanes that a list with helpers has
-        helped = sp.hmax > 1 && sp.hfill > 4 * WG / 2;
+        // the count is known only on the device: enough workgroups for any count up to n_i_max
+        helped = sp.hmax > 1;
         grid = std::max(std::max(1, v.target), std::min(fc.pl.items, 65535));
         // but in sets of few tiles no more than 16 a compute unit, which then take several items each:
         // a workgroup without any forms its plan too (N = 65536, all-single, blocks of 58 rows: 29.6 us
@@ -483,10 +485,8 @@ nb_status enqueue_force(nb_ctx *c, const Variant &v, int cls, const int32_t *ili
     switch (c->prec) {
         case NB_FP32: {
             ModeF32::Args pa{c->js.px, c->js.py, c->js.pz, c->js.vm, (float)(c->eps * c->eps)};
-            if (helped && n_i_dev && soft) force_kernel_helped<ModeF32, true, 7><<<grid, WG, 0, s>>>(pa, fc);
-            else if (helped && n_i_dev) force_kernel_helped<ModeF32, false, 7><<<grid, WG, 0, s>>>(pa, fc);
-            else if (helped && soft) force_kernel_helped<ModeF32, true, 5><<<grid, WG, 0, s>>>(pa, fc);
-            else if (helped) force_kernel_helped<ModeF32, false, 5><<<grid, WG, 0, s>>>(pa, fc);
+            if (helped && soft) force_kernel_helped<ModeF32, true><<<grid, WG, 0, s>>>(pa, fc);
+            else if (helped) force_kernel_helped<ModeF32, false><<<grid, WG, 0, s>>>(pa, fc);
             else launch_f32(pa, fc, v, soft, cls, grid, s);
             break;
         }
@@ -651,6 +651,7 @@ Spread tiles_spread(const nb_ctx *c) {
     Spread sp = spread_of(c, Variant{1, 2, 0, 0, 0});
     sp.hslices = 16;  // helpers wherever they fit: the tile is staged once
     sp.hfill = sp.fill;
+    sp.tq = 0;
     if (c->n <= RES_MAX) {  // the slices of the resident workgroup
         sp.wg = WGL;
         sp.pack = 0;

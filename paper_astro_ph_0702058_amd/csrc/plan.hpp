@@ -47,9 +47,11 @@ struct Spread {
     int32_t fill;     // lanes per tile that fill the chip (0: lane_split alone)
     int32_t wg = WG;  // lanes that lane_split spreads over a list
     int32_t pack = 0; // lists longer than a workgroup take slices that leave less padding
-    // Helpers double the instructions of a pair: a list takes them where they fill half the chip at
-    // most and a slice has 32 j-slots or more.  At the whole chip 600 rows of 20000 took 35 us for
-    // 31, 10 rows of 100000, 16 slices of one row each, 22 for 16.
+    // Helpers double the instructions of a pair: a list takes them where a slice has 32 j-slots or
+    // more and (tq) the busiest compute unit gets no more than three items, or four where it gets two
+    // without them.  With and without: 600 rows of 20000 (4 items, 1 without) 37.7 and 34.0 us, 700 of
+    // 16384 (3, 1) 31.9 and 33.6, 300 of 50000 (4, 2) 39.5 and 41.7; 10 of 100000, 16 slices of one
+    // row each, 22 and 16.
     int32_t hslices = 8, hfill = 0;
     // More slices for a list: `most` of them, and (tq) only where they spread the work: an item
     // has half the pairs of one before, so twice the items on the busiest compute unit are no gain
@@ -69,6 +71,10 @@ struct Spread {
 __host__ __device__ inline int32_t items_per_cu(int32_t n_i, int32_t S, int32_t tq) {
     const int32_t ls = log2i(S), ib = WG >> ls;
     return (((n_i + ib - 1) >> (log2i(WG) - ls)) * tq + 4095) >> 12;
+}
+__host__ __device__ inline bool helpers_pay(int32_t n_i, int32_t S, int32_t tq) {
+    const int32_t with = items_per_cu(n_i, 4 * S, tq);
+    return with <= 3 || (with == 4 && items_per_cu(n_i, S, tq) >= 2);
 }
 // ITEMS false: sp.tq is known to be 0.
 template <bool ITEMS>
@@ -103,7 +109,7 @@ __host__ __device__ inline void row_lanes(int32_t n_i, Spread sp, int32_t &S, in
     H = 1;
     if (n_i <= sp.fill) {  // also keeps the products below in range
         if (sp.hmax > 1) {
-            if (S <= sp.hslices && n_i * S * 4 <= sp.hfill) H = 4;
+            if (S <= sp.hslices && n_i * S * 4 <= sp.hfill && (!ITEMS || helpers_pay(n_i, S, sp.tq))) H = 4;
         } else {
             while (more_slices<ITEMS>(n_i, S, sp)) S *= 2;
         }

@@ -18,8 +18,9 @@ int main(int argc, char **argv) {
     int32_t v[9];
     for (int i = 1; i < 9; ++i) v[i] = atoi(argv[i]);
     Spread sp{v[5], v[6], v[7], WG, v[8]};
-    sp.hfill = v[6] > 1 ? v[7] / 2 : 0;
     const int32_t T = (v[1] + TJ - 1) / TJ, most = 8192;
+    sp.hfill = v[6] > 1 ? v[7] : 0;
+    sp.tq = v[6] > 1 ? 16 * T : 0;
     if (argc > 9) sp.whole = atoi(argv[9]);
     const BlockRows rows = rows_by_tiles(v[1], v[4], v[2], v[3], sp, sp, most);
     printf("%d %d %d", rows.lo, rows.hi, rows.most);
@@ -84,7 +85,7 @@ int main(int, char **argv) {
     const int32_t T = (n + TJ - 1) / TJ, fill = 256 * 1024 / T, tq = (int32_t)(((int64_t)T * 4096 + 255) / 256);
     Spread all[5] = {Spread{64, 4, fill}, Spread{64, 1, fill, WG, 1}, Spread{64, 1, fill, WG, 1},
                      Spread{64, 1, fill, WG, 1}, Spread{4, 1, fill}};
-    all[0].hfill = fill / 2;
+    all[0].hfill = fill; all[0].tq = tq;
     all[2].most = 8; all[2].tq = tq;
     all[3].most = 32; all[3].tq = tq;
     all[4].most = 4; all[4].tq = tq; all[4].scalar = 1;
