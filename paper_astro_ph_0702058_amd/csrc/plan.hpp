@@ -59,6 +59,9 @@ struct Spread {
     // second doubling of its lanes, 250 of 20000 (316, then 632) 52 for 59.  `scalar`: arithmetics
     // that leave their scalar j-loads with the first doubling; a second one pays only while no
     // compute unit has two items (fixed point, 400 rows: of 8000 17 us for 22, of 20000 31 for 27).
+    // The others also look two doublings ahead (DS 40 of 100000, 2, 4 and 5 items: 52 us for 61), and
+    // half the pairs on twice two items, four waves a SIMD, gain where a slice is long (DS 200 of
+    // 100000 188 us for 200).
     int32_t most = 64;
     int32_t tq = 0;      // tiles per compute unit in 1/4096 (0: not looked at)
     int32_t scalar = 0;
@@ -82,7 +85,12 @@ __host__ __device__ inline bool more_slices(int32_t n_i, int32_t S, const Spread
     if (S >= sp.most || n_i * S * 2 > sp.fill) return false;
     if (!ITEMS || sp.tq == 0) return true;
     const int32_t now = items_per_cu(n_i, S, sp.tq), then = items_per_cu(n_i, 2 * S, sp.tq);
-    return sp.scalar && S > 1 ? then <= 1 : then < 2 * (now > 2 ? now : 2);
+    if (sp.scalar && S > 1) return then <= 1;
+    const int32_t busy = now > 2 ? now : 2;
+    if (then < 2 * busy) return true;
+    if (sp.scalar) return false;
+    if (S <= 2 && now == 2) return true;
+    return S * 4 <= sp.most && n_i * S * 4 <= sp.fill && items_per_cu(n_i, 4 * S, sp.tq) < 4 * busy;
 }
 
 // Slices of a list longer than a workgroup that takes S: more, up to 4, where the i-blocks of
