@@ -823,7 +823,11 @@ __device__ void force_items_split(const typename M::Args &pa, const ForceCommon 
             tile_sums<M, UNR, SOFT, HELP>(ii, sm, slice, Sl, H, rel, eps2, S);
         }
         lanes_add<M>(S, L, H);
-        if (((int32_t)threadIdx.x & (L - 1)) == 0 && q < n_i) store_result<M>(fc, pl, ks, q, S);
+        // the row formed again: held through the sums it costs fixed point its fifth wave per SIMD
+        int32_t first = iblk * pl.ib;
+        if (ModeTraits<M>::FIXED) asm volatile("" : "+s"(first));
+        const int32_t r = first + ((int32_t)threadIdx.x >> ls);
+        if (((int32_t)threadIdx.x & (L - 1)) == 0 && r < n_i) store_result<M>(fc, pl, ks, r, S);
     }
 }
 
