@@ -34,7 +34,7 @@ using namespace nbody;
 namespace {
 // the most partial sums of a block-step list in the sets that tiles hold: 28 i-blocks on 256 planes
 constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)98 << 20;
-static_assert((size_t)TL_TILES * TL_LONG * 7 * sizeof(double) <= NOALLOC_SCRATCH_BYTES, "block-step lists");
+static_assert((size_t)TL_TILES * LONG_LIST * 7 * sizeof(double) <= NOALLOC_SCRATCH_BYTES, "block-step lists");
 constexpr int NOALLOC_MAX_DEVICES = 64;
 static __device__ __align__(256) char scratch[NOALLOC_SCRATCH_BYTES];
 std::mutex noalloc_mu;
@@ -660,15 +660,14 @@ Spread tiles_spread(const nb_ctx *c) {
 }
 
 // Rows of the blocks that tiles take; others go to the chain.  At most what the row map in LDS and
-// the partial planes, held twice, hold (past 64 tiles TL_LONG rows: larger blocks are the chain's,
-// which uses every compute unit); and beyond the sets that a resident workgroup could hold, only
+// the partial planes, held twice, hold (past 64 tiles 7/8 of it: larger blocks are the chain's, which
+// uses every compute unit); and beyond the sets that a resident workgroup could hold, only
 // blocks that the chain sums in the same order, so that a run's result does not depend on where its
 // launches are cut (the default's are all, whole_rows).  Found once per variant (0.4 ms).
 BlockRows tiles_rows(nb_ctx *c) {
     if (c->tiles_rows.most >= 0) return c->tiles_rows;
     const int64_t T = (c->n + TJ - 1) / TJ;
-    const int32_t most = (int32_t)std::min<int64_t>(c->partial_rows * (T > 64 ? 7 : 8) / (16 * T),
-                                                    T > 64 ? TL_LONG : TL_ROWS);
+    const int32_t most = (int32_t)std::min<int64_t>(c->partial_rows * (T > 64 ? 7 : 8) / (16 * T), TL_ROWS);
     const Variant &v = c->var_block;
     c->tiles_rows = c->n <= RES_MAX ? BlockRows{most, most, most}
                   : rows_by_tiles(c->n, WG * v.ipl, v.target, v.kmax, spread_of(c, v), tiles_spread(c), most);

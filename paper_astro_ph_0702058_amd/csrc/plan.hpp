@@ -9,7 +9,7 @@ namespace nbody {
 
 constexpr int WG = 256;      // work-items per workgroup
 constexpr int TJ = 256;      // j-particles per tile (LDS tile of the lane split; fold interval)
-constexpr int LONG_LIST = 7168;  // most rows of a block in tiled runs past 64 tiles
+constexpr int LONG_LIST = 7168;  // rows up to which block-step lists have a plane per tile (Spread::whole)
 
 // ------------------------------------------------------------------------------------------
 // Work decomposition of one force call, computed identically on host and device from the

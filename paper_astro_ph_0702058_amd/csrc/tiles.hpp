@@ -58,7 +58,6 @@ constexpr int TL_SUB = TL_WG / WG;   // force items a workgroup works on at a ti
 constexpr int TL_TILES = 256;        // most tiles (one workgroup per compute unit)
 constexpr int TL_REPS = 16;          // most workgroups per tile
 constexpr int TL_ROWS = 8192;        // most block rows of a step (row map in LDS)
-constexpr int TL_LONG = LONG_LIST;   // the same past 64 tiles
 constexpr int TL_WORDS = 8;          // doubles of a published record
 constexpr int TL_SUMS = 7;           // doubles of a row's partial sums
 constexpr uint32_t TL_POLLS = 1u << 24;  // about a quarter of a minute
